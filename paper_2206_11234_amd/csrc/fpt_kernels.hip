@@ -460,101 +460,208 @@ __device__ __forceinline__ int inst_of_row(const MergeInst *mi, int n_inst, uint
     return lo;
 }
 
-__global__ __launch_bounds__(256) void fpt_merge_kernel(MergeArgs a) {
-    const uint32_t tid = blockIdx.x * blockDim.x + threadIdx.x;
+// Running log-sum-exp as (m, s) = (max, sum of e^(x - m)): one exponential per term and one
+// logarithm at the end.  -inf terms add nothing; +inf and NaN carry through as in lse2.
+struct LseAcc {
+    double m = -INFINITY, s = 0.0;
+    __device__ __forceinline__ void add(double x) { fold(x, 1.0); }
+    __device__ __forceinline__ void fold(double xm, double xs) {
+        if (__builtin_isinf(xm) && xm < 0) return;
+        if (xm <= m) {
+            s += xs * exp(xm - m);
+        } else {
+            s = s * exp(m - xm) + xs;
+            m = xm;
+        }
+    }
+    __device__ __forceinline__ double value() const {
+        return (__builtin_isinf(m) && m < 0) ? m : m + log(s);
+    }
+};
+
+// Power sums of x about c: n values, S_j = sum (x - c)^j.
+struct PowerSums {
+    double c = NAN, n = 0.0, S1 = 0.0, S2 = 0.0, S3 = 0.0, S4 = 0.0;
+    // add sums of nw values taken about cw: sum (x - c)^j = sum ((x - cw) + d)^j
+    __device__ __forceinline__ void fold(double cw, double nw, double s1, double s2, double s3, double s4) {
+        if (nw == 0.0) return;
+        if (isnan(c)) c = cw;
+        const double d = cw - c;
+        S4 += s4 + 4.0 * d * s3 + 6.0 * d * d * s2 + 4.0 * d * d * d * s1 + nw * d * d * d * d;
+        S3 += s3 + 3.0 * d * s2 + 3.0 * d * d * s1 + nw * d * d * d;
+        S2 += s2 + 2.0 * d * s1 + nw * d * d;
+        S1 += s1 + nw * d;
+        n += nw;
+    }
+};
+
+// Merge: MERGE_CELLS table cells by MERGE_SPLIT slice ranges per workgroup.  Bound by the reads of
+// the slices where tables are large, by the chain of exponentials over the slices where they are
+// small: with one thread per cell that chain was n_wg log-sum-exp updates long and took 0.5 ms
+// (512 workgroups, 104 rows) to 6.3 ms (1024 workgroups, 164 rows, all cells in use).  Split over
+// MERGE_SPLIT threads per cell, each folding slices w, w + MERGE_SPLIT, ... with one exponential
+// apiece, and a tree over the threads in LDS.  32 neighbouring cells read 256 consecutive bytes of
+// a slice.  The order of the sums is fixed by the launch shape.
+constexpr int MERGE_CELLS = 32, MERGE_SPLIT = 16, MERGE_BLOCK = MERGE_CELLS * MERGE_SPLIT;
+
+__device__ __forceinline__ uint32_t merge_blocks(uint32_t cells) { return (cells + MERGE_CELLS - 1) / MERGE_CELLS; }
+
+__global__ __launch_bounds__(MERGE_BLOCK) void fpt_merge_kernel(MergeArgs a) {
+    __shared__ double red[7][MERGE_BLOCK];
     const TableLayout &L = a.lay;
     const uint32_t RT = L.n_rows, J = L.n_sub;
-    if (tid < J * RT) {
-        const uint32_t s = tid / RT, r = tid % RT;
-        uint64_t cnt = 0;
-        double l = -INFINITY;
-        for (int w = 0; w < a.n_wg; ++w) {
-            const unsigned char *sl = a.slices + static_cast<size_t>(w) * L.slice_bytes;
-            cnt += reinterpret_cast<const uint32_t *>(sl + L.off_cnt)[s * RT + r];
-            l = lse2(l, reinterpret_cast<const double *>(sl + L.off_jk_lse)[s * RT + r]);
+    const uint32_t n_cell_blocks = merge_blocks(J * RT), n_row_blocks = merge_blocks(RT);
+    const int tid = threadIdx.x;
+    const uint32_t lc = tid % MERGE_CELLS;
+    const int part = tid / MERGE_CELLS;
+    if (blockIdx.x < n_cell_blocks) {
+        // counts and log-sums of w per (subset, row)
+        const uint32_t cell = blockIdx.x * MERGE_CELLS + lc;
+        const bool have = cell < J * RT;
+        LseAcc l;
+        unsigned long long cnt = 0;
+        if (have)
+            for (int w = part; w < a.n_wg; w += MERGE_SPLIT) {
+                const unsigned char *sl = a.slices + static_cast<size_t>(w) * L.slice_bytes;
+                cnt += reinterpret_cast<const uint32_t *>(sl + L.off_cnt)[cell];
+                l.add(reinterpret_cast<const double *>(sl + L.off_jk_lse)[cell]);
+            }
+        for (int half = MERGE_SPLIT / 2; half >= 1; half >>= 1) {
+            red[0][tid] = l.m;
+            red[1][tid] = l.s;
+            red[2][tid] = __longlong_as_double(static_cast<long long>(cnt));
+            __syncthreads();
+            if (part < half) {
+                const int o = tid + half * MERGE_CELLS;
+                l.fold(red[0][o], red[1][o]);
+                cnt += static_cast<unsigned long long>(__double_as_longlong(red[2][o]));
+            }
+            __syncthreads();
         }
-        const int i = inst_of_row(a.mi, a.n_inst, r);
-        const MergeInst m = a.mi[i];
-        const uint32_t lr = r - m.row_base;
-        const ResultLayout RL = result_layout(m.n_bins, J);
-        a.counts[m.counts_off + RL.jk_count + static_cast<uint64_t>(s) * m.n_rows + lr] = cnt;
-        a.values[m.values_off + RL.jk_lse_w + static_cast<uint64_t>(s) * m.n_rows + lr] = l;
-    } else if (tid < J * RT + RT) {
-        const uint32_t r = tid - J * RT;
-        double l2 = -INFINITY;
-        double c = NAN;
-        double n = 0.0, S1 = 0.0, S2 = 0.0, S3 = 0.0, S4 = 0.0;
-        for (int w = 0; w < a.n_wg; ++w) {
-            const unsigned char *sl = a.slices + static_cast<size_t>(w) * L.slice_bytes;
-            l2 = lse2(l2, reinterpret_cast<const double *>(sl + L.off_lse_w2)[r]);
-            const double cw = reinterpret_cast<const double *>(sl + L.off_shift)[r];
-            if (isnan(cw)) continue;
-            double nw = 0.0;
-            for (uint32_t s = 0; s < J; ++s)
-                nw += static_cast<double>(reinterpret_cast<const uint32_t *>(sl + L.off_cnt)[s * RT + r]);
-            if (nw == 0.0) continue;
-            if (isnan(c)) c = cw;
-            const double d = cw - c;
-            const double s1 = reinterpret_cast<const double *>(sl + L.off_s1)[r];
-            const double s2 = reinterpret_cast<const double *>(sl + L.off_s2)[r];
-            const double s3 = reinterpret_cast<const double *>(sl + L.off_s3)[r];
-            const double s4 = reinterpret_cast<const double *>(sl + L.off_s4)[r];
-            // sum (x - c)^j = sum ((x - cw) + d)^j
-            S4 += s4 + 4.0 * d * s3 + 6.0 * d * d * s2 + 4.0 * d * d * d * s1 + nw * d * d * d * d;
-            S3 += s3 + 3.0 * d * s2 + 3.0 * d * d * s1 + nw * d * d * d;
-            S2 += s2 + 2.0 * d * s1 + nw * d * d;
-            S1 += s1 + nw * d;
-            n += nw;
+        if (have && part == 0) {
+            const uint32_t s = cell / RT, r = cell % RT;
+            const MergeInst m = a.mi[inst_of_row(a.mi, a.n_inst, r)];
+            const ResultLayout RL = result_layout(m.n_bins, J);
+            const uint64_t at = static_cast<uint64_t>(s) * m.n_rows + (r - m.row_base);
+            a.counts[m.counts_off + RL.jk_count + at] = cnt;
+            a.values[m.values_off + RL.jk_lse_w + at] = l.value();
         }
-        const int i = inst_of_row(a.mi, a.n_inst, r);
-        const MergeInst m = a.mi[i];
-        const uint32_t lr = r - m.row_base;
-        const ResultLayout RL = result_layout(m.n_bins, J);
-        double* V = a.values + m.values_off;
-        V[RL.lse_w2 + lr] = l2;
-        if (n > 0.0) {
-            const double mu = S1 / n;
-            const double e2 = S2 / n, e3 = S3 / n, e4 = S4 / n;
-            V[RL.mean_lnw + lr] = c + mu;
-            V[RL.m2_lnw + lr] = e2 - mu * mu;
-            V[RL.m3_lnw + lr] = e3 - 3.0 * mu * e2 + 2.0 * mu * mu * mu;
-            V[RL.m4_lnw + lr] = e4 - 4.0 * mu * e3 + 6.0 * mu * mu * e2 - 3.0 * mu * mu * mu * mu;
-        } else {
-            V[RL.mean_lnw + lr] = NAN;
-            V[RL.m2_lnw + lr] = NAN;
-            V[RL.m3_lnw + lr] = NAN;
-            V[RL.m4_lnw + lr] = NAN;
+    } else if (blockIdx.x < n_cell_blocks + n_row_blocks) {
+        // log-sum of w^2 and the moments of ln w per row
+        const uint32_t r = (blockIdx.x - n_cell_blocks) * MERGE_CELLS + lc;
+        const bool have = r < RT;
+        LseAcc l2;
+        PowerSums P;
+        if (have)
+            for (int w = part; w < a.n_wg; w += MERGE_SPLIT) {
+                const unsigned char *sl = a.slices + static_cast<size_t>(w) * L.slice_bytes;
+                l2.add(reinterpret_cast<const double *>(sl + L.off_lse_w2)[r]);
+                const double cw = reinterpret_cast<const double *>(sl + L.off_shift)[r];
+                if (isnan(cw)) continue;
+                double nw = 0.0;
+                for (uint32_t s = 0; s < J; ++s)
+                    nw += static_cast<double>(reinterpret_cast<const uint32_t *>(sl + L.off_cnt)[s * RT + r]);
+                P.fold(cw, nw, reinterpret_cast<const double *>(sl + L.off_s1)[r],
+                       reinterpret_cast<const double *>(sl + L.off_s2)[r], reinterpret_cast<const double *>(sl + L.off_s3)[r],
+                       reinterpret_cast<const double *>(sl + L.off_s4)[r]);
+            }
+        for (int half = MERGE_SPLIT / 2; half >= 1; half >>= 1) {
+            red[0][tid] = l2.m;
+            red[1][tid] = l2.s;
+            __syncthreads();
+            if (part < half) l2.fold(red[0][tid + half * MERGE_CELLS], red[1][tid + half * MERGE_CELLS]);
+            __syncthreads();
+            red[0][tid] = P.c;
+            red[1][tid] = P.n;
+            red[2][tid] = P.S1;
+            red[3][tid] = P.S2;
+            red[4][tid] = P.S3;
+            red[5][tid] = P.S4;
+            __syncthreads();
+            if (part < half) {
+                const int o = tid + half * MERGE_CELLS;
+                P.fold(red[0][o], red[1][o], red[2][o], red[3][o], red[4][o], red[5][o]);
+            }
+            __syncthreads();
         }
-    } else if (tid < J * RT + RT + static_cast<uint32_t>(a.n_inst)) {
-        const int i = static_cast<int>(tid - J * RT - RT);
-        double f[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
-        double k2 = 0.0, steps = 0.0, ps[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-        for (int w = 0; w < a.n_wg; ++w) {
-            const double *sc = reinterpret_cast<const double *>(a.slices + static_cast<size_t>(w) * L.slice_bytes + L.off_scal) + static_cast<size_t>(i) * 16;
-            for (int q = 0; q < 4; ++q) f[q] = lse2(f[q], sc[q]);
-            k2 += sc[4];
-            steps += sc[5];
-            for (int q = 0; q < 6; ++q) ps[q] += sc[6 + q];
+        if (have && part == 0) {
+            const MergeInst m = a.mi[inst_of_row(a.mi, a.n_inst, r)];
+            const uint32_t lr = r - m.row_base;
+            const ResultLayout RL = result_layout(m.n_bins, J);
+            double *V = a.values + m.values_off;
+            V[RL.lse_w2 + lr] = l2.value();
+            const double n = P.n;
+            if (n > 0.0) {
+                const double mu = P.S1 / n;
+                const double e2 = P.S2 / n, e3 = P.S3 / n, e4 = P.S4 / n;
+                V[RL.mean_lnw + lr] = P.c + mu;
+                V[RL.m2_lnw + lr] = e2 - mu * mu;
+                V[RL.m3_lnw + lr] = e3 - 3.0 * mu * e2 + 2.0 * mu * mu * mu;
+                V[RL.m4_lnw + lr] = e4 - 4.0 * mu * e3 + 6.0 * mu * mu * e2 - 3.0 * mu * mu * mu * mu;
+            } else {
+                V[RL.mean_lnw + lr] = NAN;
+                V[RL.m2_lnw + lr] = NAN;
+                V[RL.m3_lnw + lr] = NAN;
+                V[RL.m4_lnw + lr] = NAN;
+            }
         }
-        const MergeInst m = a.mi[i];
-        const ResultLayout RL = result_layout(m.n_bins, J);
-        double *V = a.values + m.values_off;
-        V[RL.lse_w_all] = f[0];
-        V[RL.lse_w2_all] = f[1];
-        V[RL.lse_wk] = f[2];
-        V[RL.lse_wk2] = f[3];
-        V[RL.sum_k2] = k2;
-        {
+    } else {
+        // one instance's whole-run sums
+        const int i = static_cast<int>(blockIdx.x - n_cell_blocks - n_row_blocks);
+        LseAcc f[4];
+        double acc[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+        for (int w = tid; w < a.n_wg; w += MERGE_BLOCK) {
+            const double *sc = reinterpret_cast<const double *>(a.slices + static_cast<size_t>(w) * L.slice_bytes + L.off_scal) +
+                               static_cast<size_t>(i) * 16;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) f[q].add(sc[q]);
+#pragma unroll
+            for (int q = 0; q < 8; ++q) acc[q] += sc[4 + q];
+        }
+        // fold each wave, then the waves in order
+        for (int h = 32; h >= 1; h >>= 1) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) f[q].fold(__shfl_down(f[q].m, h, 64), __shfl_down(f[q].s, h, 64));
+#pragma unroll
+            for (int q = 0; q < 8; ++q) acc[q] += __shfl_down(acc[q], h, 64);
+        }
+        if (tid % 64 == 0) {
+            double *o = &red[0][0] + (tid / 64) * 16;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                o[2 * q] = f[q].m;
+                o[2 * q + 1] = f[q].s;
+            }
+#pragma unroll
+            for (int q = 0; q < 8; ++q) o[8 + q] = acc[q];
+        }
+        __syncthreads();
+        if (tid == 0) {
+            for (int wave = 1; wave < MERGE_BLOCK / 64; ++wave) {
+                const double *o = &red[0][0] + wave * 16;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) f[q].fold(o[2 * q], o[2 * q + 1]);
+#pragma unroll
+                for (int q = 0; q < 8; ++q) acc[q] += o[8 + q];
+            }
+            const MergeInst m = a.mi[i];
+            const ResultLayout RL = result_layout(m.n_bins, J);
+            double *V = a.values + m.values_off;
+            V[RL.lse_w_all] = f[0].value();
+            V[RL.lse_w2_all] = f[1].value();
+            V[RL.lse_wk] = f[2].value();
+            V[RL.lse_wk2] = f[3].value();
+            V[RL.sum_k2] = acc[0];
             // Pearson's r of ln w with N over the ended runs (equal to that of log10 w with N)
-            const double n = ps[0];
-            const double mx = ps[1] / n, my = ps[3] / n;
-            const double cxy = ps[5] / n - mx * my;
-            const double vx = ps[2] / n - mx * mx, vy = ps[4] / n - my * my;
+            const double n = acc[2];
+            const double mx = acc[3] / n, my = acc[5] / n;
+            const double cxy = acc[7] / n - mx * my;
+            const double vx = acc[4] / n - mx * mx, vy = acc[6] / n - my * my;
             V[RL.pearson_r] = (n >= 2.0 && vx > 0.0 && vy > 0.0) ? cxy / sqrt(vx * vy) : NAN;
+            a.counts[m.counts_off + RL.n_traj] = m.n_traj;
+            a.counts[m.counts_off + RL.total_steps] = static_cast<uint64_t>(acc[1]);
+            V[RL.lognormal_gate] = 1.0;     // cleared by the finalize kernel where a bin fails
         }
-        a.counts[m.counts_off + RL.n_traj] = m.n_traj;
-        a.counts[m.counts_off + RL.total_steps] = static_cast<uint64_t>(steps);
-        V[RL.lognormal_gate] = 1.0;     // cleared by the finalize kernel where a bin fails
     }
 }
 
@@ -611,51 +718,78 @@ __device__ void lognormal_bin(double *V, const ResultLayout &RL, uint32_t lr, ui
     V[RL.normal_p + lr] = pv;
 }
 
-__global__ __launch_bounds__(256) void fpt_finalize_kernel(MergeArgs a) {
-    const uint32_t r = blockIdx.x * blockDim.x + threadIdx.x;
+// Finalize: FIN_LANES lanes per row, each taking every FIN_LANES-th jackknife subset (with one
+// thread per row the chain of 2 J exponentials took 17 to 22 us).
+constexpr int FIN_LANES = 16, FIN_ROWS = 4;
+
+__global__ __launch_bounds__(FIN_LANES * FIN_ROWS) void fpt_finalize_kernel(MergeArgs a) {
+    const uint32_t r0 = blockIdx.x * FIN_ROWS + threadIdx.x / FIN_LANES;
+    const uint32_t q = threadIdx.x % FIN_LANES;
     const uint32_t RT = a.lay.n_rows, J = a.lay.n_sub;
-    if (r >= RT) return;
+    const uint32_t r = r0 < RT ? r0 : RT - 1;      // lanes past the last row repeat it and do not write
     const int i = inst_of_row(a.mi, a.n_inst, r);
     const MergeInst m = a.mi[i];
     const uint32_t lr = r - m.row_base;
     const ResultLayout RL = result_layout(m.n_bins, J);
     uint64_t *Cn = a.counts + m.counts_off;
     double *V = a.values + m.values_off;
-    uint64_t cnt = 0;
-    double l = -INFINITY;
-    for (uint32_t s = 0; s < J; ++s) {
+    unsigned long long cnt = 0;
+    LseAcc la;
+    for (uint32_t s = q; s < J; s += FIN_LANES) {
         cnt += Cn[RL.jk_count + static_cast<uint64_t>(s) * m.n_rows + lr];
-        l = lse2(l, V[RL.jk_lse_w + static_cast<uint64_t>(s) * m.n_rows + lr]);
+        la.add(V[RL.jk_lse_w + static_cast<uint64_t>(s) * m.n_rows + lr]);
     }
-    Cn[RL.count + lr] = cnt;
-    V[RL.lse_w + lr] = l;
+#pragma unroll
+    for (int h = FIN_LANES / 2; h >= 1; h >>= 1) {
+        cnt += __shfl_down(cnt, h, FIN_LANES);
+        la.fold(__shfl_down(la.m, h, FIN_LANES), __shfl_down(la.s, h, FIN_LANES));
+    }
+    const bool owner = q == 0 && r0 < RT;
+    cnt = __shfl(cnt, 0, FIN_LANES);
+    const double l = __shfl(la.value(), 0, FIN_LANES);
+    if (owner) {
+        Cn[RL.count + lr] = cnt;
+        V[RL.lse_w + lr] = l;
+    }
     if (lr < m.n_bins) {
         const double width = a.edges[m.edge_base + lr + 1] - a.edges[m.edge_base + lr];
         const double nt = static_cast<double>(m.n_traj);
-        V[RL.log_p + lr] = l - log(width) - log(nt);
         // jackknife: P_s / P = exp(lse_s - lse) * n_traj / n_s; spread over subsets / sqrt(J)
-        double mean = 0.0, m2 = 0.0;
-        for (uint32_t s = 0; s < J; ++s) {
-            // runs of subset s: ids t = s mod J in [t_first, t_first + n_traj), as the number below
-            // the end minus the number below the start (ids below x in subset s: x/J + (x mod J > s))
-            const uint64_t x1 = m.t_first + m.n_traj, x0 = m.t_first;
-            const double ns = static_cast<double>((x1 / J + ((x1 % J) > s ? 1 : 0)) - (x0 / J + ((x0 % J) > s ? 1 : 0)));
-            const double rel = exp(V[RL.jk_lse_w + static_cast<uint64_t>(s) * m.n_rows + lr] - l) * (nt / ns);
-            const double dlt = rel - mean;
-            mean += dlt / static_cast<double>(s + 1);
-            m2 += dlt * (rel - mean);
+        double rel[64 / FIN_LANES], sum = 0.0, m2 = 0.0;
+#pragma unroll
+        for (int k = 0; k < 64 / FIN_LANES; ++k) {
+            const uint32_t s = q + k * FIN_LANES;
+            rel[k] = 0.0;
+            if (s < J) {
+                // runs of subset s: ids t = s mod J in [t_first, t_first + n_traj), as the number below
+                // the end minus the number below the start (ids below x in subset s: x/J + (x mod J > s))
+                const uint64_t x1 = m.t_first + m.n_traj, x0 = m.t_first;
+                const double ns = static_cast<double>((x1 / J + ((x1 % J) > s ? 1 : 0)) - (x0 / J + ((x0 % J) > s ? 1 : 0)));
+                rel[k] = exp(V[RL.jk_lse_w + static_cast<uint64_t>(s) * m.n_rows + lr] - l) * (nt / ns);
+                sum += rel[k];
+            }
         }
-        V[RL.rel_err_jk + lr] = sqrt(m2 / static_cast<double>(J - 1)) / sqrt(static_cast<double>(J));
-        const double k2 = exp(V[RL.lse_w2 + lr] - 2.0 * l) - 1.0 / nt;
-        V[RL.rel_err_kish + lr] = (cnt == 0) ? NAN : sqrt(fmax(k2, 0.0));
-        if (cnt == 0) V[RL.rel_err_jk + lr] = NAN;
-        // Kish's effective sample size of the bin, (sum w)^2 / sum w^2
-        V[RL.ess + lr] = (cnt == 0) ? 0.0 : exp(2.0 * l - V[RL.lse_w2 + lr]);
-        lognormal_bin(V, RL, lr, cnt, log(width) + log(nt));
-        // the paper's gate (Sec. 2.4): the lognormal estimator holds for the result when no bin
-        // with a normality p-value (n_j >= 8) falls below 0.5 %; every failing bin writes 0
-        const double pv = V[RL.normal_p + lr];
-        if (cnt >= 8 && pv == pv && pv < 0.005) V[RL.lognormal_gate] = 0.0;
+#pragma unroll
+        for (int h = FIN_LANES / 2; h >= 1; h >>= 1) sum += __shfl_xor(sum, h, FIN_LANES);
+        const double mean = sum / static_cast<double>(J);
+#pragma unroll
+        for (int k = 0; k < 64 / FIN_LANES; ++k)
+            if (q + k * FIN_LANES < J) m2 += (rel[k] - mean) * (rel[k] - mean);
+#pragma unroll
+        for (int h = FIN_LANES / 2; h >= 1; h >>= 1) m2 += __shfl_xor(m2, h, FIN_LANES);
+        if (owner) {
+            V[RL.log_p + lr] = l - log(width) - log(nt);
+            V[RL.rel_err_jk + lr] = (cnt == 0) ? NAN : sqrt(m2 / static_cast<double>(J - 1)) / sqrt(static_cast<double>(J));
+            const double k2 = exp(V[RL.lse_w2 + lr] - 2.0 * l) - 1.0 / nt;
+            V[RL.rel_err_kish + lr] = (cnt == 0) ? NAN : sqrt(fmax(k2, 0.0));
+            // Kish's effective sample size of the bin, (sum w)^2 / sum w^2
+            V[RL.ess + lr] = (cnt == 0) ? 0.0 : exp(2.0 * l - V[RL.lse_w2 + lr]);
+            lognormal_bin(V, RL, lr, cnt, log(width) + log(nt));
+            // the paper's gate (Sec. 2.4): the lognormal estimator holds for the result when no bin
+            // with a normality p-value (n_j >= 8) falls below 0.5 %; every failing bin writes 0
+            const double pv = V[RL.normal_p + lr];
+            if (cnt >= 8 && pv == pv && pv < 0.005) V[RL.lognormal_gate] = 0.0;
+        }
     }
 }
 
@@ -734,11 +868,12 @@ hipError_t launch_mlp_forward(const uint16_t *params, MlpConsts c, const float *
 }
 
 hipError_t launch_merge(const MergeArgs &args, int total_rows, int n_sub, hipStream_t stream) {
-    const int n1 = n_sub * total_rows + total_rows + args.n_inst;
-    hipLaunchKernelGGL(fpt_merge_kernel, dim3((n1 + 255) / 256), dim3(256), 0, stream, args);
+    const int64_t cells = static_cast<int64_t>(n_sub) * total_rows;
+    const int64_t blocks = (cells + MERGE_CELLS - 1) / MERGE_CELLS + (total_rows + MERGE_CELLS - 1) / MERGE_CELLS + args.n_inst;
+    hipLaunchKernelGGL(fpt_merge_kernel, dim3(static_cast<unsigned>(blocks)), dim3(MERGE_BLOCK), 0, stream, args);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(fpt_finalize_kernel, dim3((total_rows + 255) / 256), dim3(256), 0, stream, args);
+    hipLaunchKernelGGL(fpt_finalize_kernel, dim3((total_rows + FIN_ROWS - 1) / FIN_ROWS), dim3(FIN_LANES * FIN_ROWS), 0, stream, args);
     return hipGetLastError();
 }
 
