@@ -22,44 +22,55 @@ enum : int { ST_RUNNING = 0, ST_ENDED = 1, ST_CENSORED = 2, ST_ESCAPED = 3 };
 // ---------------------------------------------------------------------------
 // Counter-based noise: Philox4x32-10 (Salmon, Moraes, Dror, Shaw, SC'11).
 // Ten rounds of two 32x32->64 multiplies; the key advances by the Weyl
-// constants between rounds.  The key (the seed) is wave-uniform.
+// constants between rounds.  The key (the seed) is wave-uniform.  One 32x32->64 multiply gives both
+// halves of a product (v_mad_u64_u32), and one v_bitop3_b32 (truth table 0x96 = a ^ b ^ c) each
+// three-input xor.
 // ---------------------------------------------------------------------------
 struct U4 {
     uint32_t x, y, z, w;
 };
 
-__device__ __forceinline__ U4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
-                                             uint32_t k0, uint32_t k1) {
-#pragma unroll
-    for (int round = 0; round < 10; ++round) {
-        if (round > 0) {
-            k0 += 0x9E3779B9u;
-            k1 += 0xBB67AE85u;
-        }
-        // one 32x32->64 multiply per word gives both halves (v_mad_u64_u32)
-        const uint64_t pa = static_cast<uint64_t>(0xD2511F53u) * c0;
-        const uint64_t pb = static_cast<uint64_t>(0xCD9E8D57u) * c2;
-        const uint32_t lo_a = static_cast<uint32_t>(pa);
-        const uint32_t hi_a = static_cast<uint32_t>(pa >> 32);
-        const uint32_t lo_b = static_cast<uint32_t>(pb);
-        const uint32_t hi_b = static_cast<uint32_t>(pb >> 32);
-        // three-input xor in one v_bitop3_b32 (truth table 0x96 = a ^ b ^ c)
-        const uint32_t n0 = __builtin_amdgcn_bitop3_b32(hi_b, c1, k0, 0x96);
-        const uint32_t n2 = __builtin_amdgcn_bitop3_b32(hi_a, c3, k1, 0x96);
-        c0 = n0;
-        c1 = lo_b;
-        c2 = n2;
-        c3 = lo_a;
-    }
-    return U4{c0, c1, c2, c3};
+// What the first two Philox rounds of a run's counters (j, t_lo, t_hi, stream) do not share with j:
+// round 1's product with t_hi and all of round 2's product with round 1's first word are fixed for
+// the run, so they are formed once per run (18 multiplies a call instead of 20, and three two-input
+// xors for three-input ones).
+struct PhiloxRun {
+    uint32_t a;       // stream ^ key1: the second word entering round 2 is hi(M0 j) ^ a
+    uint32_t b;       // round 2's first output word is hi(M1 w) ^ b, w that second word
+    uint32_t c;       // round 2's third output word is lo(M0 j) ^ c
+    uint32_t d;       // round 2's fourth output word
+};
+
+__device__ __forceinline__ PhiloxRun philox_run(uint64_t t, uint32_t stream, uint32_t k0, uint32_t k1) {
+    const uint64_t pb = static_cast<uint64_t>(0xCD9E8D57u) * static_cast<uint32_t>(t >> 32);
+    const uint32_t n0 = static_cast<uint32_t>(pb >> 32) ^ static_cast<uint32_t>(t) ^ k0;
+    const uint64_t pa = static_cast<uint64_t>(0xD2511F53u) * n0;
+    return PhiloxRun{stream ^ k1, static_cast<uint32_t>(pb) ^ (k0 + 0x9E3779B9u),
+                     static_cast<uint32_t>(pa >> 32) ^ (k1 + 0xBB67AE85u), static_cast<uint32_t>(pa)};
 }
 
-// u = (2 (x >> 9) + 1) 2^-24: odd multiples of 2^-24 in (0, 1), exact in binary32.
-// Formed as (1 + (x >> 9) 2^-23) + (2^-24 - 1): the first term is the float with exponent
-// bits of 1.0 and mantissa x >> 9, the constant is exact, and the sum, a multiple of 2^-24
-// below 1, is exact too.
-__device__ __forceinline__ float uniform24(uint32_t x) {
-    return __uint_as_float(0x3F800000u | (x >> 9)) + (0x1p-24f - 1.0f);
+// philox4x32_10(j, t_lo, t_hi, stream, k0, k1) for the run r was formed from, the same words.
+__device__ __forceinline__ U4 philox_block(uint32_t j, const PhiloxRun &r, uint32_t k0, uint32_t k1) {
+    const uint64_t p1 = static_cast<uint64_t>(0xD2511F53u) * j;
+    const uint64_t p2 = static_cast<uint64_t>(0xCD9E8D57u) * (static_cast<uint32_t>(p1 >> 32) ^ r.a);
+    uint32_t c0 = static_cast<uint32_t>(p2 >> 32) ^ r.b, c1 = static_cast<uint32_t>(p2);
+    uint32_t c2 = static_cast<uint32_t>(p1) ^ r.c, c3 = r.d;
+    k0 += 0x9E3779B9u;
+    k1 += 0xBB67AE85u;
+#pragma unroll
+    for (int round = 2; round < 10; ++round) {
+        k0 += 0x9E3779B9u;
+        k1 += 0xBB67AE85u;
+        const uint64_t pa = static_cast<uint64_t>(0xD2511F53u) * c0;
+        const uint64_t pb = static_cast<uint64_t>(0xCD9E8D57u) * c2;
+        const uint32_t n0 = __builtin_amdgcn_bitop3_b32(static_cast<uint32_t>(pb >> 32), c1, k0, 0x96);
+        const uint32_t n2 = __builtin_amdgcn_bitop3_b32(static_cast<uint32_t>(pa >> 32), c3, k1, 0x96);
+        c0 = n0;
+        c1 = static_cast<uint32_t>(pb);
+        c2 = n2;
+        c3 = static_cast<uint32_t>(pa);
+    }
+    return U4{c0, c1, c2, c3};
 }
 
 // 1/x for positive normal x: Newton-Raphson y <- fma(y, fma(-x, y, 1), y), three
@@ -93,27 +104,47 @@ __device__ __forceinline__ float sqrt_f32(float x) {
     return x * y;
 }
 
-// ln x for positive normal x: x = 2^e f with f in (sqrt(1/2), sqrt 2], bit patterns
-// (0x3F3504F3, 0x3FB504F3]; ln f = 2 atanh(s), s = (f-1)/(f+1), as the odd series to s^9;
-// ln x = e ln2_hi + (e ln2_lo + ln f).  The split is done on the bits: b - 0x3F3504F4 has e
-// in its arithmetic-shifted top bits and f - 0x3F3504F4 in its low 23.
-__device__ __forceinline__ float log_f32(float x) {
-    const int32_t ix = static_cast<int32_t>(__float_as_uint(x) - 0x3F3504F4u);
-    const int e = ix >> 23;
-    const float f = __uint_as_float((static_cast<uint32_t>(ix) & 0x007FFFFFu) + 0x3F3504F4u);
-    const float s = (f - 1.0f) * recip_f32(f + 1.0f);
-    const float z = s * s;
-    float p = 1.0f / 9.0f;
-    p = __builtin_fmaf(p, z, 1.0f / 7.0f);
-    p = __builtin_fmaf(p, z, 1.0f / 5.0f);
-    p = __builtin_fmaf(p, z, 1.0f / 3.0f);
-    const float t = s + s;
-    const float tz = t * z;
-    const float lf = __builtin_fmaf(tz, p, t);
-    const float ef = static_cast<float>(e);
+// The Box-Muller radius of a Philox word x, times -1/2: g with rho = sqrt(-2 ln u) = -2 g for
+// u = (2 (x >> 9) + 1) 2^-24, an odd multiple of 2^-24 in (0, 1).
+//
+// The definition (the checker's operations): u exact; ln u = e ln2_hi + (e ln2_lo + ln f) for
+// u = 2^e f, f in (sqrt(1/2), sqrt 2] (bit patterns (0x3F3504F3, 0x3FB504F3]), ln f = 2 atanh(s),
+// s = (f-1)/(f+1), as the odd series to s^9; rho = x y with x = -2 ln u and y the reciprocal square
+// root of x from three Newton steps y <- fma(y, fma(-x/2, y*y, 1/2), y) on the seed
+// bits(0x5F3759DF - (bits(x) >> 1)) (the seed of the Quake III Arena source (1999), analysed by
+// C. Lomont, "Fast inverse square root" (2003)).
+//
+// The operations below give the same bits with six instructions fewer, as multiplying by a power of
+// two commutes with every rounding here (all values are normal numbers):
+//   - u is the float of exponent 1.0 and mantissa x >> 9, plus 2^-24 - 1, exact;
+//   - -e comes from a subtraction and a shift, and f from adding it to u's exponent field;
+//   - t = 2 s from 2 (f-1), T = t t = 4 s^2, and the series' coefficients carry the factors 1/4;
+//   - with L = ln u, x/2 = -L, the seed of x in terms of bits(L) is bits(0x9EF759DF - (bits(L) >> 1)),
+//     and x y = -2 (L y): the factor -2 goes to the caller's constant.
+__device__ __forceinline__ float radius_m2(uint32_t x) {
+    const float u = __uint_as_float(__builtin_amdgcn_alignbit(0x7Fu, x, 9)) + (0x1p-24f - 1.0f);
+    const uint32_t b = __float_as_uint(u);
+    const int ne = static_cast<int32_t>(0x3FB504F3u - b) >> 23;
+    const float f = __uint_as_float((static_cast<uint32_t>(ne) << 23) + b);
+    const float t = __builtin_fmaf(f, 2.0f, -2.0f) * recip_f32(f + 1.0f);
+    const float T = t * t;
+    float p = (1.0f / 9.0f) * 0x1p-8f;
+    p = __builtin_fmaf(p, T, (1.0f / 7.0f) * 0x1p-6f);
+    p = __builtin_fmaf(p, T, (1.0f / 5.0f) * 0x1p-4f);
+    p = __builtin_fmaf(p, T, (1.0f / 3.0f) * 0x1p-2f);
+    const float lf = __builtin_fmaf(t * T, p, t);
+    const float nf = static_cast<float>(ne);
     const float ln2_hi = 0.693145751953125f;
     const float ln2_lo = 1.42860682030941723212e-6f;
-    return __builtin_fmaf(ef, ln2_hi, __builtin_fmaf(ef, ln2_lo, lf));
+    const float L = __builtin_fmaf(nf, -ln2_hi, __builtin_fmaf(nf, -ln2_lo, lf));
+    float y = __uint_as_float(0x9EF759DFu - (__float_as_uint(L) >> 1));
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        const float yy = y * y;
+        const float e = __builtin_fmaf(L, yy, 0.5f);
+        y = __builtin_fmaf(y, e, y);
+    }
+    return L * y;
 }
 
 // cos(2 pi u), sin(2 pi u) for the uniform u = uniform24(x): nearest quarter q = rint(4u),
@@ -122,10 +153,11 @@ __device__ __forceinline__ float log_f32(float x) {
 // q and r come from the bits of x: with y = x + 2^29 (mod 2^32), q = y >> 30 (mod 4) and
 // r = (2 a + 1 - 2^21) 2^-24 for a = bits 9..29 of y, formed exactly as
 // (0.5 + (2a + 1) 2^-24) - 0.625 -- the same values as the float reduction of u, for every x.
-__device__ __forceinline__ void sincos2pi_bits(uint32_t x, float &c_out, float &s_out) {
+// odd_mask holds 0x3FFFFE (bits 1..21) in a register the compiler cannot see through, so that the
+// mask and the exponent go in with one v_and_or_b32.
+__device__ __forceinline__ void sincos2pi_bits(uint32_t x, uint32_t odd_mask, float &c_out, float &s_out) {
     const uint32_t y = x + 0x20000000u;
-    const uint32_t a = (y >> 9) & 0x1FFFFFu;
-    const float r = __uint_as_float(0x3F000001u | (a << 1)) - 0.625f;
+    const float r = __uint_as_float(((y >> 8) & odd_mask) | 0x3F000001u) - 0.625f;
     const float r2 = r * r;
     float ps = __builtin_fmaf(42.058693944897653145f, r2, -76.7058597530613858416f);
     ps = __builtin_fmaf(ps, r2, 81.6052492760750542034f);
@@ -137,23 +169,21 @@ __device__ __forceinline__ void sincos2pi_bits(uint32_t x, float &c_out, float &
     pc = __builtin_fmaf(pc, r2, 64.939394022668291491f);
     pc = __builtin_fmaf(pc, r2, -19.7392088021787172377f);
     const float cs = __builtin_fmaf(pc, r2, 1.0f);
-    // quarter-turn rotation by q = y >> 30, branch-free: odd q swaps (cos, sin); cos changes
+    // quarter-turn rotation by q = y >> 30, branch-free: odd q (bit 30 of y: as a float, y's
+    // magnitude is not below 2, infinities and NaN patterns included) swaps (cos, sin); cos changes
     // sign for q = 1, 2 (bit 31 of y + 2^30) and sin for q = 2, 3 (bit 31 of y); IEEE negation
     // is the sign bit
-    const bool swap = (y & 0x40000000u) != 0u;
-    const float c0 = swap ? sn : cs;
-    const float s0 = swap ? cs : sn;
-    const uint32_t sign_c = (y + 0x40000000u) & 0x80000000u;
-    const uint32_t sign_s = y & 0x80000000u;
-    c_out = __uint_as_float(__float_as_uint(c0) ^ sign_c);
-    s_out = __uint_as_float(__float_as_uint(s0) ^ sign_s);
+    const bool even = __builtin_fabsf(__uint_as_float(y)) < 2.0f;
+    const float c0 = even ? cs : sn;
+    const float s0 = even ? sn : cs;
+    c_out = __uint_as_float(__builtin_amdgcn_bitop3_b32(x + 0x60000000u, __float_as_uint(c0), 0x80000000u, 0x6c));
+    s_out = __uint_as_float(__builtin_amdgcn_bitop3_b32(y, __float_as_uint(s0), 0x80000000u, 0x6c));
 }
 
 // e^x for x <= 0 (x < -80 gives 0): n = rint(x / ln 2), r = x - n ln2 (two-part),
-// Taylor series of e^r to r^7, times 2^n assembled in the exponent field.
+// Taylor series of e^r to r^7, times 2^n (a normal number: n >= -116).
 __device__ __forceinline__ float exp_f32(float x) {
     const bool under = x < -80.0f;
-    if (x > 0.0f) x = 0.0f;
     if (under) x = -80.0f;
     const float n = __builtin_rintf(x * 1.44269504088896340736f);
     float r = __builtin_fmaf(-n, 0.693145751953125f, x);
@@ -166,39 +196,33 @@ __device__ __forceinline__ float exp_f32(float x) {
     p = __builtin_fmaf(p, r, 0.5f);
     p = __builtin_fmaf(p, r, 1.0f);
     p = __builtin_fmaf(p, r, 1.0f);
-    const int ni = static_cast<int>(n);
-    const float scale = __uint_as_float(static_cast<uint32_t>(ni + 127) << 23);
-    const float y = p * scale;
+    const float y = __builtin_ldexpf(p, static_cast<int>(n));
     return under ? 0.0f : y;
 }
 
-// Four standard normals for steps 4j .. 4j+3 of run t: Box-Muller on (u0,u1), (u2,u3).
+// Four standard normals for steps 4j .. 4j+3 of a run, times -1/2: Box-Muller on (u0,u1), (u2,u3).
+// xi = -2 n with n a member here: sqrt(dN) xi is n times StepConsts::sq_m2, the same bits.
 struct F4 {
     float a, b, c, d;
 };
 
-__device__ __forceinline__ F4 normals4(uint32_t j, uint64_t t, uint32_t stream, uint32_t key0, uint32_t key1) {
+__device__ __forceinline__ F4 normals4(uint32_t j, const PhiloxRun &r, uint32_t key0, uint32_t key1) {
     // the key schedule is recomputed by scalar adds at each call: left to itself the compiler
-    // hoists all twenty round keys into scalar registers and spills them to vector lanes
+    // hoists all round keys into scalar registers and spills them to vector lanes
     asm volatile("" : "+s"(key0), "+s"(key1));
-    const U4 x = philox4x32_10(j, static_cast<uint32_t>(t), static_cast<uint32_t>(t >> 32), stream, key0, key1);
+    uint32_t odd_mask = 0x3FFFFEu;
+    asm("" : "+v"(odd_mask));
+    const U4 x = philox_block(j, r, key0, key1);
     F4 out;
-    {
-        const float ua = uniform24(x.x);
-        const float rho = sqrt_f32(-2.0f * log_f32(ua));
-        float c, s;
-        sincos2pi_bits(x.y, c, s);
-        out.a = rho * c;
-        out.b = rho * s;
-    }
-    {
-        const float ua = uniform24(x.z);
-        const float rho = sqrt_f32(-2.0f * log_f32(ua));
-        float c, s;
-        sincos2pi_bits(x.w, c, s);
-        out.c = rho * c;
-        out.d = rho * s;
-    }
+    float c, s;
+    const float g0 = radius_m2(x.x);
+    sincos2pi_bits(x.y, odd_mask, c, s);
+    out.a = g0 * c;
+    out.b = g0 * s;
+    const float g1 = radius_m2(x.z);
+    sincos2pi_bits(x.w, odd_mask, c, s);
+    out.c = g1 * c;
+    out.d = g1 * s;
     return out;
 }
 
@@ -207,7 +231,7 @@ __device__ __forceinline__ F4 normals4(uint32_t j, uint64_t t, uint32_t stream, 
 // binary64 inputs).
 // ---------------------------------------------------------------------------
 struct StepConsts {
-    float dN, sq, hdN, cm;        // dN, sqrt dN, dN/2, m/(2 pi sqrt 6) (flat: S)
+    float dN, sq_m2, hdN, cm;     // dN, -2 sqrt dN, dN/2, m/(2 pi sqrt 6) (flat: S)
     float a, phi0, inv_w2, inv_2w2;
     float A, phi_end, phi_uv, two_uv;
     float phi_esc, phi_in;
@@ -215,14 +239,22 @@ struct StepConsts {
     uint32_t k_max;
 };
 
-// D = -V'/V and S = sqrt(V/3)/(2 pi) at phi (Sec. 2.3).
+// S = sqrt(V/3)/(2 pi) at phi and the whole drift D + B, D = -V'/V (Sec. 2.3), B = r S.  D is
+// formed as -2/phi (+ the bump's term): 2/phi is exact in the reciprocal, so fma(-2, 1/phi, B)
+// rounds D + B once, as adding -2/phi does.
 template <int POT>
-__device__ __forceinline__ void drift_noise(const StepConsts &C, float phi, float &D, float &S) {
+struct FieldTerms {
+    float S;         // noise amplitude
+    float y;         // 1/phi
+    float corr;      // bump: its part of D
+};
+
+template <int POT>
+__device__ __forceinline__ FieldTerms<POT> field_terms(const StepConsts &C, float phi) {
+    FieldTerms<POT> T;
     if constexpr (POT == POT_QUADRATIC) {
-        const float y = recip_f32(phi);
-        const float d = y + y;          // 2/phi
-        D = -d;
-        S = C.cm * phi;
+        T.y = recip_f32(phi);
+        T.S = C.cm * phi;
     } else if constexpr (POT == POT_QUADRATIC_BUMP) {
         const float dphi = phi - C.phi0;
         const float e2 = dphi * dphi;
@@ -231,14 +263,24 @@ __device__ __forceinline__ void drift_noise(const StepConsts &C, float phi, floa
         const float ag = C.a * g;
         const float one_ag = 1.0f + ag;
         const float num = (dphi * C.inv_w2) * ag;
-        const float corr = num * recip_f32(one_ag);
-        const float y = recip_f32(phi);
-        const float d = y + y;
-        D = corr - d;
-        S = (C.cm * phi) * sqrt_f32(one_ag);
+        T.corr = num * recip_f32(one_ag);
+        T.y = recip_f32(phi);
+        T.S = (C.cm * phi) * sqrt_f32(one_ag);
     } else {
-        D = 0.0f;
-        S = C.cm;
+        T.S = C.cm;
+    }
+    return T;
+}
+
+template <int POT, bool BIASED>
+__device__ __forceinline__ float drift(const FieldTerms<POT> &T, float B) {
+    if constexpr (POT == POT_QUADRATIC) {
+        return BIASED ? __builtin_fmaf(-2.0f, T.y, B) : -2.0f * T.y;
+    } else if constexpr (POT == POT_QUADRATIC_BUMP) {
+        const float D = __builtin_fmaf(-2.0f, T.y, T.corr);
+        return BIASED ? D + B : D;
+    } else {
+        return BIASED ? B : 0.0f;
     }
 }
 
@@ -266,44 +308,90 @@ __device__ __forceinline__ int final_status(const StepConsts &C, float phi, uint
 }
 
 // One Euler-Maruyama step of the biased Langevin equation (Sec. 2.2 eq. eq_euler_maruyam_modified,
-// drift, noise and bias at the pre-step point), the weight increment
-// -r (r dN/2 + sqrt(dN) xi) accumulated in binary64, reflection above phi_UV, and the end /
-// cap / escape tests (Sec. 2.1, Sec. 3).  run stays true while none of the three tests fires;
-// final_status() names the one that did.  r_net is the bias when it comes from the learned
-// network.  Returns r and writes sqrt(dN) xi, which the training replay reuses.
+// drift, noise and bias at the pre-step point): the field after it, reflected above phi_UV (Sec.
+// 2.1, Sec. 3), and the weight increment dlw = -r (r dN/2 + sqrt(dN) xi) that the caller adds to
+// ln w in binary64.  n = -xi/2; r_net is the bias when it comes from the learned network.  Returns
+// r and writes sqrt(dN) xi, which the training replay reuses.
 template <int POT, int BIAS>
-__device__ __forceinline__ float em_step(const StepConsts &C, float &phi, uint32_t &k, double &lw, bool &run, float xi,
-                                         float r_net, float &sxi) {
-    float D, S;
-    drift_noise<POT>(C, phi, D, S);
-    float drift, r = 0.0f;
+__device__ __forceinline__ float em_step(const StepConsts &C, float &phi, float n, float r_net, float &dlw, float &sxi) {
+    const FieldTerms<POT> T = field_terms<POT>(C, phi);
+    float r = 0.0f, drift_dN;
+    sxi = C.sq_m2 * n;
     if constexpr (BIAS == BIAS_NONE) {
-        drift = D;
+        drift_dN = drift<POT, false>(T, 0.0f) * C.dN;
     } else {
         if constexpr (BIAS == BIAS_MLP) r = r_net;
-        else r = bias_ratio<BIAS>(C, phi, S);
-        const float B = r * S;
-        drift = D + B;
+        else r = bias_ratio<BIAS>(C, phi, T.S);
+        drift_dN = drift<POT, true>(T, r * T.S) * C.dN;
     }
     // The whole increment (D + B) dN + S sqrt(dN) xi is formed first and rounded onto phi once.
     // Adding the deterministic part to phi on its own would round it to phi's grid every step:
     // at small dN it spans only tens of ulps of phi, and its fraction of an ulp changes so slowly
     // with phi that the rounding error repeats from step to step instead of averaging out.
-    sxi = C.sq * xi;
-    const float inc_phi = __builtin_fmaf(S, sxi, drift * C.dN);
-    float nphi = phi + inc_phi;
-    if constexpr (BIAS != BIAS_NONE) {
-        const float inc = __builtin_fmaf(r, C.hdN, sxi);
-        const float dlw = -(r * inc);
-        lw += static_cast<double>(dlw);
-    }
+    const float nphi = phi + __builtin_fmaf(T.S, sxi, drift_dN);
+    if constexpr (BIAS != BIAS_NONE) dlw = -(r * __builtin_fmaf(r, C.hdN, sxi));
+    else dlw = 0.0f;
     // Reflection x -> 2 phi_UV - x above the wall, as a minimum: 2 phi_UV is exact and rounding
     // is monotone, so fl(2 phi_UV - x) <= phi_UV < x exactly when x > phi_UV (and >= x otherwise);
     // with no wall 2 phi_UV is +inf and the minimum is x.
     phi = __builtin_fminf(nphi, C.two_uv - nphi);
-    k += 1;
-    run = !(phi <= C.phi_end) && (k < C.k_max) && !(phi > C.phi_esc);
     return r;
+}
+
+// Whether a run stops after step k at phi: the end surface, the step cap or escape (Sec. 2.1,
+// Sec. 3); final_status() names which.
+__device__ __forceinline__ bool stops(const StepConsts &C, float phi, uint32_t k) {
+    return phi <= C.phi_end || k >= C.k_max || phi > C.phi_esc;
+}
+
+// A run between groups of four steps: group j's steps are 4j .. 4j+3.
+struct RunState {
+    float phi;
+    uint32_t j;
+    double lw;
+};
+
+// Groups a run can take whole before the step cap: it stops in group j when j + 1 >= this.
+__device__ __forceinline__ uint32_t cap_groups(uint32_t k_max) { return (k_max >> 2) + ((k_max & 3u) != 0u ? 1u : 0u); }
+
+// The four steps of group R.j, all taken without a test between them: the group's smallest and
+// largest field and the step cap tell at its end whether the run has stopped inside it, and then
+// the first step that stops it is picked from the saved fields and weights (what the steps past it
+// computed is dropped).  Tests after every step cost 7 of 28 instructions, and the branches around
+// them kept the compiler from overlapping one step's arithmetic with the next's normals.
+// Returns whether the run stopped, with its step count in k.
+template <int POT, int BIAS>
+__device__ __forceinline__ bool group4(const StepConsts &C, uint32_t j_cap, const F4 &z, float r_net, RunState &R, uint32_t &k) {
+    const float n[4] = {z.a, z.b, z.c, z.d};
+    float p[4];
+    double w[4];
+    float phi = R.phi;
+    double lw = R.lw;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        float dlw, sxi;
+        (void)em_step<POT, BIAS>(C, phi, n[s], r_net, dlw, sxi);
+        if constexpr (BIAS != BIAS_NONE) lw += static_cast<double>(dlw);
+        p[s] = phi;
+        w[s] = lw;
+    }
+    const float lo = __builtin_fminf(__builtin_fminf(p[0], p[1]), __builtin_fminf(p[2], p[3]));
+    const float hi = __builtin_fmaxf(__builtin_fmaxf(p[0], p[1]), __builtin_fmaxf(p[2], p[3]));
+    const uint32_t j = R.j;
+    R.phi = phi;
+    R.lw = lw;
+    R.j = j + 1;
+    const bool stop = lo <= C.phi_end || hi > C.phi_esc || j + 1 >= j_cap;
+    if (__builtin_expect(stop, 0)) {
+        const uint32_t left = C.k_max - 4 * j;     // steps to the cap, >= 1
+        int s = 3;
+        for (int q = 2; q >= 0; --q)
+            if (p[q] <= C.phi_end || p[q] > C.phi_esc || static_cast<uint32_t>(q + 1) >= left) s = q;
+        R.phi = s == 0 ? p[0] : s == 1 ? p[1] : s == 2 ? p[2] : p[3];
+        R.lw = s == 0 ? w[0] : s == 1 ? w[1] : s == 2 ? w[2] : w[3];
+        k = 4 * j + 1 + static_cast<uint32_t>(s);
+    }
+    return stop;
 }
 
 }  // namespace fpt

@@ -153,15 +153,15 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
 
     // lane state
     StepConsts C{};
-    uint32_t stream = 0, n_bins = 0, row_base = 0, thr_base = 0, dump_slot = 0, k_center = 0;
+    uint32_t stream = 0, n_bins = 0, row_base = 0, thr_base = 0, dump_slot = 0, k_center = 0, j_cap = 0;
     uint64_t t0 = 0;            // the current instance's first run id
     int cur_inst = -1;
-    float phi = 0.0f;
-    uint32_t k = 0;
-    double lw = 0.0;
+    RunState R{0.0f, 0u, 0.0};
+    PhiloxRun noise{};
+    uint32_t k = 0;             // step count of a run that has stopped
     uint64_t t = 0;
-    bool run = false;
-    bool active = false;
+    bool run = false;           // the lane's run goes on
+    bool active = false;        // the lane has a run, stopped or not
     bool need = true;
     LaneAcc acc;
     acc_reset(acc, -1);
@@ -183,10 +183,8 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
         else return mlp_forward(tiles, mc, phi_, N_);
     };
     int single_inst = 0;
-    if constexpr (SINGLE) {
-        // the one instance with runs (others in the batch, if any, have none)
-        single_inst = static_cast<int>(a.order[0]);
-        const InstDev &I = a.inst[single_inst];
+    auto load_instance = [&](int ii) {
+        const InstDev &I = a.inst[ii];
         C = I.c;
         stream = I.stream;
         n_bins = I.n_bins;
@@ -196,7 +194,13 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
         k_center = I.k_center;
         t0 = I.t_first;
         if constexpr (BIAS == BIAS_MLP) mc = I.mlp;
-        cur_inst = single_inst;
+        cur_inst = ii;
+        j_cap = cap_groups(C.k_max);
+    };
+    if constexpr (SINGLE) {
+        // the one instance with runs (others in the batch, if any, have none)
+        single_inst = static_cast<int>(a.order[0]);
+        load_instance(single_inst);
     }
 
     while (true) {
@@ -236,27 +240,14 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
                         ii = static_cast<int>(a.order[lo]);
                         t = v - a.vbeg_sorted[lo];
                     }
-                    if (!SINGLE && ii != cur_inst) {
-                        const InstDev &I = a.inst[ii];
-                        C = I.c;
-                        stream = I.stream;
-                        n_bins = I.n_bins;
-                        row_base = I.row_base;
-                        thr_base = I.thr_base;
-                        dump_slot = I.dump_slot;
-                        k_center = I.k_center;
-                        t0 = I.t_first;
-                        if constexpr (BIAS == BIAS_MLP) mc = I.mlp;
-                        cur_inst = ii;
-                    }
+                    if (!SINGLE && ii != cur_inst) load_instance(ii);
                     t += t0;                   // the run's id: Philox counter and jackknife subset
                     if (acc.inst != ii) {
                         if (acc.inst >= 0) acc_commit_direct(T, acc);
                         acc_reset(acc, ii);
                     }
-                    phi = C.phi_in;
-                    k = 0;
-                    lw = 0.0;
+                    noise = philox_run(t, stream, a.key0, a.key1);
+                    R = RunState{C.phi_in, 0u, 0.0};
                     run = true;
                     active = true;
                 } else {
@@ -266,17 +257,11 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
         }
         if (!__any(active)) break;
 
-        // ---- four Euler-Maruyama steps from one Philox call
-        float sxi;
-        auto step = [&](float xi, float r_net) { (void)em_step<POT, BIAS>(C, phi, k, lw, run, xi, r_net, sxi); };
+        // ---- a pass: groups of four Euler-Maruyama steps, each from one Philox call
         if constexpr (BIAS != BIAS_MLP) {
-            if (active) {
-                const F4 z = normals4(k >> 2, t, stream, a.key0, a.key1);
-                const float zs[4] = {z.a, z.b, z.c, z.d};
-#pragma unroll
-                for (int s = 0; s < 4; ++s) {
-                    if (run) step(zs[s], 0.0f);
-                }
+            if (run) {
+                const F4 z = normals4(R.j, noise, a.key0, a.key1);
+                run = !group4<POT, BIAS>(C, j_cap, z, 0.0f, R, k);
             }
         } else {
             // the network is evaluated by all 64 lanes together, outside divergent code.  One
@@ -294,17 +279,17 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
                 constexpr int NQ = decltype(nq_tag)::value;
                 F4 zz[NQ];
 #pragma unroll
-                for (int q = 0; q < NQ; ++q) zz[q] = normals4((k >> 2) + q, t, stream, a.key0, a.key1);
+                for (int q = 0; q < NQ; ++q) {
+                    zz[q] = normals4(R.j + q, noise, a.key0, a.key1);
+                    // four draws at once would not fit the registers
+                    if (q == 1) __builtin_amdgcn_sched_barrier(0);
+                }
                 __builtin_amdgcn_s_setprio(2);
-                const float r_mlp = network(phi, static_cast<float>(k) * C.dN);
+                const float r_mlp = network(R.phi, static_cast<float>(4u * R.j) * C.dN);
                 __builtin_amdgcn_s_setprio(0);
 #pragma unroll
-                for (int q = 0; q < NQ; ++q) {
-                    const float zs[4] = {zz[q].a, zz[q].b, zz[q].c, zz[q].d};
-#pragma unroll
-                    for (int s = 0; s < 4; ++s)
-                        if (active && run) step(zs[s], r_mlp);
-                }
+                for (int q = 0; q < NQ; ++q)
+                    if (run) run = !group4<POT, BIAS>(C, j_cap, zz[q], r_mlp, R, k);
             };
             if (E == 16) {
                 pass(std::integral_constant<int, 4>{});
@@ -314,20 +299,29 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
                 pass(std::integral_constant<int, 1>{});
             } else {
                 // E = 1: an evaluation before every step
-                F4 z{};
-                if (active && run) z = normals4(k >> 2, t, stream, a.key0, a.key1);
-                const float zs[4] = {z.a, z.b, z.c, z.d};
+                const F4 z = normals4(R.j, noise, a.key0, a.key1);
+                const float ns[4] = {z.a, z.b, z.c, z.d};
 #pragma unroll
                 for (int s = 0; s < 4; ++s) {
-                    const float r_mlp = network(phi, static_cast<float>(k) * C.dN);
-                    if (active && run) step(zs[s], r_mlp);
+                    const uint32_t k0 = 4u * R.j + s;
+                    const float r_mlp = network(R.phi, static_cast<float>(k0) * C.dN);
+                    if (run) {
+                        float dlw, sxi;
+                        (void)em_step<POT, BIAS>(C, R.phi, ns[s], r_mlp, dlw, sxi);
+                        R.lw += static_cast<double>(dlw);
+                        k = k0 + 1;
+                        run = !stops(C, R.phi, k);
+                    }
                 }
+                R.j += 1;
             }
         }
 
         // ---- retire finished runs into the workgroup table
         const bool fin = active && !run;
         if (fin) {
+            const float phi = R.phi;
+            const double lw = R.lw;
             const int st = final_status(C, phi, k);
             uint32_t rl;
             if (st == ST_ENDED) {

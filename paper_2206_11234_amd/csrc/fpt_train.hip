@@ -52,6 +52,7 @@ __global__ __launch_bounds__(256) void fpt_record_kernel(RecordArgs a) {
     const uint64_t base = have ? a.rec_off[i] : 0;
     const uint64_t cap = have ? a.rec_off[i + 1] - base : 0;
     const uint32_t emask = static_cast<uint32_t>(a.group - 1);
+    const PhiloxRun noise = philox_run(t, a.inst.stream, a.key0, a.key1);
     float phi = C.phi_in;
     uint32_t k = 0;
     double lw = 0.0;
@@ -70,7 +71,7 @@ __global__ __launch_bounds__(256) void fpt_record_kernel(RecordArgs a) {
                 if (q * 4 % E == 0) r_mlp = mlp_forward(tiles, mc, phi, static_cast<float>(k) * C.dN);
             }
             F4 z{};
-            if (run) z = normals4(k >> 2, t, a.inst.stream, a.key0, a.key1);
+            if (run) z = normals4(k >> 2, noise, a.key0, a.key1);
             const float zs[4] = {z.a, z.b, z.c, z.d};
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
@@ -84,8 +85,11 @@ __global__ __launch_bounds__(256) void fpt_record_kernel(RecordArgs a) {
                         H = 0.0f;
                         n_e = 0;
                     }
-                    float sxi;
-                    const float r = em_step<POT, BIAS>(C, phi, k, lw, run, zs[s], r_mlp, sxi);
+                    float dlw, sxi;
+                    const float r = em_step<POT, BIAS>(C, phi, zs[s], r_mlp, dlw, sxi);
+                    lw += static_cast<double>(dlw);
+                    k += 1;
+                    run = !stops(C, phi, k);
                     H = H + __builtin_fmaf(r, C.dN, sxi);
                     n_e += 1;
                     if ((k & emask) == 0 || !run) {

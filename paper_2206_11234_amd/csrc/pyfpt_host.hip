@@ -355,7 +355,7 @@ int prepare(const pyfpt_instance *ins, int n_inst, Prepared &P) {
         std::memset(&D, 0, sizeof D);
         StepConsts &C = D.c;
         C.dN = static_cast<float>(I.dN);
-        C.sq = static_cast<float>(std::sqrt(I.dN));
+        C.sq_m2 = -2.0f * static_cast<float>(std::sqrt(I.dN));
         C.hdN = static_cast<float>(0.5 * I.dN);
         if (I.pot.kind == PYFPT_POT_FLAT)
             C.cm = static_cast<float>(std::sqrt(I.pot.V0 / 3.0) / (2.0 * M_PI));
