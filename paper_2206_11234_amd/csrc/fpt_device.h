@@ -376,12 +376,15 @@ __device__ __forceinline__ bool group4(const StepConsts &C, uint32_t j_cap, cons
         w[s] = lw;
     }
     const float lo = __builtin_fminf(__builtin_fminf(p[0], p[1]), __builtin_fminf(p[2], p[3]));
-    const float hi = __builtin_fmaxf(__builtin_fmaxf(p[0], p[1]), __builtin_fmaxf(p[2], p[3]));
+    float hi;       // (the compiler's own maximum first canonicalises each operand)
+    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(hi) : "v"(p[0]), "v"(p[1]), "v"(p[2]));
+    asm("v_max_f32 %0, %1, %2" : "=v"(hi) : "v"(hi), "v"(p[3]));
     const uint32_t j = R.j;
     R.phi = phi;
     R.lw = lw;
     R.j = j + 1;
-    const bool stop = lo <= C.phi_end || hi > C.phi_esc || j + 1 >= j_cap;
+    // (no short circuit: its branches would split the group's arithmetic)
+    const bool stop = (lo <= C.phi_end) | (hi > C.phi_esc) | (j + 1 >= j_cap);
     if (__builtin_expect(stop, 0)) {
         const uint32_t left = C.k_max - 4 * j;     // steps to the cap, >= 1
         int s = 3;

@@ -32,8 +32,7 @@ struct TableLayout {
     uint32_t n_inst;
     uint32_t slice_bytes;
     // binary64 arrays
-    uint32_t off_scal;    // [n_inst][16]: lse_w_all, lse_w2_all, lse_wk, lse_wk2, sum_k2, steps, then over the
-                          // ended runs: n, sum x, sum x^2, sum y, sum y^2, sum xy (x = ln w, y = k - k_center), pad
+    uint32_t off_scal;    // [n_inst][16]: two unused, lse_wk, lse_wk2, sum_k2, steps, then over the ended runs: n, sum x, sum x^2, sum y, sum y^2, sum xy (x = ln w, y = k - k_center), pad
     uint32_t off_jk_lse;  // [J][n_rows]
     uint32_t off_lse_w2;  // [n_rows]
     uint32_t off_shift;   // [n_rows]
@@ -63,6 +62,9 @@ struct StepArgs {
     TableLayout lay;
     DumpDev dump;
     uint32_t chunk;
+    uint32_t lane_cap;            // lanes of a wave that take runs (below 64 the queue is empty from the start)
+    uint32_t cus, turn;           // CUs; waves by which the order turns between the workgroups of one
+    uint32_t spread;              // first ids: 1 a lane of every wave in turn, 0 wave by wave
     const uint16_t *mlp_params;   // bfloat16 network shared by the batch (learned proposal)
     int32_t mlp_every;            // evaluate the network every 1, 4, 8 or 16 steps
 };

@@ -112,21 +112,19 @@ __device__ __forceinline__ double wave_sum(double x) {
 
 struct LaneAcc {
     int inst;
-    double w, w2, wk, wk2, k2;
+    double wk, wk2, k2;
     double steps;   // exact: integer-valued, < 2^53 per lane
 };
 
 __device__ __forceinline__ void acc_reset(LaneAcc &a, int inst) {
     a.inst = inst;
-    a.w = a.w2 = a.wk = a.wk2 = -INFINITY;
+    a.wk = a.wk2 = -INFINITY;
     a.k2 = 0.0;
     a.steps = 0.0;
 }
 
 __device__ __forceinline__ void acc_commit_direct(const Tab &T, const LaneAcc &a) {
     double *s = T.scal + static_cast<size_t>(a.inst) * 16;
-    atomic_lse(s + 0, a.w);
-    atomic_lse(s + 1, a.w2);
     atomic_lse(s + 2, a.wk);
     atomic_lse(s + 3, a.wk2);
     atomic_add_f64(s + 4, a.k2);
@@ -134,6 +132,61 @@ __device__ __forceinline__ void acc_commit_direct(const Tab &T, const LaneAcc &a
 }
 
 extern __shared__ __align__(16) unsigned char fpt_lds[];
+
+// A wave's lanes shared out over the few runs it has left.  With n <= 32 runs the wave works
+// G = 2, 4 or 8 groups of steps ahead: lane l draws the normals of group j + l / S of the run in
+// slot l % S (S = 64 / G slots, the n runs in the first n of them), and in each of the next G groups
+// a run's own lane reads its four normals from the lane that drew them; they are the values it would
+// draw itself.  A step costs a wave about 38 instructions of normals and 22 of stepping whatever its
+// number of runs, and a wave issues at most one per 5 cycles (two waves on a SIMD one per 2.4), so a
+// lone wave's step falls from 60 x 5 cycles towards the 130 of its chain of dependent operations.
+struct Team {
+    int shift = 6;                // S = 1 << shift slots
+    int slot_lane = 0;            // byte address (4 x lane) of the lane that owns this lane's slot's run
+    int fetch0 = 0;               // byte address of the lane that draws this lane's run's first group
+    PhiloxRun noise{};            // noise of the slot's run
+    __device__ __forceinline__ int groups() const { return 64 >> shift; }
+};
+
+__device__ __forceinline__ uint32_t lane_read(int addr, uint32_t v) {
+    return static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(addr, static_cast<int>(v)));
+}
+__device__ __forceinline__ float lane_read(int addr, float v) { return __uint_as_float(lane_read(addr, __float_as_uint(v))); }
+
+// Whether a wave with n runs left, on S = 1 << shift slots, can share its lanes out further.
+__device__ __forceinline__ bool team_halves(int shift, int n, int most) {
+    return 2 * n <= (1 << shift) && (64 >> shift) < most;
+}
+
+// Share the wave's lanes out over the runs of the lanes in `act` (at most 32; wave-uniform).  Runs
+// that end later leave their slots idle until the team is formed anew.
+__device__ __forceinline__ void team_form(Team &T, uint64_t act, uint64_t lt_mask, uint32_t lane, const PhiloxRun &own, int most) {
+    const int n = __popcll(act);
+    const int before = __popcll(act & lt_mask);
+    int shift = 6;
+    while (team_halves(shift, n, most)) --shift;
+    T.shift = shift;
+    const bool mine = (act >> lane) & 1u;
+    // a permutation that sends the owners to lanes 0 .. n-1 in order and the others after them
+    const int to = mine ? before : n + (static_cast<int>(lane) - before);
+    const int owner = __builtin_amdgcn_ds_permute(4 * to, static_cast<int>(lane));
+    T.slot_lane = 4 * __builtin_amdgcn_ds_bpermute(4 * (static_cast<int>(lane) & ((1 << shift) - 1)), owner);
+    T.fetch0 = 4 * before;
+    T.noise = PhiloxRun{lane_read(T.slot_lane, own.a), lane_read(T.slot_lane, own.b), lane_read(T.slot_lane, own.c),
+                        lane_read(T.slot_lane, own.d)};
+}
+
+// The normals of this lane's slot's run, lane / S groups after the group j of that run (own_j:
+// every lane's own run's group).
+__device__ __forceinline__ F4 team_draw(const Team &T, uint32_t lane, uint32_t own_j, uint32_t key0, uint32_t key1) {
+    return normals4(lane_read(T.slot_lane, own_j) + (lane >> T.shift), T.noise, key0, key1);
+}
+
+// This lane's run's normals of the g-th group of the batch z.
+__device__ __forceinline__ F4 team_fetch(const Team &T, const F4 &z, int g) {
+    const int from = T.fetch0 + ((4 * g) << T.shift);
+    return F4{lane_read(from, z.a), lane_read(from, z.b), lane_read(from, z.c), lane_read(from, z.d)};
+}
 
 // SINGLE: one instance of the batch has runs, so its constants are uniform across the workgroup
 // (the compiler keeps them in scalar registers) and queue ids are its trajectory ids.
@@ -153,8 +206,7 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
 
     // lane state
     StepConsts C{};
-    uint32_t stream = 0, n_bins = 0, row_base = 0, thr_base = 0, dump_slot = 0, k_center = 0, j_cap = 0;
-    uint64_t t0 = 0;            // the current instance's first run id
+    uint32_t j_cap = 0;
     int cur_inst = -1;
     RunState R{0.0f, 0u, 0.0};
     PhiloxRun noise{};
@@ -162,11 +214,17 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
     uint64_t t = 0;
     bool run = false;           // the lane's run goes on
     bool active = false;        // the lane has a run, stopped or not
-    bool need = true;
+    bool need = lane < a.lane_cap;
     LaneAcc acc;
     acc_reset(acc, -1);
     // this wave's reserved queue range
     uint64_t res_lo = 0, res_hi = 0;
+    // The first ids are handed out by position, the others from the queue (StepArgs::spread).
+    const uint64_t n_waves = static_cast<uint64_t>(gridDim.x) * (blockDim.x / 64);
+    const uint64_t n_first = n_waves * a.lane_cap;
+    bool first = true;
+    bool drained = n_first >= a.v_total;   // no id is left in the queue
+    Team team;
     // learned proposal: this wave's share of the network's A operands
     MlpTiles tiles;
     if constexpr (BIAS == BIAS_MLP) mlp_load_tiles(a.mlp_params, tiles);
@@ -186,13 +244,6 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
     auto load_instance = [&](int ii) {
         const InstDev &I = a.inst[ii];
         C = I.c;
-        stream = I.stream;
-        n_bins = I.n_bins;
-        row_base = I.row_base;
-        thr_base = I.thr_base;
-        dump_slot = I.dump_slot;
-        k_center = I.k_center;
-        t0 = I.t_first;
         if constexpr (BIAS == BIAS_MLP) mc = I.mlp;
         cur_inst = ii;
         j_cap = cap_groups(C.k_max);
@@ -207,23 +258,34 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
         // ---- refill: hand new trajectory ids to lanes that need one
         const uint64_t need_mask = __ballot(need);
         if (need_mask) {
-            const uint32_t n_need = __popcll(need_mask);
-            const uint32_t rank = __popcll(need_mask & lt_mask);
-            const uint64_t avail = res_hi - res_lo;
-            uint64_t v;
-            if (avail >= n_need) {
-                v = res_lo + rank;
-                res_lo += n_need;
-            } else {
-                const uint64_t short_by = n_need - avail;
-                const uint64_t amt = short_by * a.chunk;
-                const int leader = __ffsll(static_cast<unsigned long long>(need_mask)) - 1;
-                unsigned long long b = 0;
-                if (static_cast<int>(lane) == leader) b = atomicAdd(a.queue, static_cast<unsigned long long>(amt));
-                b = __shfl(b, leader, 64);
-                v = (rank < avail) ? res_lo + rank : b + (rank - avail);
-                res_lo = b + short_by;
-                res_hi = b + amt;
+            uint64_t v = ~0ull;
+            if (first) {
+                first = false;
+                // neighbouring waves go to different workgroups; the ones of a CU start their order at
+                // different waves, so that the longest runs' waves lie evenly over its SIMDs too
+                const uint32_t wpw = blockDim.x / 64;
+                const uint32_t w = (threadIdx.x / 64 + blockIdx.x / a.cus * a.turn) % wpw;
+                const uint64_t wave = static_cast<uint64_t>(w) * gridDim.x + blockIdx.x;
+                v = a.spread ? lane * n_waves + wave : wave * a.lane_cap + lane;
+            } else if (!drained) {
+                const uint32_t n_need = __popcll(need_mask);
+                const uint32_t rank = __popcll(need_mask & lt_mask);
+                const uint64_t avail = res_hi - res_lo;
+                if (avail >= n_need) {
+                    v = res_lo + rank;
+                    res_lo += n_need;
+                } else {
+                    const uint64_t short_by = n_need - avail;
+                    const uint64_t amt = short_by * a.chunk;
+                    const int leader = __ffsll(static_cast<unsigned long long>(need_mask)) - 1;
+                    unsigned long long b = 0;
+                    if (static_cast<int>(lane) == leader) b = atomicAdd(a.queue, static_cast<unsigned long long>(amt));
+                    b = n_first + __shfl(b, leader, 64);
+                    v = (rank < avail) ? res_lo + rank : b + (rank - avail);
+                    res_lo = b + short_by;
+                    res_hi = b + amt;
+                }
+                drained = __any(need && v >= a.v_total);   // a wave's ids ascend: no later one is in range
             }
             if (need) {
                 need = false;
@@ -241,12 +303,12 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
                         t = v - a.vbeg_sorted[lo];
                     }
                     if (!SINGLE && ii != cur_inst) load_instance(ii);
-                    t += t0;                   // the run's id: Philox counter and jackknife subset
+                    t += a.inst[ii].t_first;   // the run's id: Philox counter and jackknife subset
                     if (acc.inst != ii) {
                         if (acc.inst >= 0) acc_commit_direct(T, acc);
                         acc_reset(acc, ii);
                     }
-                    noise = philox_run(t, stream, a.key0, a.key1);
+                    noise = philox_run(t, a.inst[ii].stream, a.key0, a.key1);
                     R = RunState{C.phi_in, 0u, 0.0};
                     run = true;
                     active = true;
@@ -256,10 +318,24 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
             }
         }
         if (!__any(active)) break;
+        // few runs and no more to come: the idle lanes draw normals ahead for them
+        const uint64_t act = __ballot(run);
+        const int n_act = __popcll(act);
+        const bool teamed = BIAS != BIAS_MLP && drained && n_act <= 32;
 
         // ---- a pass: groups of four Euler-Maruyama steps, each from one Philox call
         if constexpr (BIAS != BIAS_MLP) {
-            if (run) {
+            if (teamed) {
+                if (team_halves(team.shift, n_act, 8)) team_form(team, act, lt_mask, lane, noise, 8);
+                const F4 z = team_draw(team, lane, R.j, a.key0, a.key1);
+                F4 zn = team_fetch(team, z, 0);
+                const int n_g = team.groups();
+                for (int g = 0; g < n_g; ++g) {
+                    const F4 zg = zn;
+                    if (g + 1 < n_g) zn = team_fetch(team, z, g + 1);
+                    if (run) run = !group4<POT, BIAS>(C, j_cap, zg, 0.0f, R, k);
+                }
+            } else if (run) {
                 const F4 z = normals4(R.j, noise, a.key0, a.key1);
                 run = !group4<POT, BIAS>(C, j_cap, z, 0.0f, R, k);
             }
@@ -317,9 +393,15 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
             }
         }
 
-        // ---- retire finished runs into the workgroup table
-        const bool fin = active && !run;
+        // ---- retire finished runs into the workgroup table: at once while their lanes can take new
+        // ones, else all together when the wave's last run has stopped (a retirement is a chain of
+        // dependent loads and atomics, as long as some tens of passes)
+        const bool all_stopped = !__any(run);
+        const bool fin = active && !run && (!drained || all_stopped);
         if (fin) {
+            const InstDev &I = a.inst[cur_inst];
+            const uint32_t n_bins = I.n_bins, row_base = I.row_base, thr_base = I.thr_base, k_center = I.k_center;
+            const uint64_t t0 = I.t_first;
             const float phi = R.phi;
             const double lw = R.lw;
             const int st = final_status(C, phi, k);
@@ -367,8 +449,6 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
             // instance-wide sums in lane registers
             const double kd = static_cast<double>(k);
             const double lk = log(kd);
-            acc.w = lse2(acc.w, lw);
-            acc.w2 = lse2(acc.w2, 2.0 * lw);
             acc.wk = lse2(acc.wk, lw + lk);
             acc.wk2 = lse2(acc.wk2, lw + 2.0 * lk);
             acc.k2 += kd * kd;
@@ -376,7 +456,7 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
             if (a.dump.n != 0 && ((t - t0) % a.dump.stride) == 0) {
                 const uint64_t idx = (t - t0) / a.dump.stride;
                 if (idx < a.dump.n) {
-                    const uint64_t pos = static_cast<uint64_t>(dump_slot) * a.dump.n + idx;
+                    const uint64_t pos = static_cast<uint64_t>(I.dump_slot) * a.dump.n + idx;
                     a.dump.k[pos] = k;
                     a.dump.lw[pos] = lw;
                     a.dump.phi[pos] = phi;
@@ -396,8 +476,6 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
         const int leader = __ffsll(static_cast<unsigned long long>(pm)) - 1;
         const int inst_l = __shfl(acc.inst, leader, 64);
         const bool mine = pending && acc.inst == inst_l;
-        const double w = wave_lse(mine ? acc.w : -INFINITY);
-        const double w2 = wave_lse(mine ? acc.w2 : -INFINITY);
         const double wk = wave_lse(mine ? acc.wk : -INFINITY);
         const double wk2 = wave_lse(mine ? acc.wk2 : -INFINITY);
         const double k2 = wave_sum(mine ? acc.k2 : 0.0);
@@ -405,7 +483,7 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
         if (static_cast<int>(lane) == leader) {
             LaneAcc r;
             r.inst = inst_l;
-            r.w = w; r.w2 = w2; r.wk = wk; r.wk2 = wk2; r.k2 = k2; r.steps = steps;
+            r.wk = wk; r.wk2 = wk2; r.k2 = k2; r.steps = steps;
             acc_commit_direct(T, r);
         }
         if (mine) pending = false;
@@ -602,27 +680,27 @@ __global__ __launch_bounds__(MERGE_BLOCK) void fpt_merge_kernel(MergeArgs a) {
     } else {
         // one instance's whole-run sums
         const int i = static_cast<int>(blockIdx.x - n_cell_blocks - n_row_blocks);
-        LseAcc f[4];
+        LseAcc f[2];
         double acc[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
         for (int w = tid; w < a.n_wg; w += MERGE_BLOCK) {
             const double *sc = reinterpret_cast<const double *>(a.slices + static_cast<size_t>(w) * L.slice_bytes + L.off_scal) +
                                static_cast<size_t>(i) * 16;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) f[q].add(sc[q]);
+            for (int q = 0; q < 2; ++q) f[q].add(sc[2 + q]);
 #pragma unroll
             for (int q = 0; q < 8; ++q) acc[q] += sc[4 + q];
         }
         // fold each wave, then the waves in order
         for (int h = 32; h >= 1; h >>= 1) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) f[q].fold(__shfl_down(f[q].m, h, 64), __shfl_down(f[q].s, h, 64));
+            for (int q = 0; q < 2; ++q) f[q].fold(__shfl_down(f[q].m, h, 64), __shfl_down(f[q].s, h, 64));
 #pragma unroll
             for (int q = 0; q < 8; ++q) acc[q] += __shfl_down(acc[q], h, 64);
         }
         if (tid % 64 == 0) {
             double *o = &red[0][0] + (tid / 64) * 16;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
+            for (int q = 0; q < 2; ++q) {
                 o[2 * q] = f[q].m;
                 o[2 * q + 1] = f[q].s;
             }
@@ -634,17 +712,15 @@ __global__ __launch_bounds__(MERGE_BLOCK) void fpt_merge_kernel(MergeArgs a) {
             for (int wave = 1; wave < MERGE_BLOCK / 64; ++wave) {
                 const double *o = &red[0][0] + wave * 16;
 #pragma unroll
-                for (int q = 0; q < 4; ++q) f[q].fold(o[2 * q], o[2 * q + 1]);
+                for (int q = 0; q < 2; ++q) f[q].fold(o[2 * q], o[2 * q + 1]);
 #pragma unroll
                 for (int q = 0; q < 8; ++q) acc[q] += o[8 + q];
             }
             const MergeInst m = a.mi[i];
             const ResultLayout RL = result_layout(m.n_bins, J);
             double *V = a.values + m.values_off;
-            V[RL.lse_w_all] = f[0].value();
-            V[RL.lse_w2_all] = f[1].value();
-            V[RL.lse_wk] = f[2].value();
-            V[RL.lse_wk2] = f[3].value();
+            V[RL.lse_wk] = f[0].value();
+            V[RL.lse_wk2] = f[1].value();
             V[RL.sum_k2] = acc[0];
             // Pearson's r of ln w with N over the ended runs (equal to that of log10 w with N)
             const double n = acc[2];
@@ -716,7 +792,34 @@ __device__ void lognormal_bin(double *V, const ResultLayout &RL, uint32_t lr, ui
 // thread per row the chain of 2 J exponentials took 17 to 22 us).
 constexpr int FIN_LANES = 16, FIN_ROWS = 4;
 
+// One wave per instance: the log-sums of w and w^2 over all its runs, from the merged cells.
+__device__ void whole_run_sums(const MergeArgs &a, int i) {
+    const MergeInst m = a.mi[i];
+    const uint32_t J = a.lay.n_sub;
+    const ResultLayout RL = result_layout(m.n_bins, J);
+    double *V = a.values + m.values_off;
+    LseAcc w, w2;
+    for (uint64_t c = threadIdx.x; c < static_cast<uint64_t>(J) * m.n_rows; c += 64) w.add(V[RL.jk_lse_w + c]);
+    for (uint32_t r = threadIdx.x; r < m.n_rows; r += 64) w2.add(V[RL.lse_w2 + r]);
+#pragma unroll
+    for (int h = 32; h >= 1; h >>= 1) {
+        w.fold(__shfl_down(w.m, h, 64), __shfl_down(w.s, h, 64));
+        w2.fold(__shfl_down(w2.m, h, 64), __shfl_down(w2.s, h, 64));
+    }
+    if (threadIdx.x == 0) {
+        V[RL.lse_w_all] = w.value();
+        V[RL.lse_w2_all] = w2.value();
+    }
+}
+
+static_assert(FIN_LANES * FIN_ROWS == 64, "finalize workgroups are one wave");
+
 __global__ __launch_bounds__(FIN_LANES * FIN_ROWS) void fpt_finalize_kernel(MergeArgs a) {
+    const uint32_t row_blocks = (a.lay.n_rows + FIN_ROWS - 1) / FIN_ROWS;
+    if (blockIdx.x >= row_blocks) {
+        whole_run_sums(a, static_cast<int>(blockIdx.x - row_blocks));
+        return;
+    }
     const uint32_t r0 = blockIdx.x * FIN_ROWS + threadIdx.x / FIN_LANES;
     const uint32_t q = threadIdx.x % FIN_LANES;
     const uint32_t RT = a.lay.n_rows, J = a.lay.n_sub;
@@ -867,7 +970,7 @@ hipError_t launch_merge(const MergeArgs &args, int total_rows, int n_sub, hipStr
     hipLaunchKernelGGL(fpt_merge_kernel, dim3(static_cast<unsigned>(blocks)), dim3(MERGE_BLOCK), 0, stream, args);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(fpt_finalize_kernel, dim3((total_rows + FIN_ROWS - 1) / FIN_ROWS), dim3(FIN_LANES * FIN_ROWS), 0, stream, args);
+    hipLaunchKernelGGL(fpt_finalize_kernel, dim3((total_rows + FIN_ROWS - 1) / FIN_ROWS + args.n_inst), dim3(FIN_LANES * FIN_ROWS), 0, stream, args);
     return hipGetLastError();
 }
 

@@ -477,7 +477,8 @@ WsMap ws_map(const Prepared &P, int n_wg) {
     return m;
 }
 
-void resolve_cfg(const Device &d, const Prepared &P, LaunchCfg &c, bool &lds) {
+// Defaults of the launch fields left 0.
+void resolve_cfg(const Prepared &P, LaunchCfg &c) {
     const bool mlp = P.bias == PYFPT_BIAS_MLP;
     if (c.block <= 0) c.block = mlp ? 256 : 512;
     // the learned bias with one active instance fits three waves per SIMD (three 256-thread
@@ -485,11 +486,80 @@ void resolve_cfg(const Device &d, const Prepared &P, LaunchCfg &c, bool &lds) {
     const bool mlp1 = mlp && P.order.size() == 1;
     if (c.wg_per_cu <= 0) c.wg_per_cu = mlp ? (mlp1 ? 3 : 1) : 2;
     if (c.chunk <= 0) c.chunk = 1;
-    // LDS budget per workgroup: the CU's LDS shared by its resident workgroups, less the
-    // single-instance learned sampler's static copy of the network's operand tiles
-    const size_t share = std::min<size_t>(d.max_lds, 160 * 1024 / static_cast<size_t>(c.wg_per_cu));
-    const size_t budget = share - (mlp1 ? std::min(share, fpt::MLP_TILE_LDS_BYTES) : 0);
-    lds = P.lay.slice_bytes <= budget;
+}
+
+// The launch of one call: the workgroups of cfg, or fewer where there are fewer runs than lanes.
+struct Shape {
+    int block = 0, n_wg = 0;
+    int lane_cap = 64;       // lanes of a wave that take runs
+    bool spread = true;      // first ids to a lane of every wave in turn
+    bool lds = false;
+};
+
+// A launch never has more workgroups than fit the chip at once: the first run ids are handed out by
+// position, and a workgroup that started late would start its runs late.  Per CU the closed-form
+// kernels hold 1024 threads, the single-instance learned sampler 768 and the several-instance one
+// 256 (their register budgets).
+int resident_per_cu(const Prepared &P, const LaunchCfg &c) {
+    const int threads = P.bias != PYFPT_BIAS_MLP ? 1024 : P.order.size() == 1 ? 768 : 256;
+    return std::max(1, std::min(c.wg_per_cu, threads / c.block));
+}
+
+// With fewer runs than lanes, a launch's time is its longest runs' steps times the time of a step,
+// which is that of the instructions a SIMD's waves issue for it: per step a wave needs `step`
+// instructions for stepping and `draw` / G for normals when its 64 / G runs leave G lanes to each
+// (see Team), one wave issues an instruction per 5 cycles and W >= 2 waves one per 2.4 together.
+// The runs per wave are those with the least W (step + draw / G), W = waves per SIMD, but no less
+// than the chain of dependent operations of one step (about 130 cycles).  500 direct runs of 5.8e3
+// steps took 1.18 ms at 64 runs per wave (whole call) and 0.65 ms at 8; 2e5 diffusion-dominated runs,
+// whose last ones end on teams, 14.7 and 8.7 ms.
+Shape launch_shape(const Device &d, const Prepared &P, const LaunchCfg &c) {
+    Shape s;
+    s.block = c.block;
+    const int per_cu = resident_per_cu(P, c);
+    s.n_wg = d.cus * per_cu;
+    const uint64_t full_waves = static_cast<uint64_t>(s.n_wg) * (c.block / 64);
+    if (P.v_total < full_waves * 64) {
+        const uint64_t simds = static_cast<uint64_t>(d.cus) * 4;
+        const double step = 22.0, draw = 38.0, chain = 130.0;
+        double best = INFINITY;
+        uint64_t waves = full_waves;
+        for (int cap = 64; cap >= 8; cap /= 2) {
+            const uint64_t w = std::max<uint64_t>(1, (P.v_total + cap - 1) / cap);
+            if (w > full_waves) break;
+            const double W = static_cast<double>(std::max<uint64_t>(2, (w + simds - 1) / simds));
+            const double cost = std::max(chain, 2.4 * W * (step + draw * cap / 64));
+            if (cost < best) {
+                best = cost;
+                s.lane_cap = cap;
+                waves = w;
+            }
+            if (P.bias == PYFPT_BIAS_MLP) break;
+        }
+        // a workgroup of four waves puts one on each SIMD of a CU; up to two waves per CU go alone;
+        // never more workgroups than cfg's grid, which the workspace is sized for
+        const uint64_t want = waves <= 2ull * d.cus ? 1 : std::min(4, c.block / 64);
+        const uint64_t per_wg = std::max<uint64_t>(want, (waves + s.n_wg - 1) / s.n_wg);
+        s.block = static_cast<int>(64 * per_wg);
+        s.n_wg = static_cast<int>((waves + per_wg - 1) / per_wg);
+    }
+    // The queue is ordered by expected length, and the first ids of a batch are its longest runs.  As
+    // long as they fill no more than half of every wave's lanes, one to each wave in turn leaves all
+    // waves with few long runs at the end, which the idle lanes then help (64 instances of 2000 runs:
+    // 137 ms spread, 181 ms wave by wave); where they fill more, wave by wave lets the waves of
+    // shorter runs end and leave their SIMDs to the others (six instances of 1e5 runs, 3e5 of them
+    // capped: 193 ms spread, 180 ms wave by wave).
+    const uint64_t lanes = static_cast<uint64_t>(s.n_wg) * s.block;
+    uint64_t longest = 0;
+    for (uint32_t i : P.order)
+        if (2.0 * P.inst[i].k_center >= P.inst[P.order[0]].k_center) longest += P.inst[i].n_traj;
+    s.spread = longest * 2 <= lanes;
+    // tables go to LDS where the workgroups that share a CU can all hold theirs, beside the
+    // single-instance learned sampler's copy of the network's operand tiles
+    const size_t share = std::min<size_t>(d.max_lds, 160 * 1024 / static_cast<size_t>(std::max(1, (s.n_wg + d.cus - 1) / d.cus)));
+    const bool mlp1 = P.bias == PYFPT_BIAS_MLP && P.order.size() == 1;
+    s.lds = P.lay.slice_bytes <= share - (mlp1 ? std::min(share, fpt::MLP_TILE_LDS_BYTES) : 0);
+    return s;
 }
 
 std::string signature(const Prepared &P, uint64_t seed_unused) {
@@ -509,15 +579,15 @@ int run_prepared(Device &d, const Prepared &P, uint64_t seed, const LaunchCfg &c
                  hipStream_t stream, void *ws, size_t ws_bytes, bool use_graph, float *timing,
                  bool noalloc = false) {
     LaunchCfg cfg = cfg_in;
-    bool lds = false;
-    resolve_cfg(d, P, cfg, lds);
+    resolve_cfg(P, cfg);
     if (cfg.block < 64 || cfg.block > 1024 || cfg.block % 64)
         return fail(PYFPT_EINVAL, "block must be a multiple of 64 in 64..1024");
     if (P.bias == PYFPT_BIAS_MLP && cfg.block > 256)
         return fail(PYFPT_EINVAL, "the learned bias runs with block <= 256");
     if (cfg.wg_per_cu * cfg.block > 2048) return fail(PYFPT_EINVAL, "wg_per_cu * block must be <= 2048");
-    const int n_wg = d.cus * cfg.wg_per_cu;
-    const WsMap m = ws_map(P, n_wg);
+    // the workspace is sized for cfg's whole grid, also where fewer runs take a smaller one
+    const WsMap m = ws_map(P, d.cus * cfg.wg_per_cu);
+    const Shape shape = launch_shape(d, P, cfg);
     if (ws_bytes < m.total) return fail(PYFPT_ENOMEM, "workspace too small: need %zu bytes, have %zu", m.total, ws_bytes);
     unsigned char *W = static_cast<unsigned char *>(ws);
 
@@ -568,6 +638,10 @@ int run_prepared(Device &d, const Prepared &P, uint64_t seed, const LaunchCfg &c
     sa.slices = W + m.slices;
     sa.lay = P.lay;
     sa.chunk = static_cast<uint32_t>(cfg.chunk);
+    sa.lane_cap = static_cast<uint32_t>(shape.lane_cap);
+    sa.spread = shape.spread ? 1u : 0u;
+    sa.cus = static_cast<uint32_t>(d.cus);
+    sa.turn = static_cast<uint32_t>(std::max(1, 4 * d.cus / std::max(1, shape.n_wg)));
     sa.mlp_params = P.mlp_params;
     sa.mlp_every = P.mlp_every;
     if (opt && opt->dump.n) {
@@ -582,19 +656,19 @@ int run_prepared(Device &d, const Prepared &P, uint64_t seed, const LaunchCfg &c
     }
     MergeArgs ma{};
     ma.slices = W + m.slices;
-    ma.n_wg = n_wg;
+    ma.n_wg = shape.n_wg;
     ma.lay = P.lay;
     ma.mi = reinterpret_cast<const MergeInst *>(W + m.mi);
     ma.n_inst = static_cast<int32_t>(P.mi.size());
     ma.edges = reinterpret_cast<const double *>(W + m.edges);
     ma.counts = reinterpret_cast<uint64_t *>(W + m.counts);
     ma.values = reinterpret_cast<double *>(W + m.values);
-    const size_t lds_bytes = lds ? P.lay.slice_bytes : 0;
+    const size_t lds_bytes = shape.lds ? P.lay.slice_bytes : 0;
 
     auto enqueue = [&](bool timed) -> int {
         HIP_TRY(launch_init_queue(sa.queue, stream), "launch init");
         if (timed) HIP_TRY(hipEventRecord(d.ev[0], stream), "event");
-        HIP_TRY(launch_step(P.pot, P.bias, lds, n_wg, cfg.block, lds_bytes, sa, stream), "launch step kernel");
+        HIP_TRY(launch_step(P.pot, P.bias, shape.lds, shape.n_wg, shape.block, lds_bytes, sa, stream), "launch step kernel");
         if (timed) HIP_TRY(hipEventRecord(d.ev[1], stream), "event");
         HIP_TRY(launch_merge(ma, static_cast<int>(P.lay.n_rows), static_cast<int>(P.n_sub), stream), "launch merge");
         if (timed) HIP_TRY(hipEventRecord(d.ev[2], stream), "event");
@@ -610,8 +684,9 @@ int run_prepared(Device &d, const Prepared &P, uint64_t seed, const LaunchCfg &c
         };
         put(&sa, sizeof sa);
         put(&ma, sizeof ma);
-        put(&cfg, sizeof cfg);
-        put(&lds, sizeof lds);
+        put(&shape.block, sizeof shape.block);
+        put(&shape.n_wg, sizeof shape.n_wg);
+        put(&shape.lds, sizeof shape.lds);
         int pb[2] = {P.pot, P.bias};
         put(pb, sizeof pb);
         put(&stream, sizeof stream);
@@ -687,7 +762,7 @@ int autotune(Device &d, const pyfpt_instance *ins, int n_inst, uint64_t seed, hi
         return PYFPT_OK;
     }
     static const LaunchCfg cands[] = {
-        {256, 4, 1}, {512, 2, 1}, {1024, 1, 1}, {256, 8, 1}, {512, 2, 4},
+        {256, 4, 1}, {512, 2, 1}, {1024, 1, 1}, {512, 2, 4},
     };
     // about one trajectory per lane of the largest grid, split over instances by their share
     const double lanes = static_cast<double>(d.cus) * 2048.0;
@@ -704,10 +779,8 @@ int autotune(Device &d, const pyfpt_instance *ins, int n_inst, uint64_t seed, hi
     best = LaunchCfg{512, 2, 1};
     std::vector<uint64_t> counts(C.counts_total);
     for (const LaunchCfg &c : cands) {
-        if (P.bias == PYFPT_BIAS_MLP && c.block > 256) continue;
         LaunchCfg cc = c;
-        bool lds = false;
-        resolve_cfg(d, C, cc, lds);
+        resolve_cfg(C, cc);
         const int n_wg = d.cus * cc.wg_per_cu;
         const WsMap m = ws_map(C, n_wg);
         void *ws = nullptr;
@@ -745,16 +818,17 @@ int run_batch_impl(const pyfpt_instance *ins, int n_inst, uint64_t seed, pyfpt_r
         cfg.wg_per_cu = opt->wg_per_cu;
         cfg.chunk = opt->chunk;
     }
-    if ((cfg.block <= 0 || cfg.wg_per_cu <= 0 || cfg.chunk <= 0) && P.v_total > 0) {
-        LaunchCfg t;
-        if ((rc = autotune(*d, ins, n_inst, seed, stream, P, t))) return rc;
+    if ((cfg.block <= 0 || cfg.wg_per_cu <= 0 || cfg.chunk <= 0) && P.bias != PYFPT_BIAS_MLP) {
+        // runs that all fit the chip at once take the shape launch_shape gives them; the learned
+        // sampler has one resident shape, its default
+        LaunchCfg t{256, 4, 1};
+        if (P.v_total > static_cast<uint64_t>(d->cus) * 1024 && (rc = autotune(*d, ins, n_inst, seed, stream, P, t))) return rc;
         if (cfg.block <= 0) cfg.block = t.block;
         if (cfg.wg_per_cu <= 0) cfg.wg_per_cu = t.wg_per_cu;
         if (cfg.chunk <= 0) cfg.chunk = t.chunk;
     }
     LaunchCfg rcfg = cfg;
-    bool lds;
-    resolve_cfg(*d, P, rcfg, lds);
+    resolve_cfg(P, rcfg);
     const int n_wg = d->cus * rcfg.wg_per_cu;
     const WsMap m = ws_map(P, n_wg);
     void *ws = nullptr;
@@ -825,8 +899,7 @@ int run_batch_noalloc_impl(const pyfpt_instance *ins, int n_inst, uint64_t seed,
             cfg.wg_per_cu = opt->wg_per_cu;
             cfg.chunk = opt->chunk;
         }
-        bool lds;
-        resolve_cfg(*d, P, cfg, lds);          // no autotuning: 0 fields take the defaults
+        resolve_cfg(P, cfg);                   // no autotuning: 0 fields take the defaults
         const int n_wg = d->cus * cfg.wg_per_cu;
         if (cfg.wg_per_cu < 1 || cfg.wg_per_cu > 64) return fail(PYFPT_EINVAL, "wg_per_cu must be 1..64");
         const WsMap m = ws_map(P, n_wg);
@@ -1029,8 +1102,7 @@ int pyfpt_workspace_size(const pyfpt_instance *inst, int32_t n_inst, const pyfpt
             c.chunk = opt->chunk;
         }
         if (c.wg_per_cu <= 0) c.wg_per_cu = 8;   // the largest grid the autotuner may pick
-        bool lds;
-        resolve_cfg(*d, P, c, lds);
+        resolve_cfg(P, c);
         *bytes = ws_map(P, d->cus * c.wg_per_cu).total;
         return PYFPT_OK;
     } catch (...) {
