@@ -225,21 +225,17 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
     bool first = true;
     bool drained = n_first >= a.v_total;   // no id is left in the queue
     Team team;
-    // learned proposal: this wave's share of the network's A operands
-    MlpTiles tiles;
-    if constexpr (BIAS == BIAS_MLP) mlp_load_tiles(a.mlp_params, tiles);
-    // the single-instance learned sampler reads its operand tiles from one LDS copy
-    constexpr bool TILES_LDS = BIAS == BIAS_MLP && SINGLE;
-    __shared__ bf16x8 tile_lds[TILES_LDS ? MLP_N_FRAG * 64 : 1];
-    if constexpr (TILES_LDS) {
-        if (threadIdx.x < 64) mlp_store_tiles_lds(tiles, tile_lds);
+    // learned proposal: one copy of the network's A operands per workgroup
+    __shared__ bf16x8 tile_lds[BIAS == BIAS_MLP ? MLP_N_FRAG * 64 : 1];
+    if constexpr (BIAS == BIAS_MLP) {
+        if (threadIdx.x < 64) {
+            MlpTiles tiles;
+            mlp_load_tiles(a.mlp_params, tiles);
+            mlp_store_tiles_lds(tiles, tile_lds);
+        }
         __syncthreads();
     }
     MlpConsts mc{};
-    auto network = [&](float phi_, float N_) {
-        if constexpr (TILES_LDS) return mlp_forward_lds(tile_lds, mc, phi_, N_);
-        else return mlp_forward(tiles, mc, phi_, N_);
-    };
     int single_inst = 0;
     auto load_instance = [&](int ii) {
         const InstDev &I = a.inst[ii];
@@ -321,7 +317,7 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
         // few runs and no more to come: the idle lanes draw normals ahead for them
         const uint64_t act = __ballot(run);
         const int n_act = __popcll(act);
-        const bool teamed = BIAS != BIAS_MLP && drained && n_act <= 32;
+        const bool teamed = drained && n_act <= 32;
 
         // ---- a pass: groups of four Euler-Maruyama steps, each from one Philox call
         if constexpr (BIAS != BIAS_MLP) {
@@ -345,6 +341,16 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
             // start at k = 0 and refill only between passes, so every lane of the wave is at a
             // multiple of the pass length here and the evaluation points of all lanes coincide.
             const int E = a.mlp_every;
+            // a team's runs fit one block of 32 columns, slot c in lane c: half the network's work,
+            // and with E >= 8 the normals of E / 4 groups shared out besides
+            const int most = E >= 8 ? E / 4 : 2;
+            if (teamed && team_halves(team.shift, n_act, most)) team_form(team, act, lt_mask, lane, noise, most);
+            auto network = [&](float phi_, float N_) {
+                const MlpIn x = mlp_input(mc, phi_, N_);
+                if (!teamed) return mc.out_scale * mlp_forward_lds(tile_lds, x);
+                const MlpIn xs{lane_read(team.slot_lane, x.lo), lane_read(team.slot_lane, x.hi)};
+                return mc.out_scale * lane_read(team.fetch0, mlp_block_lds(tile_lds, xs, 0));
+            };
             // One evaluation per pass of E = 4, 8 or 16 steps.  The pass's normals do not depend
             // on the network, so they are drawn before it and the scheduler interleaves their
             // vector work with the evaluation's matrix-core chains (they are the normals of
@@ -354,11 +360,22 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
             auto pass = [&](auto nq_tag) {
                 constexpr int NQ = decltype(nq_tag)::value;
                 F4 zz[NQ];
+                if (NQ > 1 && teamed) {
+                    F4 z{};
 #pragma unroll
-                for (int q = 0; q < NQ; ++q) {
-                    zz[q] = normals4(R.j + q, noise, a.key0, a.key1);
-                    // four draws at once would not fit the registers
-                    if (q == 1) __builtin_amdgcn_sched_barrier(0);
+                    for (int q = 0; q < NQ; q += 2) {
+                        const int g = q & (team.groups() - 1);     // group within the batch (2 or 4 groups)
+                        if (g == 0) z = team_draw(team, lane, R.j + q, a.key0, a.key1);
+                        zz[q] = team_fetch(team, z, g);
+                        if constexpr (NQ > 1) zz[q + 1] = team_fetch(team, z, g + 1);
+                    }
+                } else {
+#pragma unroll
+                    for (int q = 0; q < NQ; ++q) {
+                        zz[q] = normals4(R.j + q, noise, a.key0, a.key1);
+                        // four draws at once would not fit the registers
+                        if (q == 1) __builtin_amdgcn_sched_barrier(0);
+                    }
                 }
                 __builtin_amdgcn_s_setprio(2);
                 const float r_mlp = network(R.phi, static_cast<float>(4u * R.j) * C.dN);
@@ -497,16 +514,15 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
     }
 }
 
-// Workgroups of up to 1024 threads for the closed-form biases; the learned bias holds the
-// network's operands in registers and runs with up to 256 threads (one wave per SIMD can use
-// the whole register file).
+// Workgroups of up to 1024 threads for the closed-form biases; up to 256 for the learned bias, whose
+// several-instance kernel fits two waves per SIMD.
 template <int POT, int BIAS, bool LDS>
 __global__ __launch_bounds__(1024) void fpt_step_kernel(StepArgs a) {
     fpt_step_body<POT, BIAS, LDS>(a);
 }
 
 template <int POT, bool LDS>
-__global__ __launch_bounds__(256) void fpt_step_mlp_kernel(StepArgs a) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void fpt_step_mlp_kernel(StepArgs a) {
     fpt_step_body<POT, BIAS_MLP, LDS>(a);
 }
 

@@ -499,9 +499,9 @@ struct Shape {
 // A launch never has more workgroups than fit the chip at once: the first run ids are handed out by
 // position, and a workgroup that started late would start its runs late.  Per CU the closed-form
 // kernels hold 1024 threads, the single-instance learned sampler 768 and the several-instance one
-// 256 (their register budgets).
+// 512 (their register budgets).
 int resident_per_cu(const Prepared &P, const LaunchCfg &c) {
-    const int threads = P.bias != PYFPT_BIAS_MLP ? 1024 : P.order.size() == 1 ? 768 : 256;
+    const int threads = P.bias != PYFPT_BIAS_MLP ? 1024 : P.order.size() == 1 ? 768 : 512;
     return std::max(1, std::min(c.wg_per_cu, threads / c.block));
 }
 
@@ -521,20 +521,28 @@ Shape launch_shape(const Device &d, const Prepared &P, const LaunchCfg &c) {
     const uint64_t full_waves = static_cast<uint64_t>(s.n_wg) * (c.block / 64);
     if (P.v_total < full_waves * 64) {
         const uint64_t simds = static_cast<uint64_t>(d.cus) * 4;
-        const double step = 22.0, draw = 38.0, chain = 130.0;
+        const bool mlp = P.bias == PYFPT_BIAS_MLP;
+        const int E = P.mlp_every;
+        const int most = mlp ? std::max(2, E / 4) : 8;     // the largest G (see Team)
         double best = INFINITY;
         uint64_t waves = full_waves;
         for (int cap = 64; cap >= 8; cap /= 2) {
             const uint64_t w = std::max<uint64_t>(1, (P.v_total + cap - 1) / cap);
             if (w > full_waves) break;
             const double W = static_cast<double>(std::max<uint64_t>(2, (w + simds - 1) / simds));
-            const double cost = std::max(chain, 2.4 * W * (step + draw * cap / 64));
+            const int G = std::min(64 / cap, mlp ? std::max(1, E / 4) : most);
+            double instr = 22.0 + 38.0 / G, chain = 130.0;
+            if (mlp) {
+                instr += (cap > 32 ? 1040.0 : 520.0) / E;
+                chain += 600.0 / E;
+            }
+            const double cost = std::max(chain, 2.4 * W * instr);
             if (cost < best) {
                 best = cost;
                 s.lane_cap = cap;
                 waves = w;
             }
-            if (P.bias == PYFPT_BIAS_MLP) break;
+            if (64 / cap >= most) break;
         }
         // a workgroup of four waves puts one on each SIMD of a CU; up to two waves per CU go alone;
         // never more workgroups than cfg's grid, which the workspace is sized for
@@ -555,10 +563,9 @@ Shape launch_shape(const Device &d, const Prepared &P, const LaunchCfg &c) {
         if (2.0 * P.inst[i].k_center >= P.inst[P.order[0]].k_center) longest += P.inst[i].n_traj;
     s.spread = longest * 2 <= lanes;
     // tables go to LDS where the workgroups that share a CU can all hold theirs, beside the
-    // single-instance learned sampler's copy of the network's operand tiles
+    // learned sampler's copy of the network's operand tiles
     const size_t share = std::min<size_t>(d.max_lds, 160 * 1024 / static_cast<size_t>(std::max(1, (s.n_wg + d.cus - 1) / d.cus)));
-    const bool mlp1 = P.bias == PYFPT_BIAS_MLP && P.order.size() == 1;
-    s.lds = P.lay.slice_bytes <= share - (mlp1 ? std::min(share, fpt::MLP_TILE_LDS_BYTES) : 0);
+    s.lds = P.lay.slice_bytes <= share - (P.bias == PYFPT_BIAS_MLP ? std::min(share, fpt::MLP_TILE_LDS_BYTES) : 0);
     return s;
 }
 
@@ -828,6 +835,7 @@ int run_batch_impl(const pyfpt_instance *ins, int n_inst, uint64_t seed, pyfpt_r
         if (cfg.chunk <= 0) cfg.chunk = t.chunk;
     }
     LaunchCfg rcfg = cfg;
+    if (rcfg.wg_per_cu <= 0 && P.bias == PYFPT_BIAS_MLP && P.order.size() > 1) rcfg.wg_per_cu = 2;   // two waves per SIMD
     resolve_cfg(P, rcfg);
     const int n_wg = d->cus * rcfg.wg_per_cu;
     const WsMap m = ws_map(P, n_wg);
