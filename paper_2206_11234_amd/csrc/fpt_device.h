@@ -360,21 +360,27 @@ __device__ __forceinline__ uint32_t cap_groups(uint32_t k_max) { return (k_max >
 // computed is dropped).  Tests after every step cost 7 of 28 instructions, and the branches around
 // them kept the compiler from overlapping one step's arithmetic with the next's normals.
 // Returns whether the run stopped, with its step count in k.
+// H, where not NULL, gains fma(r, dN, sqrt(dN) xi) of each step taken, in step order.
 template <int POT, int BIAS>
-__device__ __forceinline__ bool group4(const StepConsts &C, uint32_t j_cap, const F4 &z, float r_net, RunState &R, uint32_t &k) {
+__device__ __forceinline__ bool group4(const StepConsts &C, uint32_t j_cap, const F4 &z, float r_net, RunState &R, uint32_t &k,
+                                       float *H = nullptr) {
     const float n[4] = {z.a, z.b, z.c, z.d};
-    float p[4];
+    float p[4], h[4];
     double w[4];
     float phi = R.phi;
     double lw = R.lw;
+    float sum = H ? *H : 0.0f;
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
         float dlw, sxi;
-        (void)em_step<POT, BIAS>(C, phi, n[s], r_net, dlw, sxi);
+        const float r = em_step<POT, BIAS>(C, phi, n[s], r_net, dlw, sxi);
         if constexpr (BIAS != BIAS_NONE) lw += static_cast<double>(dlw);
+        if (H) sum = sum + __builtin_fmaf(r, C.dN, sxi);
         p[s] = phi;
         w[s] = lw;
+        h[s] = sum;
     }
+    if (H) *H = sum;
     const float lo = __builtin_fminf(__builtin_fminf(p[0], p[1]), __builtin_fminf(p[2], p[3]));
     float hi;       // (the compiler's own maximum first canonicalises each operand)
     asm("v_max3_f32 %0, %1, %2, %3" : "=v"(hi) : "v"(p[0]), "v"(p[1]), "v"(p[2]));
@@ -392,6 +398,7 @@ __device__ __forceinline__ bool group4(const StepConsts &C, uint32_t j_cap, cons
             if (p[q] <= C.phi_end || p[q] > C.phi_esc || static_cast<uint32_t>(q + 1) >= left) s = q;
         R.phi = s == 0 ? p[0] : s == 1 ? p[1] : s == 2 ? p[2] : p[3];
         R.lw = s == 0 ? w[0] : s == 1 ? w[1] : s == 2 ? w[2] : w[3];
+        if (H) *H = s == 0 ? h[0] : s == 1 ? h[1] : s == 2 ? h[2] : h[3];
         k = 4 * j + 1 + static_cast<uint32_t>(s);
     }
     return stop;

@@ -33,6 +33,7 @@
 #include <math.h>
 
 #include "fpt_kernels.h"
+#include "fpt_team.h"
 #include "fpt_train.h"
 
 namespace fpt {
@@ -40,78 +41,120 @@ namespace fpt {
 // ---------------------------------------------------------------------------
 // replay into records
 // ---------------------------------------------------------------------------
+// One wave replays up to `slots` paths: with fewer paths than the chip has lanes a replay lasts as
+// long as its longest path's steps at a lone wave's rate, so a wave takes 16 or 32 paths and its other
+// lanes draw normals ahead for them (Team) and leave half of the network's columns out.
 template <int POT, int BIAS>
 __global__ __launch_bounds__(256) void fpt_record_kernel(RecordArgs a) {
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    const bool have = i < a.n_paths;
+    const uint32_t lane = __lane_id();
+    const uint32_t wave = blockIdx.x * (blockDim.x / 64) + threadIdx.x / 64;
+    const uint32_t i = wave * a.slots + lane;
+    const bool have = lane < a.slots && i < a.n_paths;
     const StepConsts C = a.inst.c;
-    MlpTiles tiles;
-    if constexpr (BIAS == BIAS_MLP) mlp_load_tiles(a.mlp_params, tiles);
+    const uint32_t j_cap = cap_groups(C.k_max);
+    __shared__ bf16x8 tile_lds[BIAS == BIAS_MLP ? MLP_N_FRAG * 64 : 1];
+    if constexpr (BIAS == BIAS_MLP) {
+        if (threadIdx.x < 64) {
+            MlpTiles tiles;
+            mlp_load_tiles(a.mlp_params, tiles);
+            mlp_store_tiles_lds(tiles, tile_lds);
+        }
+        __syncthreads();
+    }
     const MlpConsts mc = a.inst.mlp;
     const uint64_t t = have ? a.t_ids[i] : 0;
     const uint64_t base = have ? a.rec_off[i] : 0;
     const uint64_t cap = have ? a.rec_off[i + 1] - base : 0;
-    const uint32_t emask = static_cast<uint32_t>(a.group - 1);
+    const uint32_t group = static_cast<uint32_t>(a.group), stride = static_cast<uint32_t>(a.stride);
     const PhiloxRun noise = philox_run(t, a.inst.stream, a.key0, a.key1);
-    float phi = C.phi_in;
-    uint32_t k = 0;
-    double lw = 0.0;
+    RunState R{C.phi_in, 0u, 0.0};
+    uint32_t k = 0;             // step count of a run that has stopped
     bool run = have;
-    float H = 0.0f, phi_e = phi;
-    uint32_t k_e = 0, n_e = 0;
+    float H = 0.0f, phi_e = R.phi;
+    uint32_t k_e = 0;           // first step of the record's group
+    uint32_t grp = 0;           // its index
     uint64_t n_rec = 0;
+    auto record = [&](uint32_t k_end) {      // the group k_e .. k_end - 1 is complete
+        if (grp % stride == 0) {
+            if (n_rec < cap) {
+                TrainRec rec;
+                rec.phi = phi_e;
+                rec.k = k_e;
+                rec.H = H;
+                rec.pn = (i << 5) | (k_end - k_e);
+                a.rec[base + n_rec] = rec;
+            }
+            n_rec += 1;
+        }
+        grp += 1;
+        k_e = k_end;
+        phi_e = R.phi;
+        H = 0.0f;
+    };
     // the sampling network (if any) is evaluated every E steps, wave-wide: a pass covers
     // max(4, E) steps, so every lane is at a multiple of the pass length at its start
     const int E = (BIAS == BIAS_MLP) ? a.mlp_every : 4;
     const int n_q = E > 4 ? E >> 2 : 1;
-    while (__any(run)) {
-        float r_mlp = 0.0f;
-        for (int q = 0; q < n_q; ++q) {
-            if constexpr (BIAS == BIAS_MLP) {
-                if (q * 4 % E == 0) r_mlp = mlp_forward(tiles, mc, phi, static_cast<float>(k) * C.dN);
-            }
-            F4 z{};
-            if (run) z = normals4(k >> 2, noise, a.key0, a.key1);
-            const float zs[4] = {z.a, z.b, z.c, z.d};
+    // lanes share normals between the groups of a pass, or of G groups without a network
+    const int most = BIAS == BIAS_MLP ? (n_q > 1 ? n_q : 2) : 8;
+    const bool teamed = a.slots <= 32;
+    const bool share = teamed && (BIAS != BIAS_MLP || n_q > 1);
+    Team team;
+    if (teamed) {
+        const uint64_t paths = __ballot(have);
+        team_form(team, paths, (lane == 0) ? 0ull : (~0ull >> (64 - lane)), lane, noise, most);
+    }
+    auto network = [&](float phi_, float N_) {
+        const MlpIn x = mlp_input(mc, phi_, N_);
+        if (!teamed) return mc.out_scale * mlp_forward_lds(tile_lds, x);
+        const MlpIn xs{lane_read(team.slot_lane, x.lo), lane_read(team.slot_lane, x.hi)};
+        return mc.out_scale * lane_read(team.fetch0, mlp_block_lds(tile_lds, xs, 0));
+    };
+    F4 batch{};
+    float r_mlp = 0.0f;
+    const int batch_mask = share ? team.groups() - 1 : 0;
+    for (int q = 0; __any(run); ++q) {
+        // q-th group of four steps; the lanes still running are all in their group q
+        if constexpr (BIAS == BIAS_MLP) {
+            if ((q & (n_q - 1)) == 0) r_mlp = network(R.phi, static_cast<float>(4u * R.j) * C.dN);
+        }
+        F4 z;
+        if (share) {
+            if ((q & batch_mask) == 0) batch = team_draw(team, lane, R.j, a.key0, a.key1);
+            z = team_fetch(team, batch, q & batch_mask);
+        } else {
+            z = normals4(R.j, noise, a.key0, a.key1);
+        }
+        if (E == 1 || group < 4) {
+            // the network before every step, or a record of every step
+            const float ns[4] = {z.a, z.b, z.c, z.d};
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
+                const uint32_t ks = 4u * R.j + s;
                 if constexpr (BIAS == BIAS_MLP) {
-                    if (s > 0 && E == 1) r_mlp = mlp_forward(tiles, mc, phi, static_cast<float>(k) * C.dN);
+                    if (s > 0 && E == 1) r_mlp = network(R.phi, static_cast<float>(ks) * C.dN);
                 }
                 if (run) {
-                    if ((k & emask) == 0) {
-                        phi_e = phi;
-                        k_e = k;
-                        H = 0.0f;
-                        n_e = 0;
-                    }
                     float dlw, sxi;
-                    const float r = em_step<POT, BIAS>(C, phi, zs[s], r_mlp, dlw, sxi);
-                    lw += static_cast<double>(dlw);
-                    k += 1;
-                    run = !stops(C, phi, k);
+                    const float r = em_step<POT, BIAS>(C, R.phi, ns[s], r_mlp, dlw, sxi);
+                    R.lw += static_cast<double>(dlw);
                     H = H + __builtin_fmaf(r, C.dN, sxi);
-                    n_e += 1;
-                    if ((k & emask) == 0 || !run) {
-                        const uint32_t grp = k_e / static_cast<uint32_t>(a.group);
-                        if (grp % static_cast<uint32_t>(a.stride) == 0 && n_rec < cap) {
-                            TrainRec R;
-                            R.phi = phi_e;
-                            R.k = k_e;
-                            R.H = H;
-                            R.pn = (i << 5) | n_e;
-                            a.rec[base + n_rec] = R;
-                        }
-                        if (grp % static_cast<uint32_t>(a.stride) == 0) n_rec += 1;
-                    }
+                    k = ks + 1;
+                    run = !stops(C, R.phi, k);
+                    if ((k & (group - 1)) == 0 || !run) record(k);
                 }
             }
+            if (run) R.j += 1;
+        } else if (run) {
+            run = !group4<POT, BIAS>(C, j_cap, z, r_mlp, R, k, &H);
+            const uint32_t k_end = run ? 4u * R.j : k;
+            if ((k_end & (group - 1)) == 0 || !run) record(k_end);
         }
     }
     if (have) {
         a.k_out[i] = k;
-        a.lw_out[i] = lw;
-        a.st_out[i] = final_status(C, phi, k);
+        a.lw_out[i] = R.lw;
+        a.st_out[i] = final_status(C, R.phi, k);
         a.n_rec_out[i] = n_rec;
     }
 }
@@ -490,8 +533,10 @@ __global__ __launch_bounds__(256) void fpt_to_bf16_kernel(const float *theta, ui
 // ---------------------------------------------------------------------------
 template <int POT, int BIAS>
 static hipError_t launch_record_t(const RecordArgs &a, hipStream_t s) {
-    const unsigned blocks = (a.n_paths + 255) / 256;
-    hipLaunchKernelGGL((fpt_record_kernel<POT, BIAS>), dim3(blocks), dim3(256), 0, s, a);
+    // one wave per workgroup while the waves fit the chip's SIMDs once, else four
+    const unsigned waves = (a.n_paths + a.slots - 1) / a.slots;
+    const unsigned per_wg = waves <= 1024 ? 1 : 4;
+    hipLaunchKernelGGL((fpt_record_kernel<POT, BIAS>), dim3((waves + per_wg - 1) / per_wg), dim3(64 * per_wg), 0, s, a);
     return hipGetLastError();
 }
 

@@ -982,6 +982,10 @@ int records_device(const Prepared &P, uint64_t seed, int group, int stride, cons
     ra.group = group;
     ra.stride = stride;
     ra.mlp_every = P.mlp_every;
+    // paths per wave: as few as leave each SIMD two waves (launch_shape's balance)
+    ra.slots = 64;
+    const uint32_t least = P.bias == PYFPT_BIAS_MLP ? (P.mlp_every >= 16 ? 16 : 32) : 8;
+    while (ra.slots > least && (n_paths + ra.slots / 2 - 1) / (ra.slots / 2) <= 2048) ra.slots /= 2;
     ra.mlp_params = P.mlp_params;
     ra.rec_off = d_off;
     ra.rec = d_rec;
