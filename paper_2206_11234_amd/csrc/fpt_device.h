@@ -285,14 +285,20 @@ __device__ __forceinline__ float drift(const FieldTerms<POT> &T, float B) {
 }
 
 // r = B/S in noise units (Sec. 2.3 eq. eq_importance_sampling_amplitude_general
-// with f = S, and the power law of Sec. 3.4).
-template <int BIAS>
+// with f = S, and the power law of Sec. 3.4).  P > 0: the power law's exponent, known at compile time; 0: any.
+template <int BIAS, int P>
 __device__ __forceinline__ float bias_ratio(const StepConsts &C, float phi, float S) {
     if constexpr (BIAS == BIAS_NOISE_SCALED) {
         return C.A;
     } else if constexpr (BIAS == BIAS_POWER) {
         float pw = 1.0f;
-        for (int i = 0; i < C.p; ++i) pw = pw * phi;
+        if constexpr (P > 0) {
+            pw = phi;
+#pragma unroll
+            for (int i = 1; i < P; ++i) pw = pw * phi;
+        } else {
+            for (int i = 0; i < C.p; ++i) pw = pw * phi;
+        }
         return (C.A * pw) * recip_f32(S);
     } else {
         return 0.0f;
@@ -312,7 +318,7 @@ __device__ __forceinline__ int final_status(const StepConsts &C, float phi, uint
 // 2.1, Sec. 3), and the weight increment dlw = -r (r dN/2 + sqrt(dN) xi) that the caller adds to
 // ln w in binary64.  n = -xi/2; r_net is the bias when it comes from the learned network.  Returns
 // r and writes sqrt(dN) xi, which the training replay reuses.
-template <int POT, int BIAS>
+template <int POT, int BIAS, int P = 0>
 __device__ __forceinline__ float em_step(const StepConsts &C, float &phi, float n, float r_net, float &dlw, float &sxi) {
     const FieldTerms<POT> T = field_terms<POT>(C, phi);
     float r = 0.0f, drift_dN;
@@ -321,7 +327,7 @@ __device__ __forceinline__ float em_step(const StepConsts &C, float &phi, float 
         drift_dN = drift<POT, false>(T, 0.0f) * C.dN;
     } else {
         if constexpr (BIAS == BIAS_MLP) r = r_net;
-        else r = bias_ratio<BIAS>(C, phi, T.S);
+        else r = bias_ratio<BIAS, P>(C, phi, T.S);
         drift_dN = drift<POT, true>(T, r * T.S) * C.dN;
     }
     // The whole increment (D + B) dN + S sqrt(dN) xi is formed first and rounded onto phi once.
@@ -361,7 +367,7 @@ __device__ __forceinline__ uint32_t cap_groups(uint32_t k_max) { return (k_max >
 // them kept the compiler from overlapping one step's arithmetic with the next's normals.
 // Returns whether the run stopped, with its step count in k.
 // H, where not NULL, gains fma(r, dN, sqrt(dN) xi) of each step taken, in step order.
-template <int POT, int BIAS>
+template <int POT, int BIAS, int P = 0>
 __device__ __forceinline__ bool group4(const StepConsts &C, uint32_t j_cap, const F4 &z, float r_net, RunState &R, uint32_t &k,
                                        float *H = nullptr) {
     const float n[4] = {z.a, z.b, z.c, z.d};
@@ -373,7 +379,7 @@ __device__ __forceinline__ bool group4(const StepConsts &C, uint32_t j_cap, cons
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
         float dlw, sxi;
-        const float r = em_step<POT, BIAS>(C, phi, n[s], r_net, dlw, sxi);
+        const float r = em_step<POT, BIAS, P>(C, phi, n[s], r_net, dlw, sxi);
         if constexpr (BIAS != BIAS_NONE) lw += static_cast<double>(dlw);
         if (H) sum = sum + __builtin_fmaf(r, C.dN, sxi);
         p[s] = phi;

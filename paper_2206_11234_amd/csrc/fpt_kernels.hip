@@ -171,6 +171,23 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
     bool first = true;
     bool drained = n_first >= a.v_total;   // no id is left in the queue
     Team team;
+    // Power-law bias: the exponent where the wave's instances share one of 1 .. 4, whose group is
+    // compiled for it; a loop over an exponent per lane costs a step 24 instructions and its overlap
+    // with the next.
+    int p_wave = 0;
+    auto group = [&](const F4 &z) {
+        if constexpr (BIAS == BIAS_POWER) {
+            switch (p_wave) {
+            case 1: return group4<POT, BIAS, 1>(C, j_cap, z, 0.0f, R, k);
+            case 2: return group4<POT, BIAS, 2>(C, j_cap, z, 0.0f, R, k);
+            case 3: return group4<POT, BIAS, 3>(C, j_cap, z, 0.0f, R, k);
+            case 4: return group4<POT, BIAS, 4>(C, j_cap, z, 0.0f, R, k);
+            default: return group4<POT, BIAS>(C, j_cap, z, 0.0f, R, k);
+            }
+        } else {
+            return group4<POT, BIAS>(C, j_cap, z, 0.0f, R, k);
+        }
+    };
     // learned proposal: one copy of the network's A operands per workgroup
     __shared__ bf16x8 tile_lds[BIAS == BIAS_MLP ? MLP_N_FRAG * 64 : 1];
     if constexpr (BIAS == BIAS_MLP) {
@@ -260,6 +277,14 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
             }
         }
         if (!__any(active)) break;
+        if constexpr (BIAS == BIAS_POWER) {
+            if (need_mask) {
+                // inactive lanes' instances do not count
+                const int leader = __ffsll(static_cast<unsigned long long>(__ballot(active))) - 1;
+                const int p0 = __builtin_amdgcn_readlane(C.p, leader);
+                p_wave = __all(!active || C.p == p0) ? p0 : 0;
+            }
+        }
         // few runs and no more to come: the idle lanes draw normals ahead for them
         const uint64_t act = __ballot(run);
         const int n_act = __popcll(act);
@@ -275,11 +300,11 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
                 for (int g = 0; g < n_g; ++g) {
                     const F4 zg = zn;
                     if (g + 1 < n_g) zn = team_fetch(team, z, g + 1);
-                    if (run) run = !group4<POT, BIAS>(C, j_cap, zg, 0.0f, R, k);
+                    if (run) run = !group(zg);
                 }
             } else if (run) {
                 const F4 z = normals4(R.j, noise, a.key0, a.key1);
-                run = !group4<POT, BIAS>(C, j_cap, z, 0.0f, R, k);
+                run = !group(z);
             }
         } else {
             // the network is evaluated by all 64 lanes together, outside divergent code.  One
