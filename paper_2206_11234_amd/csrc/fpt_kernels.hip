@@ -173,7 +173,7 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
     Team team;
     // Power-law bias: the exponent where the wave's instances share one of 1 .. 4, whose group is
     // compiled for it; a loop over an exponent per lane costs a step 24 instructions and its overlap
-    // with the next.
+    // with the next (2e5 runs with p = 3: 5.2 against 4.6 ms).
     int p_wave = 0;
     auto group = [&](const F4 &z) {
         if constexpr (BIAS == BIAS_POWER) {

@@ -178,15 +178,17 @@ __device__ __forceinline__ void net_inputs(const MlpConsts &M, float phi, uint32
     x[2] = (M.target_N - M.in_mean[2]) * M.in_inv[2];
 }
 
+__device__ __forceinline__ float net_unit1(const float *__restrict__ th, int u, const float x[3]) {
+    float s = th[NET_B1 + u];
+    s = __builtin_fmaf(th[NET_W1 + 3 * u + 0], x[0], s);
+    s = __builtin_fmaf(th[NET_W1 + 3 * u + 1], x[1], s);
+    s = __builtin_fmaf(th[NET_W1 + 3 * u + 2], x[2], s);
+    return tanh_hw(s);
+}
+
 __device__ __forceinline__ void net_layer1(const float *__restrict__ th, const float x[3], float h1[64]) {
 #pragma unroll
-    for (int u = 0; u < 64; ++u) {
-        float s = th[NET_B1 + u];
-        s = __builtin_fmaf(th[NET_W1 + 3 * u + 0], x[0], s);
-        s = __builtin_fmaf(th[NET_W1 + 3 * u + 1], x[1], s);
-        s = __builtin_fmaf(th[NET_W1 + 3 * u + 2], x[2], s);
-        h1[u] = tanh_hw(s);
-    }
+    for (int u = 0; u < 64; ++u) h1[u] = net_unit1(th, u, x);
 }
 
 __device__ __forceinline__ float net_unit2(const float *__restrict__ th, int u, const float h1[64]) {
@@ -274,7 +276,7 @@ __global__ __launch_bounds__(1024) void fpt_train_softmax_kernel(TrainArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// backward: one wave per workgroup, 64 records per tile
+// backward: four waves per workgroup, 64 records per tile
 // ---------------------------------------------------------------------------
 constexpr int TS = 65;  // padded row stride of the [sample][unit] LDS tiles
 
@@ -284,39 +286,45 @@ typedef float f32x16v __attribute__((ext_vector_type(16)));
 // sums, like the rest of the training network).  Operand layout of that instruction, per lane l
 // and k-step: A[m = l & 31][k = l >> 5], B[k = l >> 5][n = l & 31]; accumulator element q of lane l
 // is D[m = (q & 3) + 8 (q >> 2) + 4 (l >> 5)][n = l & 31] of its 32x32 block.
+//
+// Bound by the phases of a tile that wait for one another beside the matrix work (384 instructions of
+// 72 cycles on a SIMD, measured: 27 600 cycles a tile).  The four waves of a workgroup, one per SIMD,
+// take a 32x32 block each of the contractions, 16 of the 64 units each of layer 1, and a different one
+// of the per-record and per-unit sums; four workgroups share a CU, so that on each SIMD one tile's
+// matrix work runs beside the others' vector work and waits.  With one wave per tile and SIMD, every
+// phase of a tile after the other, a tile took 61 000 cycles; now 50 000 (7.4e5 records in 286 and
+// 243 us, 1.4e6 in 487 and 422 us).
+// Every sum keeps its order, so that the gradient is the same bit for bit.
 __device__ __forceinline__ int acc_row(int q, int lane) { return (q & 3) + 8 * (q >> 2) + 4 * (lane >> 5); }
 
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1))) void fpt_train_bwd_kernel(TrainArgs a,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void fpt_train_bwd_kernel(TrainArgs a,
                                                                                           const float *__restrict__ th0) {
-    // two [sample][unit] tiles: HA holds h1, then delta1; HB holds h2, then delta2 (34 KB with the
-    // inputs and coefficients, so four single-wave workgroups share a CU, one per SIMD)
+    // two [sample][unit] tiles: HA holds h1, then delta1; HB holds h2, then delta2 (35 KB with the
+    // inputs and coefficients, so four workgroups share a CU)
     __shared__ float HA[64 * TS];
     __shared__ float HB[64 * TS];
     __shared__ float XS[64 * 4];
     __shared__ float GS[64];
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int mb = wave >> 1, nb = wave & 1;        // this wave's block of the contractions
+    const int u0 = 16 * wave;                       // and its units of layer 1 and delta2
     const int col = lane & 31, kh = lane >> 5;
     const double dNd = static_cast<double>(a.dN);
     // this lane's B fragments of W2 for the whole kernel: WT for h1 W2^T (k = input v, n = unit u),
-    // WN for delta2 W2 (k = unit u, n = input v); and its units' b2
-    float WT[2][32], WN[2][32], b2v[2];
+    // WN for delta2 W2 (k = unit u, n = input v); and its unit's b2
+    float WT[32], WN[32];
 #pragma unroll
-    for (int nb = 0; nb < 2; ++nb) {
-#pragma unroll
-        for (int ks = 0; ks < 32; ++ks) {
-            WT[nb][ks] = th0[NET_W2 + 64 * (32 * nb + col) + 2 * ks + kh];
-            WN[nb][ks] = th0[NET_W2 + 64 * (2 * ks + kh) + 32 * nb + col];
-        }
-        b2v[nb] = th0[NET_B2 + 32 * nb + col];
+    for (int ks = 0; ks < 32; ++ks) {
+        WT[ks] = th0[NET_W2 + 64 * (32 * nb + col) + 2 * ks + kh];
+        WN[ks] = th0[NET_W2 + 64 * (2 * ks + kh) + 32 * nb + col];
     }
-    f32x16v acc[2][2];
+    const float b2v = th0[NET_B2 + 32 * nb + col];
+    f32x16v acc;
 #pragma unroll
-    for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-        for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-            for (int q = 0; q < 16; ++q) acc[mb][nb][q] = 0.0f;
-    float g_w3 = 0.0f, g_b2 = 0.0f, g_b1 = 0.0f, g_w1[3] = {0.0f, 0.0f, 0.0f}, g_b3 = 0.0f;
+    for (int q = 0; q < 16; ++q) acc[q] = 0.0f;
+    // per-unit sums: w3 and b3 (wave 0), b2 (wave 1), W1 and b1 (wave 2)
+    float g0 = 0.0f, g1 = 0.0f, g2 = 0.0f, g3 = 0.0f;
     const uint64_t n_tiles = (a.n_rec + 63) / 64;
     for (uint64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
         const float *th = th0 + opaque_zero();
@@ -325,44 +333,35 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1))) void
         TrainRec R{};
         if (valid) R = a.rec[e];
         else R.phi = a.mc.in_mean[0];
-        // forward: h1 into HA (this lane's record), h2 = tanh(W2 h1 + b2) into HB on the matrix
-        // cores (M = record, N = unit, K = input), then r from this lane's row of HB
-        float g = 0.0f;
+        // forward: h1 into HA (this lane's record, this wave's units), h2 = tanh(W2 h1 + b2) into HB
+        // on the matrix cores (M = record, N = unit, K = input), then r from a record's row of HB
         {
-            float x[3], h1[64];
+            float x[3];
             net_inputs(a.mc, R.phi, R.k, a.dN, x);
-            net_layer1(th, x, h1);
 #pragma unroll
-            for (int u = 0; u < 64; ++u) HA[lane * TS + u] = h1[u];
-            XS[lane * 4 + 0] = x[0];
-            XS[lane * 4 + 1] = x[1];
-            XS[lane * 4 + 2] = x[2];
-            XS[lane * 4 + 3] = 1.0f;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb) {
-            f32x16v z[2];
-#pragma unroll
-            for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-                for (int q = 0; q < 16; ++q) z[nb][q] = 0.0f;
-#pragma unroll
-            for (int ks = 0; ks < 32; ++ks) {
-                const float av = HA[(32 * mb + col) * TS + 2 * ks + kh];
-                z[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, WT[0][ks], z[0], 0, 0, 0);
-                z[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, WT[1][ks], z[1], 0, 0, 0);
+            for (int u = 0; u < 16; ++u) HA[lane * TS + u0 + u] = net_unit1(th, u0 + u, x);
+            if (wave == 0) {
+                XS[lane * 4 + 0] = x[0];
+                XS[lane * 4 + 1] = x[1];
+                XS[lane * 4 + 2] = x[2];
+                XS[lane * 4 + 3] = 1.0f;
             }
-#pragma unroll
-            for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-                for (int q = 0; q < 16; ++q)
-                    HB[(32 * mb + acc_row(q, lane)) * TS + 32 * nb + col] = tanh_hw(z[nb][q] + b2v[nb]);
         }
         __syncthreads();
         {
-            float o = 0.0f;
-#pragma unroll 8
+            f32x16v z;
+#pragma unroll
+            for (int q = 0; q < 16; ++q) z[q] = 0.0f;
+#pragma unroll
+            for (int ks = 0; ks < 32; ++ks)
+                z = __builtin_amdgcn_mfma_f32_32x32x2f32(HA[(32 * mb + col) * TS + 2 * ks + kh], WT[ks], z, 0, 0, 0);
+#pragma unroll
+            for (int q = 0; q < 16; ++q) HB[(32 * mb + acc_row(q, lane)) * TS + 32 * nb + col] = tanh_hw(z[q] + b2v);
+        }
+        __syncthreads();
+        if (wave == 0) {
+            float o = 0.0f, g = 0.0f;
+#pragma unroll 16
             for (int u = 0; u < 64; ++u) o = __builtin_fmaf(th[NET_W3 + u], HB[lane * TS + u], o);
             if (valid) {
                 const double r = static_cast<double>(a.mc.out_scale * (o + th[NET_B3]));
@@ -372,79 +371,63 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1))) void
                                        static_cast<double>(a.mc.out_scale) * static_cast<double>(a.rec_weight));
             }
             GS[lane] = g;
-        }
-        __syncthreads();
-        // lane = unit: w3 and b3 from h2
-        {
+            // lane = unit: w3 and b3 from h2 (GS is this wave's own: no barrier)
             float sw3 = 0.0f, sb3 = 0.0f;
-#pragma unroll 4
+#pragma unroll 16
             for (int s = 0; s < 64; ++s) {
                 const float gs = GS[s];
                 sw3 = __builtin_fmaf(gs, HB[s * TS + lane], sw3);
                 sb3 += gs;
             }
-            g_w3 += sw3;
-            g_b3 += sb3;
+            g0 += sw3;
+            g1 += sb3;
         }
         __syncthreads();
-        // delta2 = g w3 (1 - h2^2), in place over this lane's h2
-#pragma unroll 4
-        for (int u = 0; u < 64; ++u) {
-            const float h = HB[lane * TS + u];
-            HB[lane * TS + u] = (g * th[NET_W3 + u]) * __builtin_fmaf(-h, h, 1.0f);
+        // delta2 = g w3 (1 - h2^2), in place over h2 (this lane's record, this wave's units)
+        {
+            const float g = GS[lane];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) {
+                const float h = HB[lane * TS + u0 + u];
+                HB[lane * TS + u0 + u] = (g * th[NET_W3 + u0 + u]) * __builtin_fmaf(-h, h, 1.0f);
+            }
         }
         __syncthreads();
         // lane = unit: b2 from delta2
-        {
+        if (wave == 1) {
             float sb2 = 0.0f;
-#pragma unroll 4
+#pragma unroll 16
             for (int s = 0; s < 64; ++s) sb2 += HB[s * TS + lane];
-            g_b2 += sb2;
+            g0 += sb2;
         }
-        // dW2[u][v] += sum_s delta2[s][u] h1[s][v]: M = u, N = v, K = the tile's samples
+        // dW2[u][v] += sum_s delta2[s][u] h1[s][v]: M = u, N = v, K = the tile's samples; and
+        // delta1 = (delta2 W2) (1 - h1^2) (M = record, N = input, K = unit), whose elements overwrite
+        // the h1 that they are scaled by (one lane owns each) once every wave has read its h1 for dW2
         {
-            const int row = lane & 31, kh = lane >> 5;
-#pragma unroll 4
+#pragma unroll 8
             for (int ks = 0; ks < 32; ++ks) {
                 const int s = 2 * ks + kh;
-                const float a0 = HB[s * TS + row], a1 = HB[s * TS + 32 + row];
-                const float b0 = HA[s * TS + row], b1 = HA[s * TS + 32 + row];
-                acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b0, acc[0][0], 0, 0, 0);
-                acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b1, acc[0][1], 0, 0, 0);
-                acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b0, acc[1][0], 0, 0, 0);
-                acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b1, acc[1][1], 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(HB[s * TS + 32 * mb + col], HA[s * TS + 32 * nb + col], acc, 0, 0, 0);
             }
-        }
-        __syncthreads();
-        // delta1 = (delta2 W2) (1 - h1^2) on the matrix cores (M = record, N = input, K = unit); each
-        // accumulator element overwrites the h1 it was scaled by (one lane owns each element)
+            f32x16v z;
 #pragma unroll
-        for (int mb = 0; mb < 2; ++mb) {
-            f32x16v z[2];
+            for (int q = 0; q < 16; ++q) z[q] = 0.0f;
 #pragma unroll
-            for (int nb = 0; nb < 2; ++nb)
+            for (int ks = 0; ks < 32; ++ks)
+                z = __builtin_amdgcn_mfma_f32_32x32x2f32(HB[(32 * mb + col) * TS + 2 * ks + kh], WN[ks], z, 0, 0, 0);
+            __syncthreads();
 #pragma unroll
-                for (int q = 0; q < 16; ++q) z[nb][q] = 0.0f;
-#pragma unroll
-            for (int ks = 0; ks < 32; ++ks) {
-                const float av = HB[(32 * mb + col) * TS + 2 * ks + kh];
-                z[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, WN[0][ks], z[0], 0, 0, 0);
-                z[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, WN[1][ks], z[1], 0, 0, 0);
+            for (int q = 0; q < 16; ++q) {
+                const int idx = (32 * mb + acc_row(q, lane)) * TS + 32 * nb + col;
+                const float h = HA[idx];
+                HA[idx] = z[q] * __builtin_fmaf(-h, h, 1.0f);
             }
-#pragma unroll
-            for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-                for (int q = 0; q < 16; ++q) {
-                    const int idx = (32 * mb + acc_row(q, lane)) * TS + 32 * nb + col;
-                    const float h = HA[idx];
-                    HA[idx] = z[nb][q] * __builtin_fmaf(-h, h, 1.0f);
-                }
         }
         __syncthreads();
         // lane = unit: W1, b1 from delta1
-        {
+        if (wave == 2) {
             float sb1 = 0.0f, s0 = 0.0f, s1 = 0.0f, s2 = 0.0f;
-#pragma unroll 4
+#pragma unroll 8
             for (int s = 0; s < 64; ++s) {
                 const float d = HA[s * TS + lane];
                 sb1 += d;
@@ -452,32 +435,28 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1))) void
                 s1 = __builtin_fmaf(d, XS[s * 4 + 1], s1);
                 s2 = __builtin_fmaf(d, XS[s * 4 + 2], s2);
             }
-            g_b1 += sb1;
-            g_w1[0] += s0;
-            g_w1[1] += s1;
-            g_w1[2] += s2;
+            g0 += sb1;
+            g1 += s0;
+            g2 += s1;
+            g3 += s2;
         }
         __syncthreads();
     }
     // partial gradient of this workgroup
     float *P = a.part + static_cast<size_t>(blockIdx.x) * NET_N_PARAMS;
 #pragma unroll
-    for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-        for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-            for (int q = 0; q < 16; ++q) {
-                const int u = 32 * mb + (q & 3) + 8 * (q >> 2) + 4 * (lane >> 5);
-                const int v = 32 * nb + (lane & 31);
-                P[NET_W2 + 64 * u + v] = acc[mb][nb][q];
-            }
-    P[NET_W1 + 3 * lane + 0] = g_w1[0];
-    P[NET_W1 + 3 * lane + 1] = g_w1[1];
-    P[NET_W1 + 3 * lane + 2] = g_w1[2];
-    P[NET_B1 + lane] = g_b1;
-    P[NET_B2 + lane] = g_b2;
-    P[NET_W3 + lane] = g_w3;
-    if (lane == 0) P[NET_B3] = g_b3;
+    for (int q = 0; q < 16; ++q) P[NET_W2 + 64 * (32 * mb + acc_row(q, lane)) + 32 * nb + col] = acc[q];
+    if (wave == 0) {
+        P[NET_W3 + lane] = g0;
+        if (lane == 0) P[NET_B3] = g1;
+    } else if (wave == 1) {
+        P[NET_B2 + lane] = g0;
+    } else if (wave == 2) {
+        P[NET_B1 + lane] = g0;
+        P[NET_W1 + 3 * lane + 0] = g1;
+        P[NET_W1 + 3 * lane + 1] = g2;
+        P[NET_W1 + 3 * lane + 2] = g3;
+    }
 }
 
 // Partial gradients summed in binary64 in a fixed order: RED_COLS parameters by RED_SPLIT ranges of
@@ -572,7 +551,7 @@ hipError_t launch_train_loss(const TrainArgs &a, hipStream_t s) {
 
 hipError_t launch_train_grad(const TrainArgs &a, hipStream_t s) {
     if (a.n_part <= 0) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(fpt_train_bwd_kernel, dim3(a.n_part), dim3(64), 0, s, a, a.theta);
+    hipLaunchKernelGGL(fpt_train_bwd_kernel, dim3(a.n_part), dim3(256), 0, s, a, a.theta);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(fpt_train_reduce_kernel, dim3((NET_N_PARAMS + RED_COLS - 1) / RED_COLS), dim3(RED_COLS * RED_SPLIT), 0, s,
