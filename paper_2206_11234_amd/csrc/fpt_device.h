@@ -360,16 +360,26 @@ struct RunState {
 // Groups a run can take whole before the step cap: it stops in group j when j + 1 >= this.
 __device__ __forceinline__ uint32_t cap_groups(uint32_t k_max) { return (k_max >> 2) + ((k_max & 3u) != 0u ? 1u : 0u); }
 
-// The four steps of group R.j, all taken without a test between them: the group's smallest and
-// largest field and the step cap tell at its end whether the run has stopped inside it, and then
-// the first step that stops it is picked from the saved fields and weights (what the steps past it
-// computed is dropped).  Tests after every step cost 7 of 28 instructions, and the branches around
-// them kept the compiler from overlapping one step's arithmetic with the next's normals.
-// Returns whether the run stopped, with its step count in k.
-// H, where not NULL, gains fma(r, dN, sqrt(dN) xi) of each step taken, in step order.
+// Where a run stopped, kept apart from the state of its lane, which steps on unread (the step kernels
+// keep it in LDS: in registers it took four copies a group).
+struct Stopped {
+    float phi;
+    uint32_t k;
+    double lw;
+};
+
+// The four steps of every lane's group R.j, all taken without a test between them: the group's
+// smallest and largest field and the step cap tell at its end whether a run has stopped inside it,
+// and then the first step that stops it is picked from the saved fields and weights into F (what the
+// steps past it computed is dropped).  Tests after every step cost 7 of 28 instructions, and the
+// branches around them kept the compiler from overlapping one step's arithmetic with the next's
+// normals.  `running` has the bits of the lanes whose runs go on; the other lanes compute along, so
+// that the whole group is one stretch of code.  Returns the lanes whose runs stopped here and takes
+// them out of `running`.  H, where not NULL, gains fma(r, dN, sqrt(dN) xi) of each step taken, in
+// step order.
 template <int POT, int BIAS, int P = 0>
-__device__ __forceinline__ bool group4(const StepConsts &C, uint32_t j_cap, const F4 &z, float r_net, RunState &R, uint32_t &k,
-                                       float *H = nullptr) {
+__device__ __forceinline__ uint64_t group4(const StepConsts &C, uint32_t j_cap, const F4 &z, float r_net, RunState &R,
+                                           uint64_t &running, Stopped *F, float *H = nullptr) {
     const float n[4] = {z.a, z.b, z.c, z.d};
     float p[4], h[4];
     double w[4];
@@ -396,18 +406,21 @@ __device__ __forceinline__ bool group4(const StepConsts &C, uint32_t j_cap, cons
     R.lw = lw;
     R.j = j + 1;
     // (no short circuit: its branches would split the group's arithmetic)
-    const bool stop = (lo <= C.phi_end) | (hi > C.phi_esc) | (j + 1 >= j_cap);
-    if (__builtin_expect(stop, 0)) {
-        const uint32_t left = C.k_max - 4 * j;     // steps to the cap, >= 1
-        int s = 3;
-        for (int q = 2; q >= 0; --q)
-            if (p[q] <= C.phi_end || p[q] > C.phi_esc || static_cast<uint32_t>(q + 1) >= left) s = q;
-        R.phi = s == 0 ? p[0] : s == 1 ? p[1] : s == 2 ? p[2] : p[3];
-        R.lw = s == 0 ? w[0] : s == 1 ? w[1] : s == 2 ? w[2] : w[3];
-        if (H) *H = s == 0 ? h[0] : s == 1 ? h[1] : s == 2 ? h[2] : h[3];
-        k = 4 * j + 1 + static_cast<uint32_t>(s);
+    const uint64_t m = __builtin_amdgcn_ballot_w64((lo <= C.phi_end) | (hi > C.phi_esc) | (j + 1 >= j_cap)) & running;
+    if (__builtin_expect(m != 0, 0)) {
+        running &= ~m;
+        if ((m >> __lane_id()) & 1u) {
+            const uint32_t left = C.k_max - 4 * j;     // steps to the cap, >= 1
+            int s = 3;
+            for (int q = 2; q >= 0; --q)
+                if (p[q] <= C.phi_end || p[q] > C.phi_esc || static_cast<uint32_t>(q + 1) >= left) s = q;
+            F->phi = s == 0 ? p[0] : s == 1 ? p[1] : s == 2 ? p[2] : p[3];
+            F->lw = s == 0 ? w[0] : s == 1 ? w[1] : s == 2 ? w[2] : w[3];
+            F->k = 4 * j + 1 + static_cast<uint32_t>(s);
+            if (H) *H = s == 0 ? h[0] : s == 1 ? h[1] : s == 2 ? h[2] : h[3];
+        }
     }
-    return stop;
+    return m;
 }
 
 }  // namespace fpt

@@ -99,37 +99,33 @@ __device__ __forceinline__ void init_table(unsigned char *base, const TableLayou
     }
 }
 
-// Wave-wide log-sum-exp / sum over lanes (all 64 lanes take part).
+// Wave-wide log-sum-exp over lanes (all 64 take part): one exponential and one logarithm.
 __device__ __forceinline__ double wave_lse(double x) {
+    double m = x;
 #pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) x = lse2(x, __shfl_xor(x, m, 64));
-    return x;
-}
-__device__ __forceinline__ double wave_sum(double x) {
+    for (int h = 32; h >= 1; h >>= 1) m = fmax(m, __shfl_xor(m, h, 64));
+    if (__builtin_isinf(m) && m < 0) return __any(x != x) ? NAN : m;
+    double s = (__builtin_isinf(x) && x < 0) ? 0.0 : exp(x - m);
 #pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) x += __shfl_xor(x, m, 64);
-    return x;
+    for (int h = 32; h >= 1; h >>= 1) s += __shfl_xor(s, h, 64);
+    return m + log(s);
 }
 
+// A lane's log-sums of w k and w k^2 over the runs it retired of one instance.
 struct LaneAcc {
     int inst;
-    double wk, wk2, k2;
-    double steps;   // exact: integer-valued, < 2^53 per lane
+    double wk, wk2;
 };
 
 __device__ __forceinline__ void acc_reset(LaneAcc &a, int inst) {
     a.inst = inst;
     a.wk = a.wk2 = -INFINITY;
-    a.k2 = 0.0;
-    a.steps = 0.0;
 }
 
 __device__ __forceinline__ void acc_commit_direct(const Tab &T, const LaneAcc &a) {
     double *s = T.scal + static_cast<size_t>(a.inst) * 16;
     atomic_lse(s + 2, a.wk);
     atomic_lse(s + 3, a.wk2);
-    atomic_add_f64(s + 4, a.k2);
-    atomic_add_f64(s + 5, a.steps);
 }
 
 extern __shared__ __align__(16) unsigned char fpt_lds[];
@@ -156,11 +152,11 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
     int cur_inst = -1;
     RunState R{0.0f, 0u, 0.0};
     PhiloxRun noise{};
-    uint32_t k = 0;             // step count of a run that has stopped
+    Stopped *const F = reinterpret_cast<Stopped *>(fpt_lds + (LDS ? a.lay.slice_bytes : 0u)) + threadIdx.x;
     uint64_t t = 0;
-    bool run = false;           // the lane's run goes on
-    bool active = false;        // the lane has a run, stopped or not
-    bool need = lane < a.lane_cap;
+    // the wave's lanes, as masks: those whose runs go on, those that have a run (stopped or not) and
+    // those that want one
+    uint64_t running = 0, active = 0, need = ~0ull >> (64 - a.lane_cap);
     LaneAcc acc;
     acc_reset(acc, -1);
     // this wave's reserved queue range
@@ -178,14 +174,14 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
     auto group = [&](const F4 &z) {
         if constexpr (BIAS == BIAS_POWER) {
             switch (p_wave) {
-            case 1: return group4<POT, BIAS, 1>(C, j_cap, z, 0.0f, R, k);
-            case 2: return group4<POT, BIAS, 2>(C, j_cap, z, 0.0f, R, k);
-            case 3: return group4<POT, BIAS, 3>(C, j_cap, z, 0.0f, R, k);
-            case 4: return group4<POT, BIAS, 4>(C, j_cap, z, 0.0f, R, k);
-            default: return group4<POT, BIAS>(C, j_cap, z, 0.0f, R, k);
+            case 1: (void)group4<POT, BIAS, 1>(C, j_cap, z, 0.0f, R, running, F); break;
+            case 2: (void)group4<POT, BIAS, 2>(C, j_cap, z, 0.0f, R, running, F); break;
+            case 3: (void)group4<POT, BIAS, 3>(C, j_cap, z, 0.0f, R, running, F); break;
+            case 4: (void)group4<POT, BIAS, 4>(C, j_cap, z, 0.0f, R, running, F); break;
+            default: (void)group4<POT, BIAS>(C, j_cap, z, 0.0f, R, running, F); break;
             }
         } else {
-            return group4<POT, BIAS>(C, j_cap, z, 0.0f, R, k);
+            (void)group4<POT, BIAS>(C, j_cap, z, 0.0f, R, running, F);
         }
     };
     // learned proposal: one copy of the network's A operands per workgroup
@@ -215,8 +211,9 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
 
     while (true) {
         // ---- refill: hand new trajectory ids to lanes that need one
-        const uint64_t need_mask = __ballot(need);
-        if (need_mask) {
+        const bool refill = need != 0;
+        if (refill) {
+            const bool mine = (need >> lane) & 1u;
             uint64_t v = ~0ull;
             if (first) {
                 first = false;
@@ -227,8 +224,8 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
                 const uint64_t wave = static_cast<uint64_t>(w) * gridDim.x + blockIdx.x;
                 v = a.spread ? lane * n_waves + wave : wave * a.lane_cap + lane;
             } else if (!drained) {
-                const uint32_t n_need = __popcll(need_mask);
-                const uint32_t rank = __popcll(need_mask & lt_mask);
+                const uint32_t n_need = __popcll(need);
+                const uint32_t rank = __popcll(need & lt_mask);
                 const uint64_t avail = res_hi - res_lo;
                 if (avail >= n_need) {
                     v = res_lo + rank;
@@ -236,7 +233,7 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
                 } else {
                     const uint64_t short_by = n_need - avail;
                     const uint64_t amt = short_by * a.chunk;
-                    const int leader = __ffsll(static_cast<unsigned long long>(need_mask)) - 1;
+                    const int leader = __ffsll(static_cast<unsigned long long>(need)) - 1;
                     unsigned long long b = 0;
                     if (static_cast<int>(lane) == leader) b = atomicAdd(a.queue, static_cast<unsigned long long>(amt));
                     b = n_first + __shfl(b, leader, 64);
@@ -244,11 +241,15 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
                     res_lo = b + short_by;
                     res_hi = b + amt;
                 }
-                drained = __any(need && v >= a.v_total);   // a wave's ids ascend: no later one is in range
+                drained = __any(mine && v >= a.v_total);   // a wave's ids ascend: no later one is in range
             }
-            if (need) {
-                need = false;
-                if (v < a.v_total) {
+            const bool got = mine && v < a.v_total;
+            const uint64_t given = __ballot(got);
+            need = 0;
+            active |= given;
+            running |= given;
+            {
+                if (got) {
                     int ii = single_inst;
                     if constexpr (SINGLE) {
                         t = v;                 // the only instance with runs starts the queue
@@ -269,42 +270,35 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
                     }
                     noise = philox_run(t, a.inst[ii].stream, a.key0, a.key1);
                     R = RunState{C.phi_in, 0u, 0.0};
-                    run = true;
-                    active = true;
-                } else {
-                    active = false;
                 }
             }
         }
-        if (!__any(active)) break;
+        if (!active) break;
         if constexpr (BIAS == BIAS_POWER) {
-            if (need_mask) {
-                // inactive lanes' instances do not count
-                const int leader = __ffsll(static_cast<unsigned long long>(__ballot(active))) - 1;
-                const int p0 = __builtin_amdgcn_readlane(C.p, leader);
-                p_wave = __all(!active || C.p == p0) ? p0 : 0;
+            if (refill) {
+                // lanes without a run do not count
+                const int p0 = __builtin_amdgcn_readlane(C.p, __ffsll(static_cast<unsigned long long>(active)) - 1);
+                p_wave = (__ballot(C.p != p0) & active) == 0 ? p0 : 0;
             }
         }
         // few runs and no more to come: the idle lanes draw normals ahead for them
-        const uint64_t act = __ballot(run);
-        const int n_act = __popcll(act);
+        const int n_act = __popcll(running);
         const bool teamed = drained && n_act <= 32;
 
         // ---- a pass: groups of four Euler-Maruyama steps, each from one Philox call
         if constexpr (BIAS != BIAS_MLP) {
             if (teamed) {
-                if (team_halves(team.shift, n_act, 8)) team_form(team, act, lt_mask, lane, noise, 8);
+                if (team_halves(team.shift, n_act, 8)) team_form(team, running, lt_mask, lane, noise, 8);
                 const F4 z = team_draw(team, lane, R.j, a.key0, a.key1);
                 F4 zn = team_fetch(team, z, 0);
                 const int n_g = team.groups();
                 for (int g = 0; g < n_g; ++g) {
                     const F4 zg = zn;
                     if (g + 1 < n_g) zn = team_fetch(team, z, g + 1);
-                    if (run) run = !group(zg);
+                    group(zg);
                 }
-            } else if (run) {
-                const F4 z = normals4(R.j, noise, a.key0, a.key1);
-                run = !group(z);
+            } else {
+                group(normals4(R.j, noise, a.key0, a.key1));
             }
         } else {
             // the network is evaluated by all 64 lanes together, outside divergent code.  One
@@ -315,7 +309,7 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
             // a team's runs fit one block of 32 columns, slot c in lane c: half the network's work,
             // and with E >= 8 the normals of E / 4 groups shared out besides
             const int most = E >= 8 ? E / 4 : 2;
-            if (teamed && team_halves(team.shift, n_act, most)) team_form(team, act, lt_mask, lane, noise, most);
+            if (teamed && team_halves(team.shift, n_act, most)) team_form(team, running, lt_mask, lane, noise, most);
             auto network = [&](float phi_, float N_) {
                 const MlpIn x = mlp_input(mc, phi_, N_);
                 if (!teamed) return mc.out_scale * mlp_forward_lds(tile_lds, x);
@@ -352,8 +346,7 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
                 const float r_mlp = network(R.phi, static_cast<float>(4u * R.j) * C.dN);
                 __builtin_amdgcn_s_setprio(0);
 #pragma unroll
-                for (int q = 0; q < NQ; ++q)
-                    if (run) run = !group4<POT, BIAS>(C, j_cap, zz[q], r_mlp, R, k);
+                for (int q = 0; q < NQ; ++q) (void)group4<POT, BIAS>(C, j_cap, zz[q], r_mlp, R, running, F);
             };
             if (E == 16) {
                 pass(std::integral_constant<int, 4>{});
@@ -369,13 +362,12 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
                 for (int s = 0; s < 4; ++s) {
                     const uint32_t k0 = 4u * R.j + s;
                     const float r_mlp = network(R.phi, static_cast<float>(k0) * C.dN);
-                    if (run) {
-                        float dlw, sxi;
-                        (void)em_step<POT, BIAS>(C, R.phi, ns[s], r_mlp, dlw, sxi);
-                        R.lw += static_cast<double>(dlw);
-                        k = k0 + 1;
-                        run = !stops(C, R.phi, k);
-                    }
+                    float dlw, sxi;
+                    (void)em_step<POT, BIAS>(C, R.phi, ns[s], r_mlp, dlw, sxi);
+                    R.lw += static_cast<double>(dlw);
+                    const uint64_t m = __ballot(stops(C, R.phi, k0 + 1)) & running;
+                    if ((m >> lane) & 1u) *F = Stopped{R.phi, k0 + 1, R.lw};
+                    running &= ~m;
                 }
                 R.j += 1;
             }
@@ -384,14 +376,14 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
         // ---- retire finished runs into the workgroup table: at once while their lanes can take new
         // ones, else all together when the wave's last run has stopped (a retirement is a chain of
         // dependent loads and atomics, as long as some tens of passes)
-        const bool all_stopped = !__any(run);
-        const bool fin = active && !run && (!drained || all_stopped);
-        if (fin) {
+        const uint64_t fin = (!drained || running == 0) ? active & ~running : 0ull;
+        if ((fin >> lane) & 1u) {
             const InstDev &I = a.inst[cur_inst];
             const uint32_t n_bins = I.n_bins, row_base = I.row_base, thr_base = I.thr_base, k_center = I.k_center;
             const uint64_t t0 = I.t_first;
-            const float phi = R.phi;
-            const double lw = R.lw;
+            const float phi = F->phi;
+            const double lw = F->lw;
+            const uint32_t k = F->k;
             const int st = final_status(C, phi, k);
             uint32_t rl;
             if (st == ST_ENDED) {
@@ -434,13 +426,14 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
                 atomic_add_f64(sc + 10, y * y);
                 atomic_add_f64(sc + 11, lw * y);
             }
-            // instance-wide sums in lane registers
+            // instance-wide sums: of k and k^2 in the table (exact: integers below 2^53 and their
+            // squares' rounded sum), the log-sums in lane registers
             const double kd = static_cast<double>(k);
+            atomic_add_f64(T.scal + static_cast<size_t>(cur_inst) * 16 + 4, kd * kd);
+            atomic_add_f64(T.scal + static_cast<size_t>(cur_inst) * 16 + 5, kd);
             const double lk = log(kd);
             acc.wk = lse2(acc.wk, lw + lk);
             acc.wk2 = lse2(acc.wk2, lw + 2.0 * lk);
-            acc.k2 += kd * kd;
-            acc.steps += kd;
             if (a.dump.n != 0 && ((t - t0) % a.dump.stride) == 0) {
                 const uint64_t idx = (t - t0) / a.dump.stride;
                 if (idx < a.dump.n) {
@@ -451,9 +444,9 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
                     a.dump.status[pos] = st;
                 }
             }
-            active = false;
-            need = true;
         }
+        active &= ~fin;
+        need = fin;
     }
 
     // ---- flush lane accumulators: one wave reduction per distinct instance
@@ -466,12 +459,11 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
         const bool mine = pending && acc.inst == inst_l;
         const double wk = wave_lse(mine ? acc.wk : -INFINITY);
         const double wk2 = wave_lse(mine ? acc.wk2 : -INFINITY);
-        const double k2 = wave_sum(mine ? acc.k2 : 0.0);
-        const double steps = wave_sum(mine ? acc.steps : 0.0);
         if (static_cast<int>(lane) == leader) {
             LaneAcc r;
             r.inst = inst_l;
-            r.wk = wk; r.wk2 = wk2; r.k2 = k2; r.steps = steps;
+            r.wk = wk;
+            r.wk2 = wk2;
             acc_commit_direct(T, r);
         }
         if (mine) pending = false;
@@ -901,12 +893,12 @@ static hipError_t launch_step_t(int n_wg, int block, size_t lds_bytes, const Ste
     } else {
         kern = fpt_step_kernel<POT, BIAS, LDS>;
     }
-    if (LDS && lds_bytes > 0) {
+    if (lds_bytes > 0) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds_bytes));
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(kern, dim3(n_wg), dim3(block), LDS ? lds_bytes : 0, stream, args);
+    hipLaunchKernelGGL(kern, dim3(n_wg), dim3(block), lds_bytes, stream, args);
     return hipGetLastError();
 }
 
@@ -934,7 +926,7 @@ static hipError_t launch_step_p(int pot, int bias, int n_wg, int block, size_t l
 hipError_t launch_step(int pot, int bias, bool tables_in_lds, int n_wg, int block, size_t lds_bytes,
                        const StepArgs &args, hipStream_t stream) {
     if (tables_in_lds) return launch_step_p<true>(pot, bias, n_wg, block, lds_bytes, args, stream);
-    return launch_step_p<false>(pot, bias, n_wg, block, 0, args, stream);
+    return launch_step_p<false>(pot, bias, n_wg, block, lds_bytes, args, stream);
 }
 
 hipError_t launch_init_queue(unsigned long long *queue, hipStream_t stream) {

@@ -68,8 +68,8 @@ __global__ __launch_bounds__(256) void fpt_record_kernel(RecordArgs a) {
     const uint32_t group = static_cast<uint32_t>(a.group), stride = static_cast<uint32_t>(a.stride);
     const PhiloxRun noise = philox_run(t, a.inst.stream, a.key0, a.key1);
     RunState R{C.phi_in, 0u, 0.0};
-    uint32_t k = 0;             // step count of a run that has stopped
-    bool run = have;
+    Stopped F{0.0f, 0u, 0.0};
+    uint64_t running = __ballot(have);
     float H = 0.0f, phi_e = R.phi;
     uint32_t k_e = 0;           // first step of the record's group
     uint32_t grp = 0;           // its index
@@ -101,8 +101,7 @@ __global__ __launch_bounds__(256) void fpt_record_kernel(RecordArgs a) {
     const bool share = teamed && (BIAS != BIAS_MLP || n_q > 1);
     Team team;
     if (teamed) {
-        const uint64_t paths = __ballot(have);
-        team_form(team, paths, (lane == 0) ? 0ull : (~0ull >> (64 - lane)), lane, noise, most);
+        team_form(team, running, (lane == 0) ? 0ull : (~0ull >> (64 - lane)), lane, noise, most);
     }
     auto network = [&](float phi_, float N_) {
         const MlpIn x = mlp_input(mc, phi_, N_);
@@ -113,7 +112,7 @@ __global__ __launch_bounds__(256) void fpt_record_kernel(RecordArgs a) {
     F4 batch{};
     float r_mlp = 0.0f;
     const int batch_mask = share ? team.groups() - 1 : 0;
-    for (int q = 0; __any(run); ++q) {
+    for (int q = 0; running; ++q) {
         // q-th group of four steps; the lanes still running are all in their group q
         if constexpr (BIAS == BIAS_MLP) {
             if ((q & (n_q - 1)) == 0) r_mlp = network(R.phi, static_cast<float>(4u * R.j) * C.dN);
@@ -134,27 +133,32 @@ __global__ __launch_bounds__(256) void fpt_record_kernel(RecordArgs a) {
                 if constexpr (BIAS == BIAS_MLP) {
                     if (s > 0 && E == 1) r_mlp = network(R.phi, static_cast<float>(ks) * C.dN);
                 }
-                if (run) {
-                    float dlw, sxi;
-                    const float r = em_step<POT, BIAS>(C, R.phi, ns[s], r_mlp, dlw, sxi);
-                    R.lw += static_cast<double>(dlw);
-                    H = H + __builtin_fmaf(r, C.dN, sxi);
-                    k = ks + 1;
-                    run = !stops(C, R.phi, k);
-                    if ((k & (group - 1)) == 0 || !run) record(k);
-                }
+                float dlw, sxi;
+                const float r = em_step<POT, BIAS>(C, R.phi, ns[s], r_mlp, dlw, sxi);
+                R.lw += static_cast<double>(dlw);
+                H = H + __builtin_fmaf(r, C.dN, sxi);
+                const uint64_t m = __ballot(stops(C, R.phi, ks + 1)) & running;
+                const bool stopped = (m >> lane) & 1u;
+                if (stopped) F = Stopped{R.phi, ks + 1, R.lw};
+                if (((running >> lane) & 1u) && (((ks + 1) & (group - 1)) == 0 || stopped)) record(ks + 1);
+                running &= ~m;
             }
-            if (run) R.j += 1;
-        } else if (run) {
-            run = !group4<POT, BIAS>(C, j_cap, z, r_mlp, R, k, &H);
-            const uint32_t k_end = run ? 4u * R.j : k;
-            if ((k_end & (group - 1)) == 0 || !run) record(k_end);
+            R.j += 1;
+        } else {
+            const uint64_t before = running;
+            const uint64_t m = group4<POT, BIAS>(C, j_cap, z, r_mlp, R, running, &F, &H);
+            // every running lane is at the same step: a record is due for all or for those that stopped
+            if (m || ((4u * q + 4u) & (group - 1)) == 0) {
+                const bool stopped = (m >> lane) & 1u;
+                const uint32_t k_end = stopped ? F.k : 4u * R.j;
+                if (((before >> lane) & 1u) && ((k_end & (group - 1)) == 0 || stopped)) record(k_end);
+            }
         }
     }
     if (have) {
-        a.k_out[i] = k;
-        a.lw_out[i] = R.lw;
-        a.st_out[i] = final_status(C, R.phi, k);
+        a.k_out[i] = F.k;
+        a.lw_out[i] = F.lw;
+        a.st_out[i] = final_status(C, F.phi, F.k);
         a.n_rec_out[i] = n_rec;
     }
 }

@@ -565,7 +565,8 @@ Shape launch_shape(const Device &d, const Prepared &P, const LaunchCfg &c) {
     // tables go to LDS where the workgroups that share a CU can all hold theirs, beside the
     // learned sampler's copy of the network's operand tiles
     const size_t share = std::min<size_t>(d.max_lds, 160 * 1024 / static_cast<size_t>(std::max(1, (s.n_wg + d.cus - 1) / d.cus)));
-    s.lds = P.lay.slice_bytes <= share - (P.bias == PYFPT_BIAS_MLP ? std::min(share, fpt::MLP_TILE_LDS_BYTES) : 0);
+    const size_t other = sizeof(Stopped) * s.block + (P.bias == PYFPT_BIAS_MLP ? fpt::MLP_TILE_LDS_BYTES : 0);
+    s.lds = P.lay.slice_bytes + other <= share;
     return s;
 }
 
@@ -670,7 +671,8 @@ int run_prepared(Device &d, const Prepared &P, uint64_t seed, const LaunchCfg &c
     ma.edges = reinterpret_cast<const double *>(W + m.edges);
     ma.counts = reinterpret_cast<uint64_t *>(W + m.counts);
     ma.values = reinterpret_cast<double *>(W + m.values);
-    const size_t lds_bytes = shape.lds ? P.lay.slice_bytes : 0;
+    // the workgroup's table, where it fits, and each lane's stopped run
+    const size_t lds_bytes = (shape.lds ? P.lay.slice_bytes : 0) + sizeof(Stopped) * shape.block;
 
     auto enqueue = [&](bool timed) -> int {
         HIP_TRY(launch_init_queue(sa.queue, stream), "launch init");
