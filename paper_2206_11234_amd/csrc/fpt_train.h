@@ -51,6 +51,7 @@ struct TrainArgs {
     const float *theta;         // binary32 master parameters
     MlpConsts mc;               // input normalisation, output scale, N*
     float dN;                   // binary32 dN
+    float *r;                   // r_theta per record (n_rec)
     double *lw_theta;           // ln w_theta per path
     const double *lw0;          // ln w_0 per path (sampled)
     double n_total;             // runs drawn

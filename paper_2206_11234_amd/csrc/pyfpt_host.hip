@@ -1296,8 +1296,8 @@ static int pyfpt_proposal_loss_grad_impl(const pyfpt_mlp *net, double target_N, 
     }
     hipStream_t stream = opt ? static_cast<hipStream_t>(opt->stream) : nullptr;
     const int n_part = backward_groups(n_rec);
-    DevBuf r, off, th, lwt, l0, c, ls, part, g;
-    if ((rc = r.alloc(16ull * n_rec)) || (rc = off.alloc(8ull * (n_paths + 1))) || (rc = th.alloc(4ull * NET_N_PARAMS)) ||
+    DevBuf r, off, th, lwt, l0, c, ls, part, g, rr;
+    if ((rc = rr.alloc(4ull * n_rec)) || (rc = r.alloc(16ull * n_rec)) || (rc = off.alloc(8ull * (n_paths + 1))) || (rc = th.alloc(4ull * NET_N_PARAMS)) ||
         (rc = lwt.alloc(8ull * n_paths)) || (rc = l0.alloc(8ull * n_paths)) ||
         (rc = c.alloc(8ull * n_paths)) || (rc = ls.alloc(8)) ||
         (rc = part.alloc(4ull * NET_N_PARAMS * static_cast<uint64_t>(n_part))) || (rc = g.alloc(8ull * NET_N_PARAMS)))
@@ -1318,6 +1318,7 @@ static int pyfpt_proposal_loss_grad_impl(const pyfpt_mlp *net, double target_N, 
     ta.theta = th.as<float>();
     ta.mc = mlp_consts(*net, target_N);
     ta.dN = static_cast<float>(dN);
+    ta.r = rr.as<float>();
     ta.lw_theta = lwt.as<double>();
     ta.lw0 = l0.as<double>();
     ta.n_total = n_total;
@@ -1504,9 +1505,9 @@ static int pyfpt_train_proposal_impl(const pyfpt_instance *inst, uint64_t seed, 
         // 3. replay into records under the proposal that drew the runs
         Prepared P;
         if ((rc = prepare(&I, 1, P))) return rc;
-        DevBuf dt, doff, drec, rk, rlw, rst, rnr, lwt, l0, c, ls, part;
+        DevBuf dt, doff, drec, rk, rlw, rst, rnr, lwt, l0, c, ls, part, rr;
         const int n_part = backward_groups(n_rec);
-        if ((rc = dt.alloc(8ull * np)) || (rc = doff.alloc(8ull * (np + 1))) || (rc = drec.alloc(16ull * n_rec)) ||
+        if ((rc = rr.alloc(4ull * n_rec)) || (rc = dt.alloc(8ull * np)) || (rc = doff.alloc(8ull * (np + 1))) || (rc = drec.alloc(16ull * n_rec)) ||
             (rc = rk.alloc(4ull * np)) || (rc = rlw.alloc(8ull * np)) || (rc = rst.alloc(4ull * np)) ||
             (rc = rnr.alloc(8ull * np)) || (rc = lwt.alloc(8ull * np)) ||
             (rc = l0.alloc(8ull * np)) || (rc = c.alloc(8ull * np)) || (rc = ls.alloc(8)) ||
@@ -1545,6 +1546,7 @@ static int pyfpt_train_proposal_impl(const pyfpt_instance *inst, uint64_t seed, 
         ta.theta = th.as<float>();
         ta.mc = P.inst[0].mlp;
         ta.dN = P.inst[0].c.dN;
+        ta.r = rr.as<float>();
         ta.lw_theta = lwt.as<double>();
         ta.lw0 = l0.as<double>();
         ta.n_total = static_cast<double>(ns);
