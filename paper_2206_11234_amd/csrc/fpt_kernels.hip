@@ -167,6 +167,8 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
     bool first = true;
     bool drained = n_first >= a.v_total;   // no id is left in the queue
     Team team;
+    F4 batch{};                 // learned bias: the team's current batch of normals
+    int batch_at = 0;           // and the group of it that comes next
     // Power-law bias: the exponent where the wave's instances share one of 1 .. 4, whose group is
     // compiled for it; a loop over an exponent per lane costs a step 24 instructions and its overlap
     // with the next (2e5 runs with p = 3: 5.2 against 4.6 ms).
@@ -306,15 +308,25 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
             // start at k = 0 and refill only between passes, so every lane of the wave is at a
             // multiple of the pass length here and the evaluation points of all lanes coincide.
             const int E = a.mlp_every;
-            // a team's runs fit one block of 32 columns, slot c in lane c: half the network's work,
-            // and with E >= 8 the normals of E / 4 groups shared out besides
-            const int most = E >= 8 ? E / 4 : 2;
-            if (teamed && team_halves(team.shift, n_act, most)) team_form(team, running, lt_mask, lane, noise, most);
+            // a team's runs fit one block of 32 columns, slot c in lane c: half the network's work (16
+            // slots: a third); its batches of normals last over G / (E / 4) passes where G is larger
+            if (teamed && team_halves(team.shift, n_act, 8)) {
+                team_form(team, running, lt_mask, lane, noise, 8);
+                batch_at = 0;
+            }
+            const int g_mask = team.groups() - 1;
+            auto team_next = [&](uint32_t q) {      // the normals of the q-th group from here
+                if (batch_at == 0) batch = team_draw(team, lane, R.j + q, a.key0, a.key1);
+                const F4 z = team_fetch(team, batch, batch_at);
+                batch_at = (batch_at + 1) & g_mask;
+                return z;
+            };
             auto network = [&](float phi_, float N_) {
                 const MlpIn x = mlp_input(mc, phi_, N_);
                 if (!teamed) return mc.out_scale * mlp_forward_lds(tile_lds, x);
                 const MlpIn xs{lane_read(team.slot_lane, x.lo), lane_read(team.slot_lane, x.hi)};
-                return mc.out_scale * lane_read(team.fetch0, mlp_block_lds(tile_lds, xs, 0));
+                const float o = team.shift <= 4 ? mlp_block_lds<true>(tile_lds, xs, 0) : mlp_block_lds(tile_lds, xs, 0);
+                return mc.out_scale * lane_read(team.fetch0, o);
             };
             // One evaluation per pass of E = 4, 8 or 16 steps.  The pass's normals do not depend
             // on the network, so they are drawn before it and the scheduler interleaves their
@@ -325,15 +337,9 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
             auto pass = [&](auto nq_tag) {
                 constexpr int NQ = decltype(nq_tag)::value;
                 F4 zz[NQ];
-                if (NQ > 1 && teamed) {
-                    F4 z{};
+                if (teamed) {
 #pragma unroll
-                    for (int q = 0; q < NQ; q += 2) {
-                        const int g = q & (team.groups() - 1);     // group within the batch (2 or 4 groups)
-                        if (g == 0) z = team_draw(team, lane, R.j + q, a.key0, a.key1);
-                        zz[q] = team_fetch(team, z, g);
-                        if constexpr (NQ > 1) zz[q + 1] = team_fetch(team, z, g + 1);
-                    }
+                    for (int q = 0; q < NQ; ++q) zz[q] = team_next(q);
                 } else {
 #pragma unroll
                     for (int q = 0; q < NQ; ++q) {
@@ -356,7 +362,7 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
                 pass(std::integral_constant<int, 1>{});
             } else {
                 // E = 1: an evaluation before every step
-                const F4 z = normals4(R.j, noise, a.key0, a.key1);
+                const F4 z = teamed ? team_next(0) : normals4(R.j, noise, a.key0, a.key1);
                 const float ns[4] = {z.a, z.b, z.c, z.d};
 #pragma unroll
                 for (int s = 0; s < 4; ++s) {

@@ -219,8 +219,44 @@ __device__ __forceinline__ MlpIn mlp_input(const MlpConsts &M, float phi, float 
     return MlpIn{__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi)};
 }
 
+// act_to_operands where only the first 16 columns are in use: lanes 16-31 and 48-63 hold no column,
+// so they take the activations of the second half of each K-block's eight units (their accumulators
+// swap rows of 16 lanes), and the packed results come back the same way: 144 instructions for a
+// layer instead of 240, the same operations for every unit.
+__device__ __forceinline__ void act_to_operands16(const f32x16 &d0, const f32x16 &d1, bf16x8 b[5]) {
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    const __bf16 z = __builtin_bit_cast(__bf16, (uint16_t)0);
+    const __bf16 one = (__bf16)1.0f;
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb) {
+        const f32x16 &d = kb < 2 ? d0 : d1;
+        const int v = 8 * (kb & 1);
+        uint32_t q[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            bf16x2 p;
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                const auto x = __builtin_amdgcn_permlane16_swap(__float_as_uint(d[v + 2 * i + s]), __float_as_uint(d[v + 4 + 2 * i + s]),
+                                                                false, false);
+                p[s] = (__bf16)tanh_act(__uint_as_float(x[0]));
+            }
+            q[i] = __builtin_bit_cast(uint32_t, p);
+        }
+        const auto h0 = __builtin_amdgcn_permlane16_swap(q[0], q[0], false, false);
+        const auto h1 = __builtin_amdgcn_permlane16_swap(q[1], q[1], false, false);
+        const u32x4 w = {q[0], q[1], h0[1], h1[1]};
+        b[kb] = __builtin_bit_cast(bf16x8, w);
+    }
+    const int h = __lane_id() >> 5;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) b[4][s] = (h == 0 && s == 0) ? one : z;
+}
+
 // w3 . h2 + b3 of the 32 trajectories of N-block nb (the inputs of lanes 32 nb .. 32 nb + 31), in
-// lanes 0 .. 31 in order.
+// lanes 0 .. 31 in order.  HALF: only the first 16 are wanted.
+template <bool HALF = false>
 __device__ __forceinline__ float mlp_block_lds(const bf16x8 *L, const MlpIn &in, int nb) {
     const int l = __lane_id();
     const int h = l >> 5;
@@ -231,7 +267,11 @@ __device__ __forceinline__ float mlp_block_lds(const bf16x8 *L, const MlpIn &in,
     f32x16 d0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(L[0 * 64 + l], bx, zacc, 0, 0, 0);
     f32x16 d1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(L[1 * 64 + l], bx, zacc, 0, 0, 0);
     bf16x8 b[5];
-    act_to_operands(d0, d1, b);
+    auto activate = [&]() {
+        if constexpr (HALF) act_to_operands16(d0, d1, b);
+        else act_to_operands(d0, d1, b);
+    };
+    activate();
     // keep each layer's LDS reads next to their use: hoisted together they would hold all
     // 17 tiles in registers again
     __builtin_amdgcn_sched_barrier(0);
@@ -242,7 +282,7 @@ __device__ __forceinline__ float mlp_block_lds(const bf16x8 *L, const MlpIn &in,
         d0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(L[(2 + kb) * 64 + l], b[kb], d0, 0, 0, 0);
         d1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(L[(7 + kb) * 64 + l], b[kb], d1, 0, 0, 0);
     }
-    act_to_operands(d0, d1, b);
+    activate();
     __builtin_amdgcn_sched_barrier(0);
     f32x16 o = zacc;
 #pragma unroll

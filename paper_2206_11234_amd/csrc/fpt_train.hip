@@ -43,8 +43,8 @@ namespace fpt {
 // replay into records
 // ---------------------------------------------------------------------------
 // One wave replays up to `slots` paths: with fewer paths than the chip has lanes a replay lasts as
-// long as its longest path's steps at a lone wave's rate, so a wave takes 16 or 32 paths and its other
-// lanes draw normals ahead for them (Team) and leave half of the network's columns out.
+// long as its longest path's steps at a lone wave's rate, so a wave takes 8 to 32 paths, its other lanes
+// draw normals ahead for them (Team), and the network's unused columns are left out.
 template <int POT, int BIAS>
 __global__ __launch_bounds__(256) void fpt_record_kernel(RecordArgs a) {
     const uint32_t lane = __lane_id();
@@ -96,30 +96,28 @@ __global__ __launch_bounds__(256) void fpt_record_kernel(RecordArgs a) {
     // max(4, E) steps, so every lane is at a multiple of the pass length at its start
     const int E = (BIAS == BIAS_MLP) ? a.mlp_every : 4;
     const int n_q = E > 4 ? E >> 2 : 1;
-    // lanes share normals between the groups of a pass, or of G groups without a network
-    const int most = BIAS == BIAS_MLP ? (n_q > 1 ? n_q : 2) : 8;
     const bool teamed = a.slots <= 32;
-    const bool share = teamed && (BIAS != BIAS_MLP || n_q > 1);
     Team team;
     if (teamed) {
-        team_form(team, running, (lane == 0) ? 0ull : (~0ull >> (64 - lane)), lane, noise, most);
+        team_form(team, running, (lane == 0) ? 0ull : (~0ull >> (64 - lane)), lane, noise, 8);
     }
     auto network = [&](float phi_, float N_) {
         const MlpIn x = mlp_input(mc, phi_, N_);
         if (!teamed) return mc.out_scale * mlp_forward_lds(tile_lds, x);
         const MlpIn xs{lane_read(team.slot_lane, x.lo), lane_read(team.slot_lane, x.hi)};
-        return mc.out_scale * lane_read(team.fetch0, mlp_block_lds(tile_lds, xs, 0));
+        const float o = team.shift <= 4 ? mlp_block_lds<true>(tile_lds, xs, 0) : mlp_block_lds(tile_lds, xs, 0);
+        return mc.out_scale * lane_read(team.fetch0, o);
     };
     F4 batch{};
     float r_mlp = 0.0f;
-    const int batch_mask = share ? team.groups() - 1 : 0;
+    const int batch_mask = team.groups() - 1;
     for (int q = 0; running; ++q) {
         // q-th group of four steps; the lanes still running are all in their group q
         if constexpr (BIAS == BIAS_MLP) {
             if ((q & (n_q - 1)) == 0) r_mlp = network(R.phi, static_cast<float>(4u * R.j) * C.dN);
         }
         F4 z;
-        if (share) {
+        if (teamed) {
             if ((q & batch_mask) == 0) batch = team_draw(team, lane, R.j, a.key0, a.key1);
             z = team_fetch(team, batch, q & batch_mask);
         } else {

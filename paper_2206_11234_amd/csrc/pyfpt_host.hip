@@ -523,17 +523,15 @@ Shape launch_shape(const Device &d, const Prepared &P, const LaunchCfg &c) {
         const uint64_t simds = static_cast<uint64_t>(d.cus) * 4;
         const bool mlp = P.bias == PYFPT_BIAS_MLP;
         const int E = P.mlp_every;
-        const int most = mlp ? std::max(2, E / 4) : 8;     // the largest G (see Team)
         double best = INFINITY;
         uint64_t waves = full_waves;
         for (int cap = 64; cap >= 8; cap /= 2) {
             const uint64_t w = std::max<uint64_t>(1, (P.v_total + cap - 1) / cap);
             if (w > full_waves) break;
             const double W = static_cast<double>(std::max<uint64_t>(2, (w + simds - 1) / simds));
-            const int G = std::min(64 / cap, mlp ? std::max(1, E / 4) : most);
-            double instr = 22.0 + 38.0 / G, chain = 130.0;
+            double instr = 22.0 + 38.0 * cap / 64, chain = 130.0;
             if (mlp) {
-                instr += (cap > 32 ? 1040.0 : 520.0) / E;
+                instr += (cap > 32 ? 1040.0 : cap > 16 ? 520.0 : 330.0) / E;
                 chain += 600.0 / E;
             }
             const double cost = std::max(chain, 2.4 * W * instr);
@@ -542,7 +540,6 @@ Shape launch_shape(const Device &d, const Prepared &P, const LaunchCfg &c) {
                 s.lane_cap = cap;
                 waves = w;
             }
-            if (64 / cap >= most) break;
         }
         // a workgroup of four waves puts one on each SIMD of a CU; up to two waves per CU go alone;
         // never more workgroups than cfg's grid, which the workspace is sized for
@@ -986,8 +983,7 @@ int records_device(const Prepared &P, uint64_t seed, int group, int stride, cons
     ra.mlp_every = P.mlp_every;
     // paths per wave: as few as leave each SIMD two waves (launch_shape's balance)
     ra.slots = 64;
-    const uint32_t least = P.bias == PYFPT_BIAS_MLP ? (P.mlp_every >= 16 ? 16 : 32) : 8;
-    while (ra.slots > least && (n_paths + ra.slots / 2 - 1) / (ra.slots / 2) <= 2048) ra.slots /= 2;
+    while (ra.slots > 8 && (n_paths + ra.slots / 2 - 1) / (ra.slots / 2) <= 2048) ra.slots /= 2;
     ra.mlp_params = P.mlp_params;
     ra.rec_off = d_off;
     ra.rec = d_rec;
