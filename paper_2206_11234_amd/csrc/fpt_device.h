@@ -206,12 +206,17 @@ struct F4 {
     float a, b, c, d;
 };
 
-__device__ __forceinline__ F4 normals4(uint32_t j, const PhiloxRun &r, uint32_t key0, uint32_t key1) {
+// odd_mask: see sincos2pi_bits.
+__device__ __forceinline__ uint32_t normals_mask() {
+    uint32_t m = 0x3FFFFEu;
+    asm volatile("" : "+v"(m));
+    return m;
+}
+
+__device__ __forceinline__ F4 normals4(uint32_t j, const PhiloxRun &r, uint32_t key0, uint32_t key1, uint32_t odd_mask) {
     // the key schedule is recomputed by scalar adds at each call: left to itself the compiler
     // hoists all round keys into scalar registers and spills them to vector lanes
     asm volatile("" : "+s"(key0), "+s"(key1));
-    uint32_t odd_mask = 0x3FFFFEu;
-    asm("" : "+v"(odd_mask));
     const U4 x = philox_block(j, r, key0, key1);
     F4 out;
     float c, s;
@@ -317,8 +322,11 @@ __device__ __forceinline__ int final_status(const StepConsts &C, float phi, uint
 // drift, noise and bias at the pre-step point): the field after it, reflected above phi_UV (Sec.
 // 2.1, Sec. 3), and the weight increment dlw = -r (r dN/2 + sqrt(dN) xi) that the caller adds to
 // ln w in binary64.  n = -xi/2; r_net is the bias when it comes from the learned network.  Returns
-// r and writes sqrt(dN) xi, which the training replay reuses.
-template <int POT, int BIAS, int P = 0>
+// r and writes sqrt(dN) xi, which the training replay reuses.  WALL: the run has a reflecting wall,
+// has none, or either.
+enum : int { WALL_NONE = 0, WALL_ALL = 1, WALL_ANY = 2 };
+
+template <int POT, int BIAS, int P = 0, int WALL = WALL_ANY>
 __device__ __forceinline__ float em_step(const StepConsts &C, float &phi, float n, float r_net, float &dlw, float &sxi) {
     const FieldTerms<POT> T = field_terms<POT>(C, phi);
     float r = 0.0f, drift_dN;
@@ -340,7 +348,7 @@ __device__ __forceinline__ float em_step(const StepConsts &C, float &phi, float 
     // Reflection x -> 2 phi_UV - x above the wall, as a minimum: 2 phi_UV is exact and rounding
     // is monotone, so fl(2 phi_UV - x) <= phi_UV < x exactly when x > phi_UV (and >= x otherwise);
     // with no wall 2 phi_UV is +inf and the minimum is x.
-    phi = __builtin_fminf(nphi, C.two_uv - nphi);
+    phi = WALL == WALL_NONE ? nphi : __builtin_fminf(nphi, C.two_uv - nphi);
     return r;
 }
 
@@ -377,7 +385,7 @@ struct Stopped {
 // that the whole group is one stretch of code.  Returns the lanes whose runs stopped here and takes
 // them out of `running`.  H, where not NULL, gains fma(r, dN, sqrt(dN) xi) of each step taken, in
 // step order.
-template <int POT, int BIAS, int P = 0>
+template <int POT, int BIAS, int P = 0, int WALL = WALL_ANY>
 __device__ __forceinline__ uint64_t group4(const StepConsts &C, uint32_t j_cap, const F4 &z, float r_net, RunState &R,
                                            uint64_t &running, Stopped *F, float *H = nullptr) {
     const float n[4] = {z.a, z.b, z.c, z.d};
@@ -389,7 +397,7 @@ __device__ __forceinline__ uint64_t group4(const StepConsts &C, uint32_t j_cap, 
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
         float dlw, sxi;
-        const float r = em_step<POT, BIAS, P>(C, phi, n[s], r_net, dlw, sxi);
+        const float r = em_step<POT, BIAS, P, WALL>(C, phi, n[s], r_net, dlw, sxi);
         if constexpr (BIAS != BIAS_NONE) lw += static_cast<double>(dlw);
         if (H) sum = sum + __builtin_fmaf(r, C.dN, sxi);
         p[s] = phi;
@@ -398,15 +406,19 @@ __device__ __forceinline__ uint64_t group4(const StepConsts &C, uint32_t j_cap, 
     }
     if (H) *H = sum;
     const float lo = __builtin_fminf(__builtin_fminf(p[0], p[1]), __builtin_fminf(p[2], p[3]));
-    float hi;       // (the compiler's own maximum first canonicalises each operand)
-    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(hi) : "v"(p[0]), "v"(p[1]), "v"(p[2]));
-    asm("v_max_f32 %0, %1, %2" : "=v"(hi) : "v"(hi), "v"(p[3]));
     const uint32_t j = R.j;
     R.phi = phi;
     R.lw = lw;
     R.j = j + 1;
     // (no short circuit: its branches would split the group's arithmetic)
-    const uint64_t m = __builtin_amdgcn_ballot_w64((lo <= C.phi_end) | (hi > C.phi_esc) | (j + 1 >= j_cap)) & running;
+    bool stop = (lo <= C.phi_end) | (j + 1 >= j_cap);
+    if constexpr (WALL != WALL_ALL) {              // runs with a wall do not escape
+        float hi;       // (the compiler's own maximum first canonicalises each operand)
+        asm("v_max3_f32 %0, %1, %2, %3" : "=v"(hi) : "v"(p[0]), "v"(p[1]), "v"(p[2]));
+        asm("v_max_f32 %0, %1, %2" : "=v"(hi) : "v"(hi), "v"(p[3]));
+        stop |= hi > C.phi_esc;
+    }
+    const uint64_t m = __builtin_amdgcn_ballot_w64(stop) & running;
     if (__builtin_expect(m != 0, 0)) {
         running &= ~m;
         if ((m >> __lane_id()) & 1u) {

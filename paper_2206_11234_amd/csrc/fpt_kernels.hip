@@ -173,19 +173,31 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
     // compiled for it; a loop over an exponent per lane costs a step 24 instructions and its overlap
     // with the next (2e5 runs with p = 3: 5.2 against 4.6 ms).
     int p_wave = 0;
-    auto group = [&](const F4 &z) {
+    // Whether the wave's runs all have a wall, all have none, or differ: two instructions a step
+    // without the reflection, three a group without the escape test.
+    int walls = WALL_ANY;
+    auto specialised = [&](auto f) {
+        auto with = [&](auto p, auto wall) { f([&](const F4 &z) { (void)group4<POT, BIAS, p(), wall()>(C, j_cap, z, 0.0f, R, running, F); }); };
+        using std::integral_constant;
+        constexpr integral_constant<int, 0> p_any;
+        constexpr integral_constant<int, WALL_ANY> wall_any;
         if constexpr (BIAS == BIAS_POWER) {
             switch (p_wave) {
-            case 1: (void)group4<POT, BIAS, 1>(C, j_cap, z, 0.0f, R, running, F); break;
-            case 2: (void)group4<POT, BIAS, 2>(C, j_cap, z, 0.0f, R, running, F); break;
-            case 3: (void)group4<POT, BIAS, 3>(C, j_cap, z, 0.0f, R, running, F); break;
-            case 4: (void)group4<POT, BIAS, 4>(C, j_cap, z, 0.0f, R, running, F); break;
-            default: (void)group4<POT, BIAS>(C, j_cap, z, 0.0f, R, running, F); break;
+            case 1: with(integral_constant<int, 1>{}, wall_any); break;
+            case 2: with(integral_constant<int, 2>{}, wall_any); break;
+            case 3: with(integral_constant<int, 3>{}, wall_any); break;
+            case 4: with(integral_constant<int, 4>{}, wall_any); break;
+            default: with(p_any, wall_any); break;
             }
+        } else if constexpr (POT == POT_QUADRATIC_BUMP) {
+            with(p_any, wall_any);
         } else {
-            (void)group4<POT, BIAS>(C, j_cap, z, 0.0f, R, running, F);
+            if (walls == WALL_NONE) with(p_any, integral_constant<int, WALL_NONE>{});
+            else if (walls == WALL_ALL) with(p_any, integral_constant<int, WALL_ALL>{});
+            else with(p_any, wall_any);
         }
     };
+    const uint32_t odd_mask = normals_mask();
     // learned proposal: one copy of the network's A operands per workgroup
     __shared__ bf16x8 tile_lds[BIAS == BIAS_MLP ? MLP_N_FRAG * 64 : 1];
     if constexpr (BIAS == BIAS_MLP) {
@@ -276,9 +288,13 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
             }
         }
         if (!active) break;
-        if constexpr (BIAS == BIAS_POWER) {
-            if (refill) {
-                // lanes without a run do not count
+        if (refill) {
+            // lanes without a run do not count
+            if constexpr (BIAS <= BIAS_NOISE_SCALED && POT != POT_QUADRATIC_BUMP) {
+                const uint64_t walled = __ballot(C.two_uv < INFINITY) & active;
+                walls = walled == 0 ? WALL_NONE : walled == active ? WALL_ALL : WALL_ANY;
+            }
+            if constexpr (BIAS == BIAS_POWER) {
                 const int p0 = __builtin_amdgcn_readlane(C.p, __ffsll(static_cast<unsigned long long>(active)) - 1);
                 p_wave = (__ballot(C.p != p0) & active) == 0 ? p0 : 0;
             }
@@ -290,17 +306,38 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
         // ---- a pass: groups of four Euler-Maruyama steps, each from one Philox call
         if constexpr (BIAS != BIAS_MLP) {
             if (teamed) {
-                if (team_halves(team.shift, n_act, 8)) team_form(team, running, lt_mask, lane, noise, 8);
-                const F4 z = team_draw(team, lane, R.j, a.key0, a.key1);
-                F4 zn = team_fetch(team, z, 0);
-                const int n_g = team.groups();
-                for (int g = 0; g < n_g; ++g) {
-                    const F4 zg = zn;
-                    if (g + 1 < n_g) zn = team_fetch(team, z, g + 1);
-                    group(zg);
-                }
+                // to the end of the wave's last run: nothing is refilled or retired before it
+                specialised([&](auto group) {
+                    while (running) {
+                        team_form(team, running, lt_mask, lane, noise, 8);
+                        const int n_g = team.groups();              // 2, 4 or 8 groups a batch
+                        uint32_t j = lane_read(team.slot_lane, R.j) + (lane >> team.shift);
+                        F4 z = normals4(j, team.noise, a.key0, a.key1, odd_mask);
+                        F4 zn = team_fetch(team, z, 0);
+                        do {
+                            // a batch ahead: its draw fills the gaps in this one's chain of steps, and
+                            // its first group is fetched before this one's last steps
+                            j += static_cast<uint32_t>(n_g);
+                            const F4 zb = normals4(j, team.noise, a.key0, a.key1, odd_mask);
+                            for (int g = 0; g < n_g; g += 2) {
+                                const F4 z0 = zn;
+                                const F4 z1 = team_fetch(team, z, g + 1);
+                                group(z0);
+                                const bool last = g + 2 == n_g;
+                                zn = team_fetch(team, last ? zb : z, last ? 0 : g + 2);
+                                group(z1);
+                            }
+                            z = zb;
+                        } while (running && !team_halves(team.shift, __popcll(running), 8));
+                    }
+                });
             } else {
-                group(normals4(R.j, noise, a.key0, a.key1));
+                // until a run stops: nothing else changes what is compiled in or hands out new runs
+                specialised([&](auto group) {
+                    const uint64_t before = running;
+                    do group(normals4(R.j, noise, a.key0, a.key1, odd_mask));
+                    while (running == before);
+                });
             }
         } else {
             // the network is evaluated by all 64 lanes together, outside divergent code.  One
@@ -316,7 +353,7 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
             }
             const int g_mask = team.groups() - 1;
             auto team_next = [&](uint32_t q) {      // the normals of the q-th group from here
-                if (batch_at == 0) batch = team_draw(team, lane, R.j + q, a.key0, a.key1);
+                if (batch_at == 0) batch = team_draw(team, lane, R.j + q, a.key0, a.key1, odd_mask);
                 const F4 z = team_fetch(team, batch, batch_at);
                 batch_at = (batch_at + 1) & g_mask;
                 return z;
@@ -343,7 +380,7 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
                 } else {
 #pragma unroll
                     for (int q = 0; q < NQ; ++q) {
-                        zz[q] = normals4(R.j + q, noise, a.key0, a.key1);
+                        zz[q] = normals4(R.j + q, noise, a.key0, a.key1, odd_mask);
                         // four draws at once would not fit the registers
                         if (q == 1) __builtin_amdgcn_sched_barrier(0);
                     }
@@ -362,7 +399,7 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
                 pass(std::integral_constant<int, 1>{});
             } else {
                 // E = 1: an evaluation before every step
-                const F4 z = teamed ? team_next(0) : normals4(R.j, noise, a.key0, a.key1);
+                const F4 z = teamed ? team_next(0) : normals4(R.j, noise, a.key0, a.key1, odd_mask);
                 const float ns[4] = {z.a, z.b, z.c, z.d};
 #pragma unroll
                 for (int s = 0; s < 4; ++s) {

@@ -53,8 +53,9 @@ __device__ __forceinline__ void team_form(Team &T, uint64_t act, uint64_t lt_mas
 
 // The normals of this lane's slot's run, lane / S groups after the group j of that run (own_j:
 // every lane's own run's group).
-__device__ __forceinline__ F4 team_draw(const Team &T, uint32_t lane, uint32_t own_j, uint32_t key0, uint32_t key1) {
-    return normals4(lane_read(T.slot_lane, own_j) + (lane >> T.shift), T.noise, key0, key1);
+__device__ __forceinline__ F4 team_draw(const Team &T, uint32_t lane, uint32_t own_j, uint32_t key0, uint32_t key1,
+                                        uint32_t odd_mask) {
+    return normals4(lane_read(T.slot_lane, own_j) + (lane >> T.shift), T.noise, key0, key1, odd_mask);
 }
 
 // This lane's run's normals of the g-th group of the batch z.

@@ -108,6 +108,7 @@ __global__ __launch_bounds__(256) void fpt_record_kernel(RecordArgs a) {
         const float o = team.shift <= 4 ? mlp_block_lds<true>(tile_lds, xs, 0) : mlp_block_lds(tile_lds, xs, 0);
         return mc.out_scale * lane_read(team.fetch0, o);
     };
+    const uint32_t odd_mask = normals_mask();
     F4 batch{};
     float r_mlp = 0.0f;
     const int batch_mask = team.groups() - 1;
@@ -118,10 +119,10 @@ __global__ __launch_bounds__(256) void fpt_record_kernel(RecordArgs a) {
         }
         F4 z;
         if (teamed) {
-            if ((q & batch_mask) == 0) batch = team_draw(team, lane, R.j, a.key0, a.key1);
+            if ((q & batch_mask) == 0) batch = team_draw(team, lane, R.j, a.key0, a.key1, odd_mask);
             z = team_fetch(team, batch, q & batch_mask);
         } else {
-            z = normals4(R.j, noise, a.key0, a.key1);
+            z = normals4(R.j, noise, a.key0, a.key1, odd_mask);
         }
         if (E == 1 || group < 4) {
             // the network before every step, or a record of every step
