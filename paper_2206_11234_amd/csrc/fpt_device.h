@@ -247,22 +247,36 @@ struct StepConsts {
 // S = sqrt(V/3)/(2 pi) at phi and the whole drift D + B, D = -V'/V (Sec. 2.3), B = r S.  D is
 // formed as -2/phi (+ the bump's term): 2/phi is exact in the reciprocal, so fma(-2, 1/phi, B)
 // rounds D + B once, as adding -2/phi does.
+// FAR (bump potential): phi is so far from the bump that its exponential is 0 (exp_f32's underflow,
+// (phi - phi0)^2 / (2 w^2) above 80), so that 1 + a g is 1 and the bump's part of D is 0; near
+// receives (phi - phi0)^2, from which the caller tells whether that held.
+constexpr float BUMP_FAR = 80.0f;
+
 template <int POT>
 struct FieldTerms {
     float S;         // noise amplitude
     float y;         // 1/phi
     float corr;      // bump: its part of D
+    float near;      // bump: (phi - phi0)^2
 };
 
-template <int POT>
+template <int POT, bool FAR>
 __device__ __forceinline__ FieldTerms<POT> field_terms(const StepConsts &C, float phi) {
     FieldTerms<POT> T;
+    T.near = 0.0f;
     if constexpr (POT == POT_QUADRATIC) {
         T.y = recip_f32(phi);
         T.S = C.cm * phi;
     } else if constexpr (POT == POT_QUADRATIC_BUMP) {
         const float dphi = phi - C.phi0;
         const float e2 = dphi * dphi;
+        T.near = e2;
+        if constexpr (FAR) {
+            T.corr = 0.0f;
+            T.y = recip_f32(phi);
+            T.S = (C.cm * phi) * sqrt_f32(1.0f);
+            return T;
+        }
         const float x = -(e2 * C.inv_2w2);
         const float g = exp_f32(x);
         const float ag = C.a * g;
@@ -277,9 +291,9 @@ __device__ __forceinline__ FieldTerms<POT> field_terms(const StepConsts &C, floa
     return T;
 }
 
-template <int POT, bool BIASED>
+template <int POT, bool BIASED, bool FAR>
 __device__ __forceinline__ float drift(const FieldTerms<POT> &T, float B) {
-    if constexpr (POT == POT_QUADRATIC) {
+    if constexpr (POT == POT_QUADRATIC || (POT == POT_QUADRATIC_BUMP && FAR)) {
         return BIASED ? __builtin_fmaf(-2.0f, T.y, B) : -2.0f * T.y;
     } else if constexpr (POT == POT_QUADRATIC_BUMP) {
         const float D = __builtin_fmaf(-2.0f, T.y, T.corr);
@@ -326,17 +340,19 @@ __device__ __forceinline__ int final_status(const StepConsts &C, float phi, uint
 // has none, or either.
 enum : int { WALL_NONE = 0, WALL_ALL = 1, WALL_ANY = 2 };
 
-template <int POT, int BIAS, int P = 0, int WALL = WALL_ANY>
-__device__ __forceinline__ float em_step(const StepConsts &C, float &phi, float n, float r_net, float &dlw, float &sxi) {
-    const FieldTerms<POT> T = field_terms<POT>(C, phi);
+template <int POT, int BIAS, int P = 0, int WALL = WALL_ANY, bool FAR = false>
+__device__ __forceinline__ float em_step(const StepConsts &C, float &phi, float n, float r_net, float &dlw, float &sxi,
+                                         float *near = nullptr) {
+    const FieldTerms<POT> T = field_terms<POT, FAR>(C, phi);
+    if (near) *near = T.near;
     float r = 0.0f, drift_dN;
     sxi = C.sq_m2 * n;
     if constexpr (BIAS == BIAS_NONE) {
-        drift_dN = drift<POT, false>(T, 0.0f) * C.dN;
+        drift_dN = drift<POT, false, FAR>(T, 0.0f) * C.dN;
     } else {
         if constexpr (BIAS == BIAS_MLP) r = r_net;
         else r = bias_ratio<BIAS, P>(C, phi, T.S);
-        drift_dN = drift<POT, true>(T, r * T.S) * C.dN;
+        drift_dN = drift<POT, true, FAR>(T, r * T.S) * C.dN;
     }
     // The whole increment (D + B) dN + S sqrt(dN) xi is formed first and rounded onto phi once.
     // Adding the deterministic part to phi on its own would round it to phi's grid every step:
@@ -376,6 +392,35 @@ struct Stopped {
     double lw;
 };
 
+// Four steps from R: the field, ln w and (with H) the noise sum after each, and the smallest `near` of
+// the four starting points.
+struct Steps4 {
+    float p[4], h[4];
+    double w[4];
+    float near;
+};
+
+template <int POT, int BIAS, int P, int WALL, bool FAR>
+__device__ __forceinline__ Steps4 steps4(const StepConsts &C, const F4 &z, float r_net, const RunState &R, const float *H) {
+    const float n[4] = {z.a, z.b, z.c, z.d};
+    Steps4 S;
+    float phi = R.phi, near[4];
+    double lw = R.lw;
+    float sum = H ? *H : 0.0f;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        float dlw, sxi;
+        const float r = em_step<POT, BIAS, P, WALL, FAR>(C, phi, n[s], r_net, dlw, sxi, &near[s]);
+        if constexpr (BIAS != BIAS_NONE) lw += static_cast<double>(dlw);
+        if (H) sum = sum + __builtin_fmaf(r, C.dN, sxi);
+        S.p[s] = phi;
+        S.w[s] = lw;
+        S.h[s] = sum;
+    }
+    S.near = __builtin_fminf(__builtin_fminf(near[0], near[1]), __builtin_fminf(near[2], near[3]));
+    return S;
+}
+
 // The four steps of every lane's group R.j, all taken without a test between them: the group's
 // smallest and largest field and the step cap tell at its end whether a run has stopped inside it,
 // and then the first step that stops it is picked from the saved fields and weights into F (what the
@@ -385,30 +430,34 @@ struct Stopped {
 // that the whole group is one stretch of code.  Returns the lanes whose runs stopped here and takes
 // them out of `running`.  H, where not NULL, gains fma(r, dN, sqrt(dN) xi) of each step taken, in
 // step order.
+//
+// Bump potential: `far` tells whether the wave's runs were all far from the bump in the last group;
+// then this one is taken without it (65 instructions a step instead of 108), and again with it if a
+// run came near.
 template <int POT, int BIAS, int P = 0, int WALL = WALL_ANY>
 __device__ __forceinline__ uint64_t group4(const StepConsts &C, uint32_t j_cap, const F4 &z, float r_net, RunState &R,
-                                           uint64_t &running, Stopped *F, float *H = nullptr) {
-    const float n[4] = {z.a, z.b, z.c, z.d};
-    float p[4], h[4];
-    double w[4];
-    float phi = R.phi;
-    double lw = R.lw;
-    float sum = H ? *H : 0.0f;
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-        float dlw, sxi;
-        const float r = em_step<POT, BIAS, P, WALL>(C, phi, n[s], r_net, dlw, sxi);
-        if constexpr (BIAS != BIAS_NONE) lw += static_cast<double>(dlw);
-        if (H) sum = sum + __builtin_fmaf(r, C.dN, sxi);
-        p[s] = phi;
-        w[s] = lw;
-        h[s] = sum;
+                                           uint64_t &running, Stopped *F, bool &far, float *H = nullptr) {
+    Steps4 S;
+    if constexpr (POT == POT_QUADRATIC_BUMP) {
+        auto came_near = [&]() { return (__builtin_amdgcn_ballot_w64(!(S.near * C.inv_2w2 > BUMP_FAR)) & running) != 0; };
+        if (far) {
+            S = steps4<POT, BIAS, P, WALL, true>(C, z, r_net, R, H);
+            far = !came_near();
+        }
+        if (!far) {
+            S = steps4<POT, BIAS, P, WALL, false>(C, z, r_net, R, H);
+            far = !came_near();
+        }
+    } else {
+        S = steps4<POT, BIAS, P, WALL, false>(C, z, r_net, R, H);
     }
-    if (H) *H = sum;
+    const float *p = S.p, *h = S.h;
+    const double *w = S.w;
+    if (H) *H = h[3];
     const float lo = __builtin_fminf(__builtin_fminf(p[0], p[1]), __builtin_fminf(p[2], p[3]));
     const uint32_t j = R.j;
-    R.phi = phi;
-    R.lw = lw;
+    R.phi = p[3];
+    R.lw = w[3];
     R.j = j + 1;
     // (no short circuit: its branches would split the group's arithmetic)
     bool stop = (lo <= C.phi_end) | (j + 1 >= j_cap);

@@ -176,8 +176,9 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
     // Whether the wave's runs all have a wall, all have none, or differ: two instructions a step
     // without the reflection, three a group without the escape test.
     int walls = WALL_ANY;
+    bool far = false;           // bump potential: see group4
     auto specialised = [&](auto f) {
-        auto with = [&](auto p, auto wall) { f([&](const F4 &z) { (void)group4<POT, BIAS, p(), wall()>(C, j_cap, z, 0.0f, R, running, F); }); };
+        auto with = [&](auto p, auto wall) { f([&](const F4 &z) { (void)group4<POT, BIAS, p(), wall()>(C, j_cap, z, 0.0f, R, running, F, far); }); };
         using std::integral_constant;
         constexpr integral_constant<int, 0> p_any;
         constexpr integral_constant<int, WALL_ANY> wall_any;
@@ -389,7 +390,7 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
                 const float r_mlp = network(R.phi, static_cast<float>(4u * R.j) * C.dN);
                 __builtin_amdgcn_s_setprio(0);
 #pragma unroll
-                for (int q = 0; q < NQ; ++q) (void)group4<POT, BIAS>(C, j_cap, zz[q], r_mlp, R, running, F);
+                for (int q = 0; q < NQ; ++q) (void)group4<POT, BIAS>(C, j_cap, zz[q], r_mlp, R, running, F, far);
             };
             if (E == 16) {
                 pass(std::integral_constant<int, 4>{});

@@ -109,6 +109,7 @@ __global__ __launch_bounds__(256) void fpt_record_kernel(RecordArgs a) {
         return mc.out_scale * lane_read(team.fetch0, o);
     };
     const uint32_t odd_mask = normals_mask();
+    bool far = false;           // bump potential: see group4
     F4 batch{};
     float r_mlp = 0.0f;
     const int batch_mask = team.groups() - 1;
@@ -146,7 +147,7 @@ __global__ __launch_bounds__(256) void fpt_record_kernel(RecordArgs a) {
             R.j += 1;
         } else {
             const uint64_t before = running;
-            const uint64_t m = group4<POT, BIAS>(C, j_cap, z, r_mlp, R, running, &F, &H);
+            const uint64_t m = group4<POT, BIAS>(C, j_cap, z, r_mlp, R, running, &F, far, &H);
             // every running lane is at the same step: a record is due for all or for those that stopped
             if (m || ((4u * q + 4u) & (group - 1)) == 0) {
                 const bool stopped = (m >> lane) & 1u;
