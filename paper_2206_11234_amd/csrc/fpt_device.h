@@ -460,14 +460,14 @@ __device__ __forceinline__ uint64_t group4(const StepConsts &C, uint32_t j_cap, 
     R.lw = w[3];
     R.j = j + 1;
     // (no short circuit: its branches would split the group's arithmetic)
-    bool stop = (lo <= C.phi_end) | (j + 1 >= j_cap);
+    uint64_t m = __builtin_amdgcn_ballot_w64(lo <= C.phi_end) | __builtin_amdgcn_ballot_w64(j + 1 >= j_cap);
     if constexpr (WALL != WALL_ALL) {              // runs with a wall do not escape
         float hi;       // (the compiler's own maximum first canonicalises each operand)
         asm("v_max3_f32 %0, %1, %2, %3" : "=v"(hi) : "v"(p[0]), "v"(p[1]), "v"(p[2]));
         asm("v_max_f32 %0, %1, %2" : "=v"(hi) : "v"(hi), "v"(p[3]));
-        stop |= hi > C.phi_esc;
+        m |= __builtin_amdgcn_ballot_w64(hi > C.phi_esc);
     }
-    const uint64_t m = __builtin_amdgcn_ballot_w64(stop) & running;
+    m &= running;
     if (__builtin_expect(m != 0, 0)) {
         running &= ~m;
         if ((m >> __lane_id()) & 1u) {

@@ -315,7 +315,20 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
                         uint32_t j = lane_read(team.slot_lane, R.j) + (lane >> team.shift);
                         F4 z = normals4(j, team.noise, a.key0, a.key1, odd_mask);
                         F4 zn = team_fetch(team, z, 0);
-                        do {
+                        if (n_g == 8) {
+                            // as below, with every group's place in the batch known
+                            do {
+                                j += 8;
+                                const F4 zb = normals4(j, team.noise, a.key0, a.key1, odd_mask);
+#pragma unroll
+                                for (int g = 0; g < 8; ++g) {
+                                    const F4 zg = zn;
+                                    zn = g < 7 ? team_fetch8(team, z, g + 1) : team_fetch8(team, zb, 0);
+                                    group(zg);
+                                }
+                                z = zb;
+                            } while (running);
+                        } else do {
                             // a batch ahead: its draw fills the gaps in this one's chain of steps, and
                             // its first group is fetched before this one's last steps
                             j += static_cast<uint32_t>(n_g);

@@ -64,4 +64,10 @@ __device__ __forceinline__ F4 team_fetch(const Team &T, const F4 &z, int g) {
     return F4{lane_read(from, z.a), lane_read(from, z.b), lane_read(from, z.c), lane_read(from, z.d)};
 }
 
+// The same for G = 8, where the place in the batch is an offset of the exchange.
+__device__ __forceinline__ F4 team_fetch8(const Team &T, const F4 &z, int g) {
+    const int from = T.fetch0 + 32 * g;
+    return F4{lane_read(from, z.a), lane_read(from, z.b), lane_read(from, z.c), lane_read(from, z.d)};
+}
+
 }  // namespace fpt
