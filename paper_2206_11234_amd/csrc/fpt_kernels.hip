@@ -360,24 +360,23 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
             // multiple of the pass length here and the evaluation points of all lanes coincide.
             const int E = a.mlp_every;
             // a team's runs fit one block of 32 columns, slot c in lane c: half the network's work (16
-            // slots: a third); its batches of normals last over G / (E / 4) passes where G is larger
-            if (teamed && team_halves(team.shift, n_act, 8)) {
-                team_form(team, running, lt_mask, lane, noise, 8);
-                batch_at = 0;
-            }
-            const int g_mask = team.groups() - 1;
+            // and 8 slots: a third and a quarter); its batches of normals last over G / (E / 4) passes
+            // where G is larger
+            int g_mask = 0;
             auto team_next = [&](uint32_t q) {      // the normals of the q-th group from here
                 if (batch_at == 0) batch = team_draw(team, lane, R.j + q, a.key0, a.key1, odd_mask);
                 const F4 z = team_fetch(team, batch, batch_at);
                 batch_at = (batch_at + 1) & g_mask;
                 return z;
             };
-            auto network = [&](float phi_, float N_) {
+            auto network = [&](auto in_team, float phi_, float N_) {
                 const MlpIn x = mlp_input(mc, phi_, N_);
-                if (!teamed) return mc.out_scale * mlp_forward_lds(tile_lds, x);
-                const MlpIn xs{lane_read(team.slot_lane, x.lo), lane_read(team.slot_lane, x.hi)};
-                const float o = team.shift <= 4 ? mlp_block_lds<true>(tile_lds, xs, 0) : mlp_block_lds(tile_lds, xs, 0);
-                return mc.out_scale * lane_read(team.fetch0, o);
+                if constexpr (!decltype(in_team)::value) {
+                    return mc.out_scale * mlp_forward_lds(tile_lds, x);
+                } else {
+                    const MlpIn xs{lane_read(team.slot_lane, x.lo), lane_read(team.slot_lane, x.hi)};
+                    return mc.out_scale * lane_read(team.fetch0, mlp_team_lds(tile_lds, xs, team.shift));
+                }
             };
             // One evaluation per pass of E = 4, 8 or 16 steps.  The pass's normals do not depend
             // on the network, so they are drawn before it and the scheduler interleaves their
@@ -385,10 +384,10 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
             // counters k/4 .. k/4 + E/4 - 1, the ones the steps would draw; a lane whose run ends
             // early leaves the rest unused).  The evaluation runs at a raised wave priority, so
             // that it finishes sooner while the SIMD's other waves fill the gaps with steps.
-            auto pass = [&](auto nq_tag) {
+            auto pass = [&](auto in_team, auto nq_tag) {
                 constexpr int NQ = decltype(nq_tag)::value;
                 F4 zz[NQ];
-                if (teamed) {
+                if constexpr (decltype(in_team)::value) {
 #pragma unroll
                     for (int q = 0; q < NQ; ++q) zz[q] = team_next(q);
                 } else {
@@ -400,25 +399,21 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
                     }
                 }
                 __builtin_amdgcn_s_setprio(2);
-                const float r_mlp = network(R.phi, static_cast<float>(4u * R.j) * C.dN);
+                const float r_mlp = network(in_team, R.phi, static_cast<float>(4u * R.j) * C.dN);
                 __builtin_amdgcn_s_setprio(0);
 #pragma unroll
                 for (int q = 0; q < NQ; ++q) (void)group4<POT, BIAS>(C, j_cap, zz[q], r_mlp, R, running, F, far);
             };
-            if (E == 16) {
-                pass(std::integral_constant<int, 4>{});
-            } else if (E == 8) {
-                pass(std::integral_constant<int, 2>{});
-            } else if (E == 4) {
-                pass(std::integral_constant<int, 1>{});
-            } else {
-                // E = 1: an evaluation before every step
-                const F4 z = teamed ? team_next(0) : normals4(R.j, noise, a.key0, a.key1, odd_mask);
+            // E = 1: an evaluation before every step
+            auto pass1 = [&](auto in_team) {
+                F4 z;
+                if constexpr (decltype(in_team)::value) z = team_next(0);
+                else z = normals4(R.j, noise, a.key0, a.key1, odd_mask);
                 const float ns[4] = {z.a, z.b, z.c, z.d};
 #pragma unroll
                 for (int s = 0; s < 4; ++s) {
                     const uint32_t k0 = 4u * R.j + s;
-                    const float r_mlp = network(R.phi, static_cast<float>(k0) * C.dN);
+                    const float r_mlp = network(in_team, R.phi, static_cast<float>(k0) * C.dN);
                     float dlw, sxi;
                     (void)em_step<POT, BIAS>(C, R.phi, ns[s], r_mlp, dlw, sxi);
                     R.lw += static_cast<double>(dlw);
@@ -427,7 +422,28 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
                     running &= ~m;
                 }
                 R.j += 1;
-            }
+            };
+            // the passes until a run stops; a team's until its last one has, or half its slots are idle
+            auto passes = [&](auto one) {
+                if (teamed) {
+                    while (running) {
+                        team_form(team, running, lt_mask, lane, noise, 8);
+                        batch_at = 0;
+                        g_mask = team.groups() - 1;
+                        do one(std::true_type{});
+                        while (running && !team_halves(team.shift, __popcll(running), 8));
+                    }
+                } else {
+                    const uint64_t before = running;
+                    do one(std::false_type{});
+                    while (running == before);
+                }
+            };
+            using std::integral_constant;
+            if (E == 16) passes([&](auto in_team) { pass(in_team, integral_constant<int, 4>{}); });
+            else if (E == 8) passes([&](auto in_team) { pass(in_team, integral_constant<int, 2>{}); });
+            else if (E == 4) passes([&](auto in_team) { pass(in_team, integral_constant<int, 1>{}); });
+            else passes(pass1);
         }
 
         // ---- retire finished runs into the workgroup table: at once while their lanes can take new

@@ -254,9 +254,47 @@ __device__ __forceinline__ void act_to_operands16(const f32x16 &d0, const f32x16
     for (int s = 0; s < 8; ++s) b[4][s] = (h == 0 && s == 0) ? one : z;
 }
 
+// The same where only the first 8 columns are in use: each 8 lanes of a half wave take two of a
+// K-block's eight units (a shift by 8 lanes within the rows of 16, then the swap of rows), so that a
+// lane has 8 activations a layer.  A wave alone on its SIMD issues one instruction per 5 cycles, and
+// these are most of its evaluation (with loops of their own for the passes, 60 000 runs evaluated every
+// 4 steps: 105 ms, now 74).
+__device__ __forceinline__ void act_to_operands8(const f32x16 &d0, const f32x16 &d1, bf16x8 b[5]) {
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    const __bf16 z = __builtin_bit_cast(__bf16, (uint16_t)0);
+    const __bf16 one = (__bf16)1.0f;
+    constexpr int ROW_SHL8 = 0x108, ROW_SHR8 = 0x118, UPPER_8 = 0xC;     // DPP controls, bank mask
+    // x in lanes 0 .. 7 of each row of 16, y's lanes 0 .. 7 in its lanes 8 .. 15
+    auto both = [=](float x, float y) {
+        return static_cast<uint32_t>(
+            __builtin_amdgcn_update_dpp(__float_as_int(x), __float_as_int(y), ROW_SHR8, 0xF, UPPER_8, false));
+    };
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb) {
+        const f32x16 &d = kb < 2 ? d0 : d1;
+        const int v = 8 * (kb & 1);
+        bf16x2 p;
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const auto x = __builtin_amdgcn_permlane16_swap(both(d[v + s], d[v + 2 + s]), both(d[v + 4 + s], d[v + 6 + s]), false, false);
+            p[s] = (__bf16)tanh_act(__uint_as_float(x[0]));
+        }
+        const uint32_t q0 = __builtin_bit_cast(uint32_t, p);
+        const uint32_t q1 = static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(static_cast<int>(q0), ROW_SHL8, 0xF, 0xF, true));
+        const auto h0 = __builtin_amdgcn_permlane16_swap(q0, q0, false, false);
+        const auto h1 = __builtin_amdgcn_permlane16_swap(q1, q1, false, false);
+        const u32x4 w = {q0, q1, h0[1], h1[1]};
+        b[kb] = __builtin_bit_cast(bf16x8, w);
+    }
+    const int h = __lane_id() >> 5;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) b[4][s] = (h == 0 && s == 0) ? one : z;
+}
+
 // w3 . h2 + b3 of the 32 trajectories of N-block nb (the inputs of lanes 32 nb .. 32 nb + 31), in
-// lanes 0 .. 31 in order.  HALF: only the first 16 are wanted.
-template <bool HALF = false>
+// lanes 0 .. 31 in order.  COLS: only the first 16 or 8 are wanted.
+template <int COLS = 32>
 __device__ __forceinline__ float mlp_block_lds(const bf16x8 *L, const MlpIn &in, int nb) {
     const int l = __lane_id();
     const int h = l >> 5;
@@ -268,7 +306,8 @@ __device__ __forceinline__ float mlp_block_lds(const bf16x8 *L, const MlpIn &in,
     f32x16 d1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(L[1 * 64 + l], bx, zacc, 0, 0, 0);
     bf16x8 b[5];
     auto activate = [&]() {
-        if constexpr (HALF) act_to_operands16(d0, d1, b);
+        if constexpr (COLS == 8) act_to_operands8(d0, d1, b);
+        else if constexpr (COLS == 16) act_to_operands16(d0, d1, b);
         else act_to_operands(d0, d1, b);
     };
     activate();
@@ -288,6 +327,11 @@ __device__ __forceinline__ float mlp_block_lds(const bf16x8 *L, const MlpIn &in,
 #pragma unroll
     for (int kb = 0; kb < 5; ++kb) o = __builtin_amdgcn_mfma_f32_32x32x16_bf16(L[(12 + kb) * 64 + l], b[kb], o, 0, 0, 0);
     return o[0];
+}
+
+// The network's output for a team's slots, 32 of them or fewer.
+__device__ __forceinline__ float mlp_team_lds(const bf16x8 *L, const MlpIn &in, int shift) {
+    return shift <= 3 ? mlp_block_lds<8>(L, in, 0) : shift == 4 ? mlp_block_lds<16>(L, in, 0) : mlp_block_lds<32>(L, in, 0);
 }
 
 // The same for all 64 trajectories of the wave, one N-block after the other.

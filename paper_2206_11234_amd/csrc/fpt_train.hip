@@ -105,7 +105,7 @@ __global__ __launch_bounds__(256) void fpt_record_kernel(RecordArgs a) {
         const MlpIn x = mlp_input(mc, phi_, N_);
         if (!teamed) return mc.out_scale * mlp_forward_lds(tile_lds, x);
         const MlpIn xs{lane_read(team.slot_lane, x.lo), lane_read(team.slot_lane, x.hi)};
-        const float o = team.shift <= 4 ? mlp_block_lds<true>(tile_lds, xs, 0) : mlp_block_lds(tile_lds, xs, 0);
+        const float o = mlp_team_lds(tile_lds, xs, team.shift);
         return mc.out_scale * lane_read(team.fetch0, o);
     };
     const uint32_t odd_mask = normals_mask();
