@@ -359,6 +359,7 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
             // start at k = 0 and refill only between passes, so every lane of the wave is at a
             // multiple of the pass length here and the evaluation points of all lanes coincide.
             const int E = a.mlp_every;
+            const int n_q = E > 4 ? E >> 2 : 1;
             // a team's runs fit one block of 32 columns, slot c in lane c: half the network's work (16
             // and 8 slots: a third and a quarter); its batches of normals last over G / (E / 4) passes
             // where G is larger
@@ -375,7 +376,10 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
                     return mc.out_scale * mlp_forward_lds(tile_lds, x);
                 } else {
                     const MlpIn xs{lane_read(team.slot_lane, x.lo), lane_read(team.slot_lane, x.hi)};
-                    return mc.out_scale * lane_read(team.fetch0, mlp_team_lds(tile_lds, xs, team.shift));
+                    const float o = decltype(in_team)::value == 8 ? mlp_block_lds<8>(tile_lds, xs, 0)
+                                    : team.shift == 4             ? mlp_block_lds<16>(tile_lds, xs, 0)
+                                                                  : mlp_block_lds<32>(tile_lds, xs, 0);
+                    return mc.out_scale * lane_read(team.fetch0, o);
                 }
             };
             // One evaluation per pass of E = 4, 8 or 16 steps.  The pass's normals do not depend
@@ -387,7 +391,10 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
             auto pass = [&](auto in_team, auto nq_tag) {
                 constexpr int NQ = decltype(nq_tag)::value;
                 F4 zz[NQ];
-                if constexpr (decltype(in_team)::value) {
+                if constexpr (decltype(in_team)::value == 8) {
+#pragma unroll
+                    for (int q = 0; q < NQ; ++q) zz[q] = team_fetch8(team, batch, batch_at + q);
+                } else if constexpr (decltype(in_team)::value) {
 #pragma unroll
                     for (int q = 0; q < NQ; ++q) zz[q] = team_next(q);
                 } else {
@@ -407,7 +414,8 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
             // E = 1: an evaluation before every step
             auto pass1 = [&](auto in_team) {
                 F4 z;
-                if constexpr (decltype(in_team)::value) z = team_next(0);
+                if constexpr (decltype(in_team)::value == 8) z = team_fetch8(team, batch, batch_at);
+                else if constexpr (decltype(in_team)::value) z = team_next(0);
                 else z = normals4(R.j, noise, a.key0, a.key1, odd_mask);
                 const float ns[4] = {z.a, z.b, z.c, z.d};
 #pragma unroll
@@ -430,12 +438,21 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
                         team_form(team, running, lt_mask, lane, noise, 8);
                         batch_at = 0;
                         g_mask = team.groups() - 1;
-                        do one(std::true_type{});
-                        while (running && !team_halves(team.shift, __popcll(running), 8));
+                        if (g_mask == 7) {
+                            // a batch of normals serves 8 / NQ passes of NQ groups (E = 1: one each)
+                            while (running) {
+                                batch = team_draw(team, lane, R.j, a.key0, a.key1, odd_mask);
+#pragma unroll 1
+                                for (batch_at = 0; batch_at < 8 && running; batch_at += n_q) one(std::integral_constant<int, 8>{});
+                            }
+                        } else {
+                            do one(std::integral_constant<int, 1>{});
+                            while (running && !team_halves(team.shift, __popcll(running), 8));
+                        }
                     }
                 } else {
                     const uint64_t before = running;
-                    do one(std::false_type{});
+                    do one(std::integral_constant<int, 0>{});
                     while (running == before);
                 }
             };

@@ -310,22 +310,35 @@ __device__ __forceinline__ float mlp_block_lds(const bf16x8 *L, const MlpIn &in,
         else if constexpr (COLS == 16) act_to_operands16(d0, d1, b);
         else act_to_operands(d0, d1, b);
     };
+    // keep each layer's LDS reads next to their use: hoisted together they would hold all 17 tiles in
+    // registers again (with few columns, where a wave is often alone on its SIMD, a layer's first tiles
+    // are read before the activations that it needs)
+    constexpr int EARLY = COLS == 8 ? 2 : 0, EARLY3 = COLS == 8 ? 5 : 0;
+    bf16x8 t0[EARLY + 1], t1[EARLY + 1], t3[EARLY3 + 1];
+#pragma unroll
+    for (int kb = 0; kb < EARLY; ++kb) {
+        t0[kb] = L[(2 + kb) * 64 + l];
+        t1[kb] = L[(7 + kb) * 64 + l];
+    }
+    if constexpr (EARLY > 0) __builtin_amdgcn_sched_barrier(0);
     activate();
-    // keep each layer's LDS reads next to their use: hoisted together they would hold all
-    // 17 tiles in registers again
     __builtin_amdgcn_sched_barrier(0);
     d0 = zacc;
     d1 = zacc;
 #pragma unroll
     for (int kb = 0; kb < 5; ++kb) {
-        d0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(L[(2 + kb) * 64 + l], b[kb], d0, 0, 0, 0);
-        d1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(L[(7 + kb) * 64 + l], b[kb], d1, 0, 0, 0);
+        d0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kb < EARLY ? t0[kb] : L[(2 + kb) * 64 + l], b[kb], d0, 0, 0, 0);
+        d1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kb < EARLY ? t1[kb] : L[(7 + kb) * 64 + l], b[kb], d1, 0, 0, 0);
     }
+#pragma unroll
+    for (int kb = 0; kb < EARLY3; ++kb) t3[kb] = L[(12 + kb) * 64 + l];
+    if constexpr (EARLY3 > 0) __builtin_amdgcn_sched_barrier(0);
     activate();
     __builtin_amdgcn_sched_barrier(0);
     f32x16 o = zacc;
 #pragma unroll
-    for (int kb = 0; kb < 5; ++kb) o = __builtin_amdgcn_mfma_f32_32x32x16_bf16(L[(12 + kb) * 64 + l], b[kb], o, 0, 0, 0);
+    for (int kb = 0; kb < 5; ++kb)
+        o = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kb < EARLY3 ? t3[kb] : L[(12 + kb) * 64 + l], b[kb], o, 0, 0, 0);
     return o[0];
 }
 
