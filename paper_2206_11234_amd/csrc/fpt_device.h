@@ -121,30 +121,78 @@ __device__ __forceinline__ float sqrt_f32(float x) {
 //   - t = 2 s from 2 (f-1), T = t t = 4 s^2, and the series' coefficients carry the factors 1/4;
 //   - with L = ln u, x/2 = -L, the seed of x in terms of bits(L) is bits(0x9EF759DF - (bits(L) >> 1)),
 //     and x y = -2 (L y): the factor -2 goes to the caller's constant.
-__device__ __forceinline__ float radius_m2(uint32_t x) {
-    const float u = __uint_as_float(__builtin_amdgcn_alignbit(0x7Fu, x, 9)) + (0x1p-24f - 1.0f);
-    const uint32_t b = __float_as_uint(u);
-    const int ne = static_cast<int32_t>(0x3FB504F3u - b) >> 23;
-    const float f = __uint_as_float((static_cast<uint32_t>(ne) << 23) + b);
-    const float t = __builtin_fmaf(f, 2.0f, -2.0f) * recip_f32(f + 1.0f);
-    const float T = t * t;
-    float p = (1.0f / 9.0f) * 0x1p-8f;
-    p = __builtin_fmaf(p, T, (1.0f / 7.0f) * 0x1p-6f);
-    p = __builtin_fmaf(p, T, (1.0f / 5.0f) * 0x1p-4f);
-    p = __builtin_fmaf(p, T, (1.0f / 3.0f) * 0x1p-2f);
-    const float lf = __builtin_fmaf(t * T, p, t);
-    const float nf = static_cast<float>(ne);
-    const float ln2_hi = 0.693145751953125f;
-    const float ln2_lo = 1.42860682030941723212e-6f;
-    const float L = __builtin_fmaf(nf, -ln2_hi, __builtin_fmaf(nf, -ln2_lo, lf));
-    float y = __uint_as_float(0x9EF759DFu - (__float_as_uint(L) >> 1));
+//
+// Two words at a time, one operation of each in turn: a wave's instruction that needs the one before
+// it waits 9 cycles, an independent one 5, and the compiler, which takes every operation to be ready
+// at once, orders one chain after the other (a group of steps by the count 1840 cycles of a lone wave,
+// now 1450; 70 000 runs on the bump, two waves per SIMD, 51.8 ms, now 48.4; four waves per SIMD hide it).
+__device__ __forceinline__ void in_turn(float x, float y) { asm volatile("" ::"v"(x), "v"(y)); }
+__device__ __forceinline__ void in_turn(uint32_t x, uint32_t y) { asm volatile("" ::"v"(x), "v"(y)); }
+
+struct Pair {
+    float a, b;
+};
+
+template <typename F>
+__device__ __forceinline__ Pair each(const Pair &x, F f) {
+    Pair r{f(x.a), f(x.b)};
+    in_turn(r.a, r.b);
+    return r;
+}
+template <typename F>
+__device__ __forceinline__ Pair each(const Pair &x, const Pair &y, F f) {
+    Pair r{f(x.a, y.a), f(x.b, y.b)};
+    in_turn(r.a, r.b);
+    return r;
+}
+template <typename F>
+__device__ __forceinline__ Pair each(const Pair &x, const Pair &y, const Pair &z, F f) {
+    Pair r{f(x.a, y.a, z.a), f(x.b, y.b, z.b)};
+    in_turn(r.a, r.b);
+    return r;
+}
+
+__device__ __forceinline__ Pair radius_m2(uint32_t xa, uint32_t xb) {
+    auto u0 = [](uint32_t x) { return __uint_as_float(__builtin_amdgcn_alignbit(0x7Fu, x, 9)); };
+    const Pair m{u0(xa), u0(xb)};
+    const Pair u = each(m, [](float v) { return v + (0x1p-24f - 1.0f); });
+    uint32_t na = 0x3FB504F3u - __float_as_uint(u.a), nb = 0x3FB504F3u - __float_as_uint(u.b);
+    in_turn(na, nb);
+    const Pair nf{static_cast<float>(static_cast<int32_t>(na) >> 23), static_cast<float>(static_cast<int32_t>(nb) >> 23)};
+    na &= 0xFF800000u;
+    nb &= 0xFF800000u;
+    in_turn(na, nb);
+    na += __float_as_uint(u.a);
+    nb += __float_as_uint(u.b);
+    in_turn(na, nb);
+    const Pair f{__uint_as_float(na), __uint_as_float(nb)};
+    const Pair f2 = each(f, [](float v) { return __builtin_fmaf(v, 2.0f, -2.0f); });
+    const Pair d = each(f, [](float v) { return v + 1.0f; });
+    // 1/d as recip_f32
+    Pair y = each(d, [](float v) { return __uint_as_float(0x7EF311C3u - __float_as_uint(v)); });
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
-        const float yy = y * y;
-        const float e = __builtin_fmaf(L, yy, 0.5f);
-        y = __builtin_fmaf(y, e, y);
+        const Pair e = each(d, y, [](float v, float w) { return __builtin_fmaf(-v, w, 1.0f); });
+        y = each(y, e, [](float v, float w) { return __builtin_fmaf(v, w, v); });
     }
-    return L * y;
+    const Pair t = each(f2, y, [](float v, float w) { return v * w; });
+    const Pair T = each(t, [](float v) { return v * v; });
+    Pair p = each(T, [](float v) { return __builtin_fmaf((1.0f / 9.0f) * 0x1p-8f, v, (1.0f / 7.0f) * 0x1p-6f); });
+    p = each(p, T, [](float v, float w) { return __builtin_fmaf(v, w, (1.0f / 5.0f) * 0x1p-4f); });
+    p = each(p, T, [](float v, float w) { return __builtin_fmaf(v, w, (1.0f / 3.0f) * 0x1p-2f); });
+    const Pair tT = each(t, T, [](float v, float w) { return v * w; });
+    Pair L = each(tT, p, t, [](float v, float w, float z) { return __builtin_fmaf(v, w, z); });
+    L = each(nf, L, [](float v, float w) { return __builtin_fmaf(v, -1.42860682030941723212e-6f, w); });
+    L = each(nf, L, [](float v, float w) { return __builtin_fmaf(v, -0.693145751953125f, w); });
+    y = each(L, [](float v) { return __uint_as_float(__float_as_uint(v) >> 1); });
+    y = each(y, [](float v) { return __uint_as_float(0x9EF759DFu - __float_as_uint(v)); });
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        const Pair yy = each(y, [](float v) { return v * v; });
+        const Pair e = each(L, yy, [](float v, float w) { return __builtin_fmaf(v, w, 0.5f); });
+        y = each(y, e, [](float v, float w) { return __builtin_fmaf(v, w, v); });
+    }
+    return each(L, y, [](float v, float w) { return v * w; });
 }
 
 // cos(2 pi u), sin(2 pi u) for the uniform u = uniform24(x): nearest quarter q = rint(4u),
@@ -155,29 +203,34 @@ __device__ __forceinline__ float radius_m2(uint32_t x) {
 // (0.5 + (2a + 1) 2^-24) - 0.625 -- the same values as the float reduction of u, for every x.
 // odd_mask holds 0x3FFFFE (bits 1..21) in a register the compiler cannot see through, so that the
 // mask and the exponent go in with one v_and_or_b32.
-__device__ __forceinline__ void sincos2pi_bits(uint32_t x, uint32_t odd_mask, float &c_out, float &s_out) {
-    const uint32_t y = x + 0x20000000u;
-    const float r = __uint_as_float(((y >> 8) & odd_mask) | 0x3F000001u) - 0.625f;
-    const float r2 = r * r;
-    float ps = __builtin_fmaf(42.058693944897653145f, r2, -76.7058597530613858416f);
-    ps = __builtin_fmaf(ps, r2, 81.6052492760750542034f);
-    ps = __builtin_fmaf(ps, r2, -41.341702240399760234f);
-    ps = __builtin_fmaf(ps, r2, 6.28318530717958647692f);
-    const float sn = ps * r;
-    float pc = __builtin_fmaf(-26.4262567833743974529f, r2, 60.2446413718766603627f);
-    pc = __builtin_fmaf(pc, r2, -85.456817206693727736f);
-    pc = __builtin_fmaf(pc, r2, 64.939394022668291491f);
-    pc = __builtin_fmaf(pc, r2, -19.7392088021787172377f);
-    const float cs = __builtin_fmaf(pc, r2, 1.0f);
+__device__ __forceinline__ void sincos2pi_bits(uint32_t xa, uint32_t xb, uint32_t odd_mask, Pair &c_out, Pair &s_out) {
+    uint32_t ya = xa + 0x20000000u, yb = xb + 0x20000000u;
+    in_turn(ya, yb);
+    Pair r{__uint_as_float(((ya >> 8) & odd_mask) | 0x3F000001u), __uint_as_float(((yb >> 8) & odd_mask) | 0x3F000001u)};
+    in_turn(r.a, r.b);
+    r = each(r, [](float v) { return v - 0.625f; });
+    const Pair r2 = each(r, [](float v) { return v * v; });
+    Pair ps = each(r2, [](float v) { return __builtin_fmaf(42.058693944897653145f, v, -76.7058597530613858416f); });
+    Pair pc = each(r2, [](float v) { return __builtin_fmaf(-26.4262567833743974529f, v, 60.2446413718766603627f); });
+    ps = each(ps, r2, [](float v, float w) { return __builtin_fmaf(v, w, 81.6052492760750542034f); });
+    pc = each(pc, r2, [](float v, float w) { return __builtin_fmaf(v, w, -85.456817206693727736f); });
+    ps = each(ps, r2, [](float v, float w) { return __builtin_fmaf(v, w, -41.341702240399760234f); });
+    pc = each(pc, r2, [](float v, float w) { return __builtin_fmaf(v, w, 64.939394022668291491f); });
+    ps = each(ps, r2, [](float v, float w) { return __builtin_fmaf(v, w, 6.28318530717958647692f); });
+    pc = each(pc, r2, [](float v, float w) { return __builtin_fmaf(v, w, -19.7392088021787172377f); });
+    const Pair sn = each(ps, r, [](float v, float w) { return v * w; });
+    const Pair cs = each(pc, r2, [](float v, float w) { return __builtin_fmaf(v, w, 1.0f); });
     // quarter-turn rotation by q = y >> 30, branch-free: odd q (bit 30 of y: as a float, y's
     // magnitude is not below 2, infinities and NaN patterns included) swaps (cos, sin); cos changes
     // sign for q = 1, 2 (bit 31 of y + 2^30) and sin for q = 2, 3 (bit 31 of y); IEEE negation
     // is the sign bit
-    const bool even = __builtin_fabsf(__uint_as_float(y)) < 2.0f;
-    const float c0 = even ? cs : sn;
-    const float s0 = even ? sn : cs;
-    c_out = __uint_as_float(__builtin_amdgcn_bitop3_b32(x + 0x60000000u, __float_as_uint(c0), 0x80000000u, 0x6c));
-    s_out = __uint_as_float(__builtin_amdgcn_bitop3_b32(y, __float_as_uint(s0), 0x80000000u, 0x6c));
+    const bool even_a = __builtin_fabsf(__uint_as_float(ya)) < 2.0f, even_b = __builtin_fabsf(__uint_as_float(yb)) < 2.0f;
+    Pair c{even_a ? cs.a : sn.a, even_b ? cs.b : sn.b}, s{even_a ? sn.a : cs.a, even_b ? sn.b : cs.b};
+    auto turned = [](uint32_t q, float v) {
+        return __uint_as_float(__builtin_amdgcn_bitop3_b32(q, __float_as_uint(v), 0x80000000u, 0x6c));
+    };
+    c_out = Pair{turned(xa + 0x60000000u, c.a), turned(xb + 0x60000000u, c.b)};
+    s_out = Pair{turned(ya, s.a), turned(yb, s.b)};
 }
 
 // e^x for x <= 0 (x < -80 gives 0): n = rint(x / ln 2), r = x - n ln2 (two-part),
@@ -218,17 +271,10 @@ __device__ __forceinline__ F4 normals4(uint32_t j, const PhiloxRun &r, uint32_t 
     // hoists all round keys into scalar registers and spills them to vector lanes
     asm volatile("" : "+s"(key0), "+s"(key1));
     const U4 x = philox_block(j, r, key0, key1);
-    F4 out;
-    float c, s;
-    const float g0 = radius_m2(x.x);
-    sincos2pi_bits(x.y, odd_mask, c, s);
-    out.a = g0 * c;
-    out.b = g0 * s;
-    const float g1 = radius_m2(x.z);
-    sincos2pi_bits(x.w, odd_mask, c, s);
-    out.c = g1 * c;
-    out.d = g1 * s;
-    return out;
+    Pair c, s;
+    const Pair g = radius_m2(x.x, x.z);
+    sincos2pi_bits(x.y, x.w, odd_mask, c, s);
+    return F4{g.a * c.a, g.a * s.a, g.b * c.b, g.b * s.b};
 }
 
 // ---------------------------------------------------------------------------
