@@ -70,6 +70,12 @@ struct AdamArgs {
 };
 
 hipError_t launch_records(int pot, int bias, const RecordArgs &a, hipStream_t s);
+// Is a record's path index below n_paths and its step count 1 .. 16?
+__host__ __device__ inline bool train_record_ok(uint32_t pn, uint32_t n_paths) {
+    return (pn >> 5) < n_paths && (pn & 31u) >= 1 && (pn & 31u) <= 16;
+}
+
+hipError_t launch_train_check(const TrainArgs &a, unsigned long long *first_bad, hipStream_t s);
 hipError_t launch_train_loss(const TrainArgs &a, hipStream_t s);
 hipError_t launch_train_grad(const TrainArgs &a, hipStream_t s);
 hipError_t launch_adam(const AdamArgs &a, hipStream_t s);

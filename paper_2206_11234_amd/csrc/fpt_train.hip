@@ -261,6 +261,15 @@ __global__ __launch_bounds__(256) void fpt_train_path_kernel(TrainArgs a) {
     if (threadIdx.x == 0) a.lw_theta[i] = red[0];
 }
 
+// The lowest index of a record whose path index or step count is out of range (a host loop over 7.4e5
+// records took longer than the kernels that use them).
+__global__ __launch_bounds__(256) void fpt_train_check_kernel(const TrainRec *rec, uint64_t n_rec, uint32_t n_paths,
+                                                              unsigned long long *first_bad) {
+    const uint64_t e = static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (e >= n_rec) return;
+    if (!train_record_ok(rec[e].pn, n_paths)) atomicMin(first_bad, static_cast<unsigned long long>(e));
+}
+
 // ---------------------------------------------------------------------------
 // softmax over paths and log M2
 // ---------------------------------------------------------------------------
@@ -394,7 +403,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
             for (int u = 0; u < 64; ++u) o = __builtin_fmaf(th[NET_W3 + u], HB[lane * TS + u], o);
             if (valid) {
                 const double r = static_cast<double>(a.mc.out_scale * (o + th[NET_B3]));
-                const uint32_t path = R.pn >> 5;
+                // (a path index out of range is reported once the call's work is done)
+                const uint32_t path = min(R.pn >> 5, static_cast<uint32_t>(a.n_paths - 1));
                 const double n = static_cast<double>(R.pn & 31u);
                 g = static_cast<float>(a.c[path] * (r * n * dNd - static_cast<double>(R.H)) *
                                        static_cast<double>(a.mc.out_scale) * static_cast<double>(a.rec_weight));
@@ -567,6 +577,13 @@ hipError_t launch_records(int pot, int bias, const RecordArgs &a, hipStream_t s)
     case POT_FLAT: return launch_record_b<POT_FLAT>(bias, a, s);
     default: return hipErrorInvalidValue;
     }
+}
+
+hipError_t launch_train_check(const TrainArgs &a, unsigned long long *first_bad, hipStream_t s) {
+    if (a.n_rec == 0) return hipSuccess;
+    hipLaunchKernelGGL(fpt_train_check_kernel, dim3(static_cast<unsigned>((a.n_rec + 255) / 256)), dim3(256), 0, s, a.rec, a.n_rec,
+                       static_cast<uint32_t>(a.n_paths), first_bad);
+    return hipGetLastError();
 }
 
 hipError_t launch_train_loss(const TrainArgs &a, hipStream_t s) {

@@ -1284,49 +1284,73 @@ static int pyfpt_proposal_loss_grad_impl(const pyfpt_mlp *net, double target_N, 
         return fail(PYFPT_EINVAL, "need finite dN > 0, n_total > 0 and finite target_N");
     int rc = check_offsets(rec_off, n_paths, n_rec);
     if (rc) return rc;
-    for (uint64_t e = 0; e < n_rec; ++e) {
-        const uint32_t pn = rec[e].path_n;
-        if ((pn >> 5) >= static_cast<uint32_t>(n_paths) || (pn & 31u) < 1 || (pn & 31u) > 16)
-            return fail(PYFPT_EINVAL, "record %llu: path index or step count out of range",
-                        static_cast<unsigned long long>(e));
-    }
     hipStream_t stream = opt ? static_cast<hipStream_t>(opt->stream) : nullptr;
     const int n_part = backward_groups(n_rec);
-    DevBuf r, off, th, lwt, l0, c, ls, part, g, rr;
-    if ((rc = rr.alloc(4ull * n_rec)) || (rc = r.alloc(16ull * n_rec)) || (rc = off.alloc(8ull * (n_paths + 1))) || (rc = th.alloc(4ull * NET_N_PARAMS)) ||
-        (rc = lwt.alloc(8ull * n_paths)) || (rc = l0.alloc(8ull * n_paths)) ||
-        (rc = c.alloc(8ull * n_paths)) || (rc = ls.alloc(8)) ||
-        (rc = part.alloc(4ull * NET_N_PARAMS * static_cast<uint64_t>(n_part))) || (rc = g.alloc(8ull * NET_N_PARAMS)))
+    // one allocation for the call's device arrays
+    size_t top = 0;
+    auto take = [&](size_t bytes) {
+        const size_t at = top;
+        top = align_up(top + bytes, kAlign);
+        return at;
+    };
+    const size_t o_rec = take(16ull * n_rec), o_r = take(4ull * n_rec), o_off = take(8ull * (n_paths + 1)),
+                 o_lwt = take(8ull * n_paths), o_l0 = take(8ull * n_paths), o_c = take(8ull * n_paths),
+                 o_part = take(4ull * NET_N_PARAMS * static_cast<uint64_t>(n_part)), o_th = take(4ull * NET_N_PARAMS),
+                 o_ls = take(16 + 8ull * NET_N_PARAMS), o_g = o_ls + 16;
+    auto refuse = [](uint64_t e) {
+        return fail(PYFPT_EINVAL, "record %llu: path index or step count out of range", static_cast<unsigned long long>(e));
+    };
+    // up: the parameters, the loss and the first record out of range; down: the latter two and
+    // the gradient
+    std::vector<unsigned char> up(o_ls + 16 - o_th), down(16 + 8ull * NET_N_PARAMS);
+    DevBuf buf;
+    if ((rc = buf.alloc(top))) {
+        // no memory to check them in: a record out of range is refused as such all the same
+        for (uint64_t e = 0; e < n_rec; ++e)
+            if (!train_record_ok(rec[e].path_n, static_cast<uint32_t>(n_paths))) return refuse(e);
         return rc;
-    if (n_rec) HIP_TRY(hipMemcpyAsync(r.p, rec, 16ull * n_rec, hipMemcpyHostToDevice, stream), "upload records");
-    HIP_TRY(hipMemcpyAsync(off.p, rec_off, 8ull * (n_paths + 1), hipMemcpyHostToDevice, stream), "upload offsets");
-    HIP_TRY(hipMemcpyAsync(th.p, theta, 4ull * NET_N_PARAMS, hipMemcpyHostToDevice, stream), "upload theta");
-    HIP_TRY(hipMemcpyAsync(l0.p, lw0, 8ull * n_paths, hipMemcpyHostToDevice, stream), "upload lw0");
+    }
+    unsigned char *D = buf.as<unsigned char>();
+    const uint64_t none[2] = {0, UINT64_MAX};
+    std::memcpy(up.data(), theta, 4ull * NET_N_PARAMS);
+    std::memcpy(up.data() + (o_ls - o_th), none, 16);
+    HIP_TRY(hipMemcpyAsync(D + o_th, up.data(), up.size(), hipMemcpyHostToDevice, stream), "upload theta");
+    if (n_rec) HIP_TRY(hipMemcpyAsync(D + o_rec, rec, 16ull * n_rec, hipMemcpyHostToDevice, stream), "upload records");
+    HIP_TRY(hipMemcpyAsync(D + o_off, rec_off, 8ull * (n_paths + 1), hipMemcpyHostToDevice, stream), "upload offsets");
+    HIP_TRY(hipMemcpyAsync(D + o_l0, lw0, 8ull * n_paths, hipMemcpyHostToDevice, stream), "upload lw0");
     TrainArgs ta{};
-    ta.rec = r.as<TrainRec>();
+    ta.rec = reinterpret_cast<TrainRec *>(D + o_rec);
     ta.n_rec = n_rec;
-    ta.rec_off = off.as<uint64_t>();
+    ta.rec_off = reinterpret_cast<uint64_t *>(D + o_off);
     ta.n_paths = n_paths;
     ta.n_part = n_part;
     ta.objective = objective;
     ta.temper = static_cast<float>(temper);
     ta.rec_weight = static_cast<float>(rec_weight);
-    ta.theta = th.as<float>();
+    ta.theta = reinterpret_cast<float *>(D + o_th);
     ta.mc = mlp_consts(*net, target_N);
     ta.dN = static_cast<float>(dN);
-    ta.r = rr.as<float>();
-    ta.lw_theta = lwt.as<double>();
-    ta.lw0 = l0.as<double>();
+    ta.r = reinterpret_cast<float *>(D + o_r);
+    ta.lw_theta = reinterpret_cast<double *>(D + o_lwt);
+    ta.lw0 = reinterpret_cast<double *>(D + o_l0);
     ta.n_total = n_total;
-    ta.c = c.as<double>();
-    ta.loss = ls.as<double>();
-    ta.part = part.as<float>();
-    ta.grad = g.as<double>();
+    ta.c = reinterpret_cast<double *>(D + o_c);
+    ta.loss = reinterpret_cast<double *>(D + o_ls);
+    ta.part = reinterpret_cast<float *>(D + o_part);
+    ta.grad = reinterpret_cast<double *>(D + o_g);
+    HIP_TRY(launch_train_check(ta, reinterpret_cast<unsigned long long *>(D + o_ls + 8), stream), "launch record check");
     HIP_TRY(launch_train_loss(ta, stream), "launch loss kernels");
     HIP_TRY(launch_train_grad(ta, stream), "launch gradient kernels");
-    HIP_TRY(hipMemcpyAsync(loss, ls.p, 8, hipMemcpyDeviceToHost, stream), "download loss");
-    HIP_TRY(hipMemcpyAsync(grad, g.p, 8ull * NET_N_PARAMS, hipMemcpyDeviceToHost, stream), "download grad");
-    HIP_TRY(hipMemcpyAsync(lw_theta, lwt.p, 8ull * n_paths, hipMemcpyDeviceToHost, stream), "download lw_theta");
+    // the records were checked on the device, beside the work (which reads no array through them
+    // out of range): nothing is given back where one is out of range
+    HIP_TRY(hipMemcpyAsync(down.data(), D + o_ls, down.size(), hipMemcpyDeviceToHost, stream), "download loss and grad");
+    HIP_TRY(hipStreamSynchronize(stream), "hipStreamSynchronize");
+    uint64_t bad;
+    std::memcpy(&bad, down.data() + 8, 8);
+    if (bad != UINT64_MAX) return refuse(bad);
+    std::memcpy(loss, down.data(), 8);
+    std::memcpy(grad, down.data() + 16, 8ull * NET_N_PARAMS);
+    HIP_TRY(hipMemcpyAsync(lw_theta, D + o_lwt, 8ull * n_paths, hipMemcpyDeviceToHost, stream), "download lw_theta");
     HIP_TRY(hipStreamSynchronize(stream), "hipStreamSynchronize");
     return PYFPT_OK;
 }
