@@ -33,6 +33,8 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 
+#include <algorithm>
+
 #include "fpt_kernels.h"
 #include "fpt_team.h"
 #include "fpt_train.h"
@@ -199,43 +201,85 @@ __device__ __forceinline__ void net_layer1(const float *__restrict__ th, const f
 // ---------------------------------------------------------------------------
 // forward: r per record, ln w_theta per path
 // ---------------------------------------------------------------------------
-// Bound by vector arithmetic: 4500 fused multiply-adds and 128 activations per record.  Records are
-// taken in order, EVAL_PER to a lane, so that every lane is busy whatever the paths' lengths and each
-// scalar load of a weight serves two multiply-adds: with one workgroup per path and one record per
-// lane, 7.4e5 records of 700 paths took 190 us, now 126 and 5 us.
-constexpr int EVAL_PER = 2;
+// Bound by arithmetic: 4500 fused multiply-adds and 128 activations per record.  A wave takes 64 records
+// in order, whatever their paths, and keeps h2 = W2 h1 on the matrix cores (M = unit, N = record,
+// K = input), W2 in registers for the whole kernel: one lane computes both units of a k pair for its
+// record, and a swap of half waves turns them into the operands of records 0 .. 31 and 32 .. 63; the
+// same swap of the two results gives each lane its record's units back, so nothing goes through LDS.
+// The binary32 product adds k in ascending order with one rounding each, as a chain of fma does, so r
+// is the same bit for bit.  7.4e5 records of 700 paths: one workgroup per path 190 us; two records per
+// lane with W2 (more than the scalar cache) read by scalar loads 126 us; now 87 us.
+constexpr int EVAL_WG_PER_CU = 3;
+typedef float f32x16v __attribute__((ext_vector_type(16)));
 
-__global__ __launch_bounds__(256) void fpt_train_eval_kernel(TrainArgs a, const float *__restrict__ th0) {
-    const uint64_t e0 = static_cast<uint64_t>(blockIdx.x) * (256 * EVAL_PER) + threadIdx.x;
-    const float *th = th0 + opaque_zero();
-    float h1[EVAL_PER][64], o[EVAL_PER];
+struct Half2 {
+    float lo, hi;
+};
+// lo = the low half waves of x and y, hi = their high halves
+__device__ __forceinline__ Half2 swap_halves(float x, float y) {
+    const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    return {__uint_as_float(p[0]), __uint_as_float(p[1])};
+}
+
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(EVAL_WG_PER_CU, EVAL_WG_PER_CU))) void
+fpt_train_eval_kernel(TrainArgs a, const float *__restrict__ th0) {
+    const int lane = threadIdx.x & 63;
+    const int col = lane & 31, kh = lane >> 5;
+    // A fragments of W2: row = unit 32 ub + col, k = 2 ks + kh
+    float W[2][32];
 #pragma unroll
-    for (int i = 0; i < EVAL_PER; ++i) {
-        const uint64_t e = e0 + 256 * i;
+    for (int ub = 0; ub < 2; ++ub)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const float4 v = *reinterpret_cast<const float4 *>(th0 + NET_W2 + 64 * (32 * ub + col) + 8 * j + 4 * kh);
+            const Half2 p = swap_halves(v.x, v.y), q = swap_halves(v.z, v.w);
+            W[ub][4 * j + 0] = p.lo;
+            W[ub][4 * j + 1] = q.lo;
+            W[ub][4 * j + 2] = p.hi;
+            W[ub][4 * j + 3] = q.hi;
+        }
+    const uint64_t n_tiles = (a.n_rec + 63) / 64;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
+    for (uint64_t tile = wave; tile < n_tiles; tile += 4 * gridDim.x) {
+        const float *th = th0 + opaque_zero();
+        const uint64_t e = tile * 64 + lane;
         const TrainRec R = a.rec[e < a.n_rec ? e : a.n_rec - 1];
         float x[3];
         net_inputs(a.mc, R.phi, R.k, a.dN, x);
-        net_layer1(th, x, h1[i]);
-        o[i] = 0.0f;
-    }
-#pragma unroll 1
-    for (int u = 0; u < 64; ++u) {
-        float s[EVAL_PER];
+        f32x16v z[2][2];
 #pragma unroll
-        for (int i = 0; i < EVAL_PER; ++i) s[i] = th[NET_B2 + u];
+        for (int ub = 0; ub < 2; ++ub)
 #pragma unroll
-        for (int v = 0; v < 64; ++v) {
-            const float w = th[NET_W2 + 64 * u + v];
+            for (int g = 0; g < 4; ++g) {
+                const float4 b = *reinterpret_cast<const float4 *>(th + NET_B2 + 32 * ub + 8 * g + 4 * kh);
+                z[ub][0][4 * g + 0] = z[ub][1][4 * g + 0] = b.x;
+                z[ub][0][4 * g + 1] = z[ub][1][4 * g + 1] = b.y;
+                z[ub][0][4 * g + 2] = z[ub][1][4 * g + 2] = b.z;
+                z[ub][0][4 * g + 3] = z[ub][1][4 * g + 3] = b.w;
+            }
 #pragma unroll
-            for (int i = 0; i < EVAL_PER; ++i) s[i] = __builtin_fmaf(w, h1[i][v], s[i]);
+        for (int ks = 0; ks < 32; ++ks) {
+            const Half2 h = swap_halves(net_unit1(th, 2 * ks, x), net_unit1(th, 2 * ks + 1, x));
+#pragma unroll
+            for (int ub = 0; ub < 2; ++ub) {
+                z[ub][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(W[ub][ks], h.lo, z[ub][0], 0, 0, 0);
+                z[ub][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(W[ub][ks], h.hi, z[ub][1], 0, 0, 0);
+            }
         }
+        float o = 0.0f;
 #pragma unroll
-        for (int i = 0; i < EVAL_PER; ++i) o[i] = __builtin_fmaf(th[NET_W3 + u], tanh_hw(s[i]), o[i]);
-    }
+        for (int ub = 0; ub < 2; ++ub)
 #pragma unroll
-    for (int i = 0; i < EVAL_PER; ++i) {
-        const uint64_t e = e0 + 256 * i;
-        if (e < a.n_rec) a.r[e] = a.mc.out_scale * (o[i] + th0[NET_B3]);
+            for (int g = 0; g < 4; ++g) {
+                Half2 h[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) h[q] = swap_halves(z[ub][0][4 * g + q], z[ub][1][4 * g + q]);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) o = __builtin_fmaf(th[NET_W3 + 32 * ub + 8 * g + q], tanh_hw(h[q].lo), o);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) o = __builtin_fmaf(th[NET_W3 + 32 * ub + 8 * g + 4 + q], tanh_hw(h[q].hi), o);
+            }
+        if (e < a.n_rec) a.r[e] = a.mc.out_scale * (o + th[NET_B3]);
     }
 }
 
@@ -317,8 +361,6 @@ __global__ __launch_bounds__(1024) void fpt_train_softmax_kernel(TrainArgs a) {
 // backward: four waves per workgroup, 64 records per tile
 // ---------------------------------------------------------------------------
 constexpr int TS = 65;  // padded row stride of the [sample][unit] LDS tiles
-
-typedef float f32x16v __attribute__((ext_vector_type(16)));
 
 // The three 64x64x64 contractions of a tile run on v_mfma_f32_32x32x2f32 (binary32 products and
 // sums, like the rest of the training network).  Operand layout of that instruction, per lane l
@@ -590,9 +632,8 @@ hipError_t launch_train_loss(const TrainArgs &a, hipStream_t s) {
     if (a.n_paths <= 0) return hipErrorInvalidValue;
     hipError_t e = hipSuccess;
     if (a.n_rec > 0) {
-        const uint64_t per_wg = 256 * EVAL_PER;
-        hipLaunchKernelGGL(fpt_train_eval_kernel, dim3(static_cast<unsigned>((a.n_rec + per_wg - 1) / per_wg)), dim3(256), 0, s, a,
-                           a.theta);
+        const uint64_t wgs = std::min<uint64_t>((a.n_rec + 255) / 256, EVAL_WG_PER_CU * 256);
+        hipLaunchKernelGGL(fpt_train_eval_kernel, dim3(static_cast<unsigned>(wgs)), dim3(256), 0, s, a, a.theta);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
