@@ -479,7 +479,8 @@ __device__ __forceinline__ Steps4 steps4(const StepConsts &C, const F4 &z, float
 //
 // Bump potential: `far` tells whether the wave's runs were all far from the bump in the last group;
 // then this one is taken without it (65 instructions a step instead of 108), and again with it if a
-// run came near.
+// run came near.  The rule is the wave's, as a divergent step would issue both; it pays where the
+// wave's runs move together (70 000 runs that all fit the launch: 60.3 ms, now 52.6).
 template <int POT, int BIAS, int P = 0, int WALL = WALL_ANY>
 __device__ __forceinline__ uint64_t group4(const StepConsts &C, uint32_t j_cap, const F4 &z, float r_net, RunState &R,
                                            uint64_t &running, Stopped *F, bool &far, float *H = nullptr) {

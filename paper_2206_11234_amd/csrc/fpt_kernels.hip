@@ -171,10 +171,13 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
     int batch_at = 0;           // and the group of it that comes next
     // Power-law bias: the exponent where the wave's instances share one of 1 .. 4, whose group is
     // compiled for it; a loop over an exponent per lane costs a step 24 instructions and its overlap
-    // with the next (2e5 runs with p = 3: 5.2 against 4.6 ms).
+    // with the next (2e5 runs with p = 3: 5.2 against 4.6 ms, in the loop of that time; now 4.1).
     int p_wave = 0;
     // Whether the wave's runs all have a wall, all have none, or differ: two instructions a step
-    // without the reflection, three a group without the escape test.
+    // without the reflection, three a group without the escape test.  Both choices are made where a
+    // run has stopped or been handed out, and the groups between follow each other in a loop of one
+    // branch: with the choice, the refill's tests and the teams' around each group, six instances of
+    // 1e5 runs took 186 ms (chosen by group, 214), now 166.
     int walls = WALL_ANY;
     bool far = false;           // bump potential: see group4
     auto specialised = [&](auto f) {
@@ -307,7 +310,9 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
         // ---- a pass: groups of four Euler-Maruyama steps, each from one Philox call
         if constexpr (BIAS != BIAS_MLP) {
             if (teamed) {
-                // to the end of the wave's last run: nothing is refilled or retired before it
+                // To the end of the wave's last run: nothing is refilled or retired before it.  A wave
+                // alone on its SIMD issues an instruction per 5 cycles, so the count is the time: 42 a step
+                // in the loop over any G, 30 in the stretch for G = 8 (500 direct runs: 518 and 457 us).
                 specialised([&](auto group) {
                     while (running) {
                         team_form(team, running, lt_mask, lane, noise, 8);
@@ -316,7 +321,7 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
                         F4 z = normals4(j, team.noise, a.key0, a.key1, odd_mask);
                         F4 zn = team_fetch(team, z, 0);
                         if (n_g == 8) {
-                            // as below, with every group's place in the batch known
+                            // as below, with every group's place in the batch a constant
                             do {
                                 j += 8;
                                 const F4 zb = normals4(j, team.noise, a.key0, a.key1, odd_mask);
@@ -360,9 +365,10 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
             // multiple of the pass length here and the evaluation points of all lanes coincide.
             const int E = a.mlp_every;
             const int n_q = E > 4 ? E >> 2 : 1;
-            // a team's runs fit one block of 32 columns, slot c in lane c: half the network's work (16
+            // A team's runs fit one block of 32 columns, slot c in lane c: half the network's work (16
             // and 8 slots: a third and a quarter); its batches of normals last over G / (E / 4) passes
-            // where G is larger
+            // where G is larger.  A lone wave of 8 runs takes 321 cycles a step at E = 16 and 722 at E = 4;
+            // asking before each group whether a batch is due, 360 and 856.
             int g_mask = 0;
             auto team_next = [&](uint32_t q) {      // the normals of the q-th group from here
                 if (batch_at == 0) batch = team_draw(team, lane, R.j + q, a.key0, a.key1, odd_mask);

@@ -511,8 +511,8 @@ int resident_per_cu(const Prepared &P, const LaunchCfg &c) {
 // (see Team), one wave issues an instruction per 5 cycles and W >= 2 waves one per 2.4 together.
 // The runs per wave are those with the least W (step + draw / G), W = waves per SIMD, but no less
 // than the chain of dependent operations of one step (about 130 cycles).  500 direct runs of 5.8e3
-// steps took 1.18 ms at 64 runs per wave (whole call) and 0.65 ms at 8; 2e5 diffusion-dominated runs,
-// whose last ones end on teams, 14.7 and 8.7 ms.
+// steps took 1.18 ms at 64 runs per wave (whole call) and 0.65 ms at 8 (now 0.46); 2e5
+// diffusion-dominated runs, whose last ones end on teams, 14.7 and 8.7 ms (now 7.2).
 Shape launch_shape(const Device &d, const Prepared &P, const LaunchCfg &c) {
     Shape s;
     s.block = c.block;
@@ -551,9 +551,9 @@ Shape launch_shape(const Device &d, const Prepared &P, const LaunchCfg &c) {
     // The queue is ordered by expected length, and the first ids of a batch are its longest runs.  As
     // long as they fill no more than half of every wave's lanes, one to each wave in turn leaves all
     // waves with few long runs at the end, which the idle lanes then help (64 instances of 2000 runs:
-    // 137 ms spread, 181 ms wave by wave); where they fill more, wave by wave lets the waves of
-    // shorter runs end and leave their SIMDs to the others (six instances of 1e5 runs, 3e5 of them
-    // capped: 193 ms spread, 180 ms wave by wave).
+    // 137 ms spread, 181 ms wave by wave, when the rule was taken; now 110); where they fill more, wave
+    // by wave lets the waves of shorter runs end and leave their SIMDs to the others (six instances of
+    // 1e5 runs, 2e5 of them capped: 193 ms spread, 180 ms wave by wave; now 166).
     const uint64_t lanes = static_cast<uint64_t>(s.n_wg) * s.block;
     uint64_t longest = 0;
     for (uint32_t i : P.order)
