@@ -24,9 +24,9 @@ if ROOT not in sys.path:
 
 # VALU issue peak of MI355X: 256 CUs x 4 SIMDs x 32 lanes per clock x 2.4 GHz = 7.86e13
 # lane-ops/s, i.e. the 157.3 TFLOP/s fp32 vector peak divided by 2 flops per FMA.  In the step
-# kernel every VALU instruction kind it uses issues at that rate: its counters show 70.4 VALU
-# instructions per wave-step in 171.4 SIMD-cycles, 29.5 of them fma, 32x32 integer multiplies,
-# f64 adds and conversions; at two issue slots for those the wave-step would need 199.8 cycles.
+# kernel every VALU instruction kind it uses issues at about that rate: its counters show 61.9 VALU
+# instructions per wave-step in 142.9 SIMD-cycles, 30.4 of them fma, 32x32 integer multiplies,
+# f64 adds and conversions; at two issue slots for those the wave-step would need 184.6 cycles.
 PEAK_LANE_OPS = 256 * 4 * 32 * 2.4e9
 # MI355X binary32 vector peak (packed FMA on every lane), for the FLOP reading of the roofline
 PEAK_FP32_FLOPS = 157.3e12
@@ -35,14 +35,15 @@ PEAK_FP32_FLOPS = 157.3e12
 # and the count of the compiled kernel from its counters (SQ_INSTS_VALU_FLOPS_FP32 per
 # trajectory-step), profiles/fpt_step_kernel_c2_sweep_valu_counters.md
 FLOP_PER_STEP_ALGORITHMIC = 50.0
-FLOP_PER_STEP_COUNTED = 61.7
+FLOP_PER_STEP_COUNTED = 60.6
 # Algorithmic lane operations per trajectory-step of the quadratic, noise-scaled path: the VALU
-# instructions of the compiled four-step pass of fpt_step_kernel<0,1,false>, loop control and
-# retirement excluded (fma, three-input xor and 32x32->64 multiply one each):
-#   Philox 40/4 (20 v_mad_u64_u32 and 20 v_bitop3_b32: ten rounds per 4 steps)
-#   radius uniforms and the two Box-Muller pairs 119/4 (own log, sqrt and sincos)
-#   the step 114/4 (reciprocal, drift/noise/bias, phi update, weight, wall, k, stopping tests)
-OPS_PER_STEP = (40 + 119 + 114) / 4
+# instructions of the compiled group of four steps of fpt_step_kernel<0,1,false>, retirement excluded
+# (fma, three-input xor and 32x32->64 multiply one each), in its variant for runs with a wall (94 % of
+# the steps; without one five fewer):
+#   Philox 37/4 (18 v_mad_u64_u32 and 19 xors: what depends on the run alone is kept from its start)
+#   radius uniforms and the two Box-Muller pairs 118/4 (own log, sqrt and sincos)
+#   the step 87/4 (reciprocal, drift/noise/bias, phi update, weight, wall; one stopping test a group)
+OPS_PER_STEP = (37 + 118 + 87) / 4
 # HBM bytes per launch of the step kernel on this workload: rocprofv3 FETCH_SIZE x 2 + WRITE_SIZE x 1
 # (factors read off a plain 1 GiB copy, `--copy-calibration`), summaries under profiles/.
 # Reset to None whenever the step kernel changes until the counters are taken again.
@@ -50,7 +51,7 @@ OPS_PER_STEP = (40 + 119 + 114) / 4
 # + round) and every selection pilot seed (those + 2^30 + c), so the evaluated proposal does not
 # depend on the evaluation's noise.
 EVAL_SEED = 99991
-TRAFFIC = (582272.875 * 1.99994 + 2624860.21875 * 1.0) * 1024
+TRAFFIC = (519111.375 * 1.99994 + 2879290.6875 * 1.0) * 1024
 
 
 def parse():

@@ -218,7 +218,10 @@ typedef struct pyfpt_options {
     int32_t block;                   /* threads per workgroup (64..1024, multiple of 64; <= 256 for the
                                         learned bias); 0 = autotune */
     int32_t chunk;                   /* queue claim multiplier per wave (>= 1); 0 = autotune */
-    int32_t wg_per_cu;               /* persistent workgroups per CU; 0 = autotune */
+    int32_t wg_per_cu;               /* persistent workgroups per CU; 0 = autotune.  Autotuning takes place
+                                        where there are more runs than the largest shape has lanes; a
+                                        launch with fewer runs than its shape's lanes takes fewer or
+                                        smaller workgroups than block and wg_per_cu say */
     int32_t use_graph;               /* capture the launch sequence in a hipGraph and replay it */
     void *workspace;                 /* device scratch; NULL = library-managed */
     size_t workspace_bytes;
