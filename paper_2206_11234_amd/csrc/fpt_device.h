@@ -2,7 +2,7 @@
 // biased slow-roll Langevin equation, for gfx950.
 //
 // Method: arXiv:2206.11234, Sec. 2.1-2.3.  Every binary32 operation below is
-// part of the step semantics shared with the CPU checker: the step count of a
+// part of the step semantics shared with the CPU oracle: the step count of a
 // run is decided in binary32, so the order of operations and the places where
 // fma is used are fixed (the library is built with -ffp-contract=off and no
 // fast-math).  Reciprocals and square roots are fma-only Newton sequences:
@@ -107,7 +107,7 @@ __device__ __forceinline__ float sqrt_f32(float x) {
 // The Box-Muller radius of a Philox word x, times -1/2: g with rho = sqrt(-2 ln u) = -2 g for
 // u = (2 (x >> 9) + 1) 2^-24, an odd multiple of 2^-24 in (0, 1).
 //
-// The definition (the checker's operations): u exact; ln u = e ln2_hi + (e ln2_lo + ln f) for
+// The definition (the oracle's operations): u exact; ln u = e ln2_hi + (e ln2_lo + ln f) for
 // u = 2^e f, f in (sqrt(1/2), sqrt 2] (bit patterns (0x3F3504F3, 0x3FB504F3]), ln f = 2 atanh(s),
 // s = (f-1)/(f+1), as the odd series to s^9; rho = x y with x = -2 ln u and y the reciprocal square
 // root of x from three Newton steps y <- fma(y, fma(-x/2, y*y, 1/2), y) on the seed
