@@ -75,10 +75,11 @@ __global__ __launch_bounds__(256) void fpt_record_kernel(RecordArgs a) {
     uint64_t running = __ballot(have);
     float H = 0.0f, phi_e = R.phi;
     uint32_t k_e = 0;           // first step of the record's group
-    uint32_t grp = 0;           // its index
+    uint32_t skip = 0;          // groups until the next that is kept
     uint64_t n_rec = 0;
-    auto record = [&](uint32_t k_end) {      // the group k_e .. k_end - 1 is complete
-        if (grp % stride == 0) {
+    auto record = [&](uint32_t k_end) __attribute__((always_inline)) {      // the group k_e .. k_end - 1 is complete
+        if (skip == 0) {
+            skip = stride;
             if (n_rec < cap) {
                 TrainRec rec;
                 rec.phi = phi_e;
@@ -89,7 +90,7 @@ __global__ __launch_bounds__(256) void fpt_record_kernel(RecordArgs a) {
             }
             n_rec += 1;
         }
-        grp += 1;
+        skip -= 1;
         k_e = k_end;
         phi_e = R.phi;
         H = 0.0f;
@@ -103,7 +104,7 @@ __global__ __launch_bounds__(256) void fpt_record_kernel(RecordArgs a) {
     if (teamed) {
         team_form(team, running, (lane == 0) ? 0ull : (~0ull >> (64 - lane)), lane, noise, 8);
     }
-    auto network = [&](float phi_, float N_) {
+    auto network = [&](float phi_, float N_) __attribute__((always_inline)) {
         const MlpIn x = mlp_input(mc, phi_, N_);
         if (!teamed) return mc.out_scale * mlp_forward_lds(tile_lds, x);
         const MlpIn xs{lane_read(team.slot_lane, x.lo), lane_read(team.slot_lane, x.hi)};
@@ -115,6 +116,43 @@ __global__ __launch_bounds__(256) void fpt_record_kernel(RecordArgs a) {
     F4 batch{};
     float r_mlp = 0.0f;
     const int batch_mask = team.groups() - 1;
+    // the running lanes are all in group q; a record is due for all of them or for those that stopped
+    auto step_group = [&](const F4 &z, uint32_t q) __attribute__((always_inline)) {
+        const uint64_t before = running;
+        const uint64_t m = group4<POT, BIAS>(C, j_cap, z, r_mlp, R, running, &F, far, &H);
+        if (m || ((4u * q + 4u) & (group - 1)) == 0) {
+            const bool stopped = (m >> lane) & 1u;
+            const uint32_t k_end = stopped ? F.k : 4u * R.j;
+            if (((before >> lane) & 1u) && ((k_end & (group - 1)) == 0 || stopped)) record(k_end);
+        }
+    };
+    // With 8 paths or fewer a wave, a batch of normals is drawn for the passes that use it and a pass's
+    // normals are fetched before its evaluation: a wave is alone on its SIMD here, and asking before
+    // each group whether a batch, an evaluation or a fetch is due and waiting for the latter took a
+    // fifth of its time (600 paths of 6e4 steps, evaluated every 16: 12.8 ms, now 10.5).
+    if (teamed && batch_mask == 7 && E != 1 && group >= 4) {
+        uint32_t q = 0;
+        auto passes = [&](auto n_groups) {
+            constexpr int NQ = decltype(n_groups)::value;
+            while (running) {
+                batch = team_draw(team, lane, R.j, a.key0, a.key1, odd_mask);
+#pragma unroll 1
+                for (int at = 0; at < 8 && running; at += NQ) {
+                    F4 zz[NQ];
+#pragma unroll
+                    for (int i = 0; i < NQ; ++i) zz[i] = team_fetch8(team, batch, at + i);
+                    if constexpr (BIAS == BIAS_MLP) r_mlp = network(R.phi, static_cast<float>(4u * R.j) * C.dN);
+#pragma unroll
+                    for (int i = 0; i < NQ; ++i) step_group(zz[i], q + i);
+                    q += NQ;
+                }
+            }
+        };
+        using std::integral_constant;
+        if (BIAS != BIAS_MLP || n_q == 4) passes(integral_constant<int, 4>{});
+        else if (n_q == 2) passes(integral_constant<int, 2>{});
+        else passes(integral_constant<int, 1>{});
+    }
     for (int q = 0; running; ++q) {
         // q-th group of four steps; the lanes still running are all in their group q
         if constexpr (BIAS == BIAS_MLP) {
@@ -148,14 +186,7 @@ __global__ __launch_bounds__(256) void fpt_record_kernel(RecordArgs a) {
             }
             R.j += 1;
         } else {
-            const uint64_t before = running;
-            const uint64_t m = group4<POT, BIAS>(C, j_cap, z, r_mlp, R, running, &F, far, &H);
-            // every running lane is at the same step: a record is due for all or for those that stopped
-            if (m || ((4u * q + 4u) & (group - 1)) == 0) {
-                const bool stopped = (m >> lane) & 1u;
-                const uint32_t k_end = stopped ? F.k : 4u * R.j;
-                if (((before >> lane) & 1u) && ((k_end & (group - 1)) == 0 || stopped)) record(k_end);
-            }
+            step_group(z, q);
         }
     }
     if (have) {

@@ -91,7 +91,8 @@ def test_learned_runs_do_not_depend_on_the_launch(fpt, every):
 
 
 @pytest.mark.parametrize("n_paths", [1, 8, 9, 63, 65, 300])
-@pytest.mark.parametrize("proposal,group", [("fixed", 1), ("fixed", 4), ("network", 1), ("network", 4), ("network", 16)])
+@pytest.mark.parametrize("proposal,group", [("fixed", 1), ("fixed", 4), ("fixed", 16), ("network", 1), ("network", 4),
+                                            ("network", 8), ("network", 16)])
 def test_records_of_few_paths(fpt, n_paths, proposal, group):
     print(f"[case] {n_paths} paths {proposal} group {group}", flush=True)
     base = dataclasses.replace(W.c2(1)[3], phi_in=2.5, k_max=3000)
