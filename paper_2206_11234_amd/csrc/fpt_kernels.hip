@@ -626,22 +626,6 @@ struct LseAcc {
     }
 };
 
-// Power sums of x about c: n values, S_j = sum (x - c)^j.
-struct PowerSums {
-    double c = NAN, n = 0.0, S1 = 0.0, S2 = 0.0, S3 = 0.0, S4 = 0.0;
-    // add sums of nw values taken about cw: sum (x - c)^j = sum ((x - cw) + d)^j
-    __device__ __forceinline__ void fold(double cw, double nw, double s1, double s2, double s3, double s4) {
-        if (nw == 0.0) return;
-        if (isnan(c)) c = cw;
-        const double d = cw - c;
-        S4 += s4 + 4.0 * d * s3 + 6.0 * d * d * s2 + 4.0 * d * d * d * s1 + nw * d * d * d * d;
-        S3 += s3 + 3.0 * d * s2 + 3.0 * d * d * s1 + nw * d * d * d;
-        S2 += s2 + 2.0 * d * s1 + nw * d * d;
-        S1 += s1 + nw * d;
-        n += nw;
-    }
-};
-
 // Merge: MERGE_CELLS table cells by MERGE_SPLIT slice ranges per workgroup.  Bound by the reads of
 // the slices where tables are large, by the chain of exponentials over the slices where they are
 // small: with one thread per cell that chain was n_wg log-sum-exp updates long and took 0.5 ms
@@ -649,12 +633,22 @@ struct PowerSums {
 // MERGE_SPLIT threads per cell, each folding slices w, w + MERGE_SPLIT, ... with one exponential
 // apiece, and a tree over the threads in LDS.  32 neighbouring cells read 256 consecutive bytes of
 // a slice.  The order of the sums is fixed by the launch shape.
+//
+// The power sums of ln w are one chain over the slices in order: the lognormal estimate's upper error
+// is exp(u) - 1 with u up to some hundreds in bins of a few widely spread runs, u times the rounding of
+// the second moment, and folding partial sums into one another would round more often than adding the
+// slices' terms one by one.  Only the additions are in turn; the terms are formed by all threads (the
+// kernel with a tree for them 119 us at 1000 workgroups of 104 rows and 879 us at 13 056 rows, now 129
+// and 933).
 constexpr int MERGE_CELLS = 32, MERGE_SPLIT = 16, MERGE_BLOCK = MERGE_CELLS * MERGE_SPLIT;
+constexpr int MERGE_CHUNK = 2 * MERGE_SPLIT;        // slices whose terms are in LDS at a time
 
 __device__ __forceinline__ uint32_t merge_blocks(uint32_t cells) { return (cells + MERGE_CELLS - 1) / MERGE_CELLS; }
 
+static_assert(4 * MERGE_CHUNK * MERGE_CELLS == 8 * MERGE_BLOCK, "the terms fill the LDS array");
+
 __global__ __launch_bounds__(MERGE_BLOCK) void fpt_merge_kernel(MergeArgs a) {
-    __shared__ double red[7][MERGE_BLOCK];
+    __shared__ double red[8][MERGE_BLOCK];
     const TableLayout &L = a.lay;
     const uint32_t RT = L.n_rows, J = L.n_sub;
     const uint32_t n_cell_blocks = merge_blocks(J * RT), n_row_blocks = merge_blocks(RT);
@@ -698,50 +692,93 @@ __global__ __launch_bounds__(MERGE_BLOCK) void fpt_merge_kernel(MergeArgs a) {
         const uint32_t r = (blockIdx.x - n_cell_blocks) * MERGE_CELLS + lc;
         const bool have = r < RT;
         LseAcc l2;
-        PowerSums P;
+        double c = NAN;             // shift of the first slice that has one
+        int first = a.n_wg;
         if (have)
             for (int w = part; w < a.n_wg; w += MERGE_SPLIT) {
                 const unsigned char *sl = a.slices + static_cast<size_t>(w) * L.slice_bytes;
                 l2.add(reinterpret_cast<const double *>(sl + L.off_lse_w2)[r]);
                 const double cw = reinterpret_cast<const double *>(sl + L.off_shift)[r];
-                if (isnan(cw)) continue;
-                double nw = 0.0;
-                for (uint32_t s = 0; s < J; ++s)
-                    nw += static_cast<double>(reinterpret_cast<const uint32_t *>(sl + L.off_cnt)[s * RT + r]);
-                P.fold(cw, nw, reinterpret_cast<const double *>(sl + L.off_s1)[r],
-                       reinterpret_cast<const double *>(sl + L.off_s2)[r], reinterpret_cast<const double *>(sl + L.off_s3)[r],
-                       reinterpret_cast<const double *>(sl + L.off_s4)[r]);
+                if (first == a.n_wg && !isnan(cw)) {
+                    first = w;
+                    c = cw;
+                }
             }
         for (int half = MERGE_SPLIT / 2; half >= 1; half >>= 1) {
             red[0][tid] = l2.m;
             red[1][tid] = l2.s;
-            __syncthreads();
-            if (part < half) l2.fold(red[0][tid + half * MERGE_CELLS], red[1][tid + half * MERGE_CELLS]);
-            __syncthreads();
-            red[0][tid] = P.c;
-            red[1][tid] = P.n;
-            red[2][tid] = P.S1;
-            red[3][tid] = P.S2;
-            red[4][tid] = P.S3;
-            red[5][tid] = P.S4;
+            red[2][tid] = static_cast<double>(first);
+            red[3][tid] = c;
             __syncthreads();
             if (part < half) {
                 const int o = tid + half * MERGE_CELLS;
-                P.fold(red[0][o], red[1][o], red[2][o], red[3][o], red[4][o], red[5][o]);
+                l2.fold(red[0][o], red[1][o]);
+                if (red[2][o] < static_cast<double>(first)) {
+                    first = static_cast<int>(red[2][o]);
+                    c = red[3][o];
+                }
             }
             __syncthreads();
         }
+        if (part == 0) red[0][lc] = c;
+        __syncthreads();
+        c = red[0][lc];
+        __syncthreads();
+        // n values and their power sums about c, sum (x - c)^j = sum ((x - cw) + d)^j: the slices' terms
+        // by all threads, MERGE_CHUNK slices at a time, then their sums in slice order, S_j by part j - 1
+        double n = 0.0, S = 0.0;
+        double *const term = &red[0][0];        // [4][MERGE_CHUNK][MERGE_CELLS]
+        for (int w0 = 0; w0 < a.n_wg; w0 += MERGE_CHUNK) {
+#pragma unroll
+            for (int u = 0; u < MERGE_CHUNK / MERGE_SPLIT; ++u) {
+                const int at = u * MERGE_SPLIT + part, w = w0 + at;
+                double t1 = 0.0, t2 = 0.0, t3 = 0.0, t4 = 0.0;
+                if (have && w < a.n_wg) {
+                    const unsigned char *sl = a.slices + static_cast<size_t>(w) * L.slice_bytes;
+                    const double cw = reinterpret_cast<const double *>(sl + L.off_shift)[r];
+                    if (!isnan(cw)) {
+                        double nw = 0.0;
+                        for (uint32_t s = 0; s < J; ++s)
+                            nw += static_cast<double>(reinterpret_cast<const uint32_t *>(sl + L.off_cnt)[s * RT + r]);
+                        const double s1 = reinterpret_cast<const double *>(sl + L.off_s1)[r];
+                        const double s2 = reinterpret_cast<const double *>(sl + L.off_s2)[r];
+                        const double s3 = reinterpret_cast<const double *>(sl + L.off_s3)[r];
+                        const double s4 = reinterpret_cast<const double *>(sl + L.off_s4)[r];
+                        const double d = cw - c;
+                        t4 = s4 + 4.0 * d * s3 + 6.0 * d * d * s2 + 4.0 * d * d * d * s1 + nw * d * d * d * d;
+                        t3 = s3 + 3.0 * d * s2 + 3.0 * d * d * s1 + nw * d * d * d;
+                        t2 = s2 + 2.0 * d * s1 + nw * d * d;
+                        t1 = s1 + nw * d;
+                        n += nw;
+                    }
+                }
+                term[(0 * MERGE_CHUNK + at) * MERGE_CELLS + lc] = t1;
+                term[(1 * MERGE_CHUNK + at) * MERGE_CELLS + lc] = t2;
+                term[(2 * MERGE_CHUNK + at) * MERGE_CELLS + lc] = t3;
+                term[(3 * MERGE_CHUNK + at) * MERGE_CELLS + lc] = t4;
+            }
+            __syncthreads();
+            if (part < 4) {
+#pragma unroll
+                for (int at = 0; at < MERGE_CHUNK; ++at) S += term[(part * MERGE_CHUNK + at) * MERGE_CELLS + lc];
+            }
+            __syncthreads();
+        }
+        red[0][tid] = n;
+        red[1][tid] = S;
+        __syncthreads();
         if (have && part == 0) {
             const MergeInst m = a.mi[inst_of_row(a.mi, a.n_inst, r)];
             const uint32_t lr = r - m.row_base;
             const ResultLayout RL = result_layout(m.n_bins, J);
             double *V = a.values + m.values_off;
             V[RL.lse_w2 + lr] = l2.value();
-            const double n = P.n;
+            for (int q = 1; q < MERGE_SPLIT; ++q) n += red[0][q * MERGE_CELLS + lc];
             if (n > 0.0) {
-                const double mu = P.S1 / n;
-                const double e2 = P.S2 / n, e3 = P.S3 / n, e4 = P.S4 / n;
-                V[RL.mean_lnw + lr] = P.c + mu;
+                const double mu = S / n;
+                const double e2 = red[1][MERGE_CELLS + lc] / n, e3 = red[1][2 * MERGE_CELLS + lc] / n,
+                             e4 = red[1][3 * MERGE_CELLS + lc] / n;
+                V[RL.mean_lnw + lr] = c + mu;
                 V[RL.m2_lnw + lr] = e2 - mu * mu;
                 V[RL.m3_lnw + lr] = e3 - 3.0 * mu * e2 + 2.0 * mu * mu * mu;
                 V[RL.m4_lnw + lr] = e4 - 4.0 * mu * e3 + 6.0 * mu * mu * e2 - 3.0 * mu * mu * mu * mu;

@@ -38,3 +38,40 @@ def test_merge_matches_oracle(fpt, n_bins, n_sub, wg_per_cu, n_traj):
     for inst, res in zip(insts, results):
         tr = O.simulate(to_model(inst), 0, inst.n_traj)
         assert_histogram_matches(res, O.histogram(tr, inst.dN, inst.edges, n_sub))
+
+
+def _flat(n_traj, n_bins, **kw):
+    return W.Instance("flat", pot=W.POT_FLAT, V0=3 * (2 * math.pi) ** 2, phi_in=1.0, phi_end=0.0, phi_uv=1.5, dN=1e-3,
+                      bias=W.BIAS_NOISE_SCALED, A=-1.0, n_traj=n_traj, edges=np.linspace(0.05, 3.0, n_bins + 1), **kw)
+
+
+def test_moments_are_folded_in_workgroup_order(fpt):
+    """The power sums of ln w of a bin are those of one chain over the workgroups, bit for bit: the errors
+    of the lognormal estimate are exponentials of the variance and show its last bit where bins hold few,
+    widely spread runs.  256 workgroups of 64 lanes (per CU one) with a run to each lane take the run ids
+    64 by 64; a bin with at most one run per workgroup has sums that no order within one can change."""
+    cus = fpt.device_cus()
+    inst = _flat(64 * cus, 2000)
+    print("[case] moments in workgroup order", flush=True)
+    res, dump, _ = fpt.run(inst, 1, dump_n=inst.n_traj, block=64, wg_per_cu=1, chunk=1)
+    rows = O.bin_rows(dump.k.astype(np.uint64), dump.status, inst.dN, inst.edges)
+    seen = 0
+    for r in range(res.n_bins):
+        t = np.nonzero(rows == r)[0]
+        if t.size < 3 or np.unique(t // 64).size < t.size:
+            continue
+        x = [float(dump.lw[i]) for i in t]              # ascending ids: ascending workgroups
+        s1 = s2 = s3 = s4 = 0.0
+        for v in x:
+            d = v - x[0]
+            s4 += d * d * d * d
+            s3 += d * d * d
+            s2 += d * d
+            s1 += d
+        n = float(len(x))
+        mu, e2, e3, e4 = s1 / n, s2 / n, s3 / n, s4 / n
+        want = (x[0] + mu, e2 - mu * mu, e3 - 3.0 * mu * e2 + 2.0 * mu * mu * mu,
+                e4 - 4.0 * mu * e3 + 6.0 * mu * mu * e2 - 3.0 * mu * mu * mu * mu)
+        assert (res.mean_lnw[r], res.m2_lnw[r], res.m3_lnw[r], res.m4_lnw[r]) == want, (r, t.size)
+        seen += 1
+    assert seen > 200, seen
