@@ -467,6 +467,14 @@ __device__ __forceinline__ Steps4 steps4(const StepConsts &C, const F4 &z, float
     return S;
 }
 
+// Bump potential: whether the launch's groups may be taken without the bump, and whether the wave's
+// next one is (group4).  They may not where a run can get so far from the bump that (phi - phi0) / w^2
+// overflows: the bump's term is then infinity times 0, and leaving it out would give another field.
+struct BumpFar {
+    bool may;
+    bool now = false;
+};
+
 // The four steps of every lane's group R.j, all taken without a test between them: the group's
 // smallest and largest field and the step cap tell at its end whether a run has stopped inside it,
 // and then the first step that stops it is picked from the saved fields and weights into F (what the
@@ -477,23 +485,23 @@ __device__ __forceinline__ Steps4 steps4(const StepConsts &C, const F4 &z, float
 // them out of `running`.  H, where not NULL, gains fma(r, dN, sqrt(dN) xi) of each step taken, in
 // step order.
 //
-// Bump potential: `far` tells whether the wave's runs were all far from the bump in the last group;
+// Bump potential: far.now tells whether the wave's runs were all far from the bump in the last group;
 // then this one is taken without it (65 instructions a step instead of 108), and again with it if a
 // run came near.  The rule is the wave's, as a divergent step would issue both; it pays where the
-// wave's runs move together (70 000 runs that all fit the launch: 60.3 ms, now 52.6).
+// wave's runs move together (70 000 runs that all fit the launch: 60.3 ms, then 52.6).
 template <int POT, int BIAS, int P = 0, int WALL = WALL_ANY>
 __device__ __forceinline__ uint64_t group4(const StepConsts &C, uint32_t j_cap, const F4 &z, float r_net, RunState &R,
-                                           uint64_t &running, Stopped *F, bool &far, float *H = nullptr) {
+                                           uint64_t &running, Stopped *F, BumpFar &far, float *H = nullptr) {
     Steps4 S;
     if constexpr (POT == POT_QUADRATIC_BUMP) {
         auto came_near = [&]() { return (__builtin_amdgcn_ballot_w64(!(S.near * C.inv_2w2 > BUMP_FAR)) & running) != 0; };
-        if (far) {
+        if (far.now) {
             S = steps4<POT, BIAS, P, WALL, true>(C, z, r_net, R, H);
-            far = !came_near();
+            far.now = !came_near();
         }
-        if (!far) {
+        if (!far.now) {
             S = steps4<POT, BIAS, P, WALL, false>(C, z, r_net, R, H);
-            far = !came_near();
+            far.now = far.may && !came_near();
         }
     } else {
         S = steps4<POT, BIAS, P, WALL, false>(C, z, r_net, R, H);

@@ -30,6 +30,7 @@ struct RecordArgs {
     int32_t stride;             // keep the record of every stride-th group (g % stride == 0)
     int32_t mlp_every;
     uint32_t slots;             // paths per wave: 64, 32, 16 or 8
+    uint32_t bump_far;          // see StepArgs
     const uint16_t *mlp_params; // bfloat16 network of the sampling proposal
     const uint64_t *rec_off;    // n_paths + 1 record offsets
     TrainRec *rec;

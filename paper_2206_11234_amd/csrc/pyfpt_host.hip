@@ -15,6 +15,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <limits>
 #include <map>
 #include <mutex>
 #include <string>
@@ -187,6 +188,7 @@ struct Prepared {
     TableLayout lay{};
     const uint16_t *mlp_params = nullptr;
     int mlp_every = 1;
+    bool bump_far = true;    // no run can get where the bump's (phi - phi0) / w^2 overflows
     uint64_t v_total = 0;
     uint64_t counts_total = 0, values_total = 0;
     int pot = 0, bias = 0;
@@ -382,6 +384,13 @@ int prepare(const pyfpt_instance *ins, int n_inst, Prepared &P) {
         C.phi_esc = wall ? INFINITY : static_cast<float>(I.phi_esc > 0 ? I.phi_esc : 100.0 * I.phi_in);
         C.phi_in = static_cast<float>(I.phi_in);
         C.k_max = static_cast<uint32_t>(k_max);
+        if (I.pot.kind == PYFPT_POT_QUADRATIC_BUMP) {
+            // a run steps from fields in (phi_end, wall or escape level]; half the range is left for
+            // the roundings
+            const double top = wall ? C.phi_uv : C.phi_esc;
+            const double reach = std::max(std::fabs(top - C.phi0), std::fabs(static_cast<double>(C.phi_end) - C.phi0));
+            P.bump_far = P.bump_far && reach * C.inv_w2 < 0.5 * std::numeric_limits<float>::max();
+        }
         D.stream = I.stream;
         D.n_bins = static_cast<uint32_t>(I.bins.n_bins);
         D.row_base = rows;
@@ -645,6 +654,7 @@ int run_prepared(Device &d, const Prepared &P, uint64_t seed, const LaunchCfg &c
     sa.chunk = static_cast<uint32_t>(cfg.chunk);
     sa.lane_cap = static_cast<uint32_t>(shape.lane_cap);
     sa.spread = shape.spread ? 1u : 0u;
+    sa.bump_far = P.bump_far ? 1u : 0u;
     sa.cus = static_cast<uint32_t>(d.cus);
     sa.turn = static_cast<uint32_t>(std::max(1, 4 * d.cus / std::max(1, shape.n_wg)));
     sa.mlp_params = P.mlp_params;
@@ -984,6 +994,7 @@ int records_device(const Prepared &P, uint64_t seed, int group, int stride, cons
     // paths per wave: as few as leave each SIMD two waves (launch_shape's balance)
     ra.slots = 64;
     while (ra.slots > 8 && (n_paths + ra.slots / 2 - 1) / (ra.slots / 2) <= 2048) ra.slots /= 2;
+    ra.bump_far = P.bump_far ? 1u : 0u;
     ra.mlp_params = P.mlp_params;
     ra.rec_off = d_off;
     ra.rec = d_rec;

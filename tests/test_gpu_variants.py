@@ -149,3 +149,12 @@ def test_records_out_of_range_are_refused(fpt, where, pn):
     recs, _ = _records(fpt, 4097, 5)
     again = fpt.proposal_loss_grad(p, 196.0, 1e-3, p.values_f32(), recs, lw0, 100.0)
     assert again[0] == good[0] and np.array_equal(again[1], good[1]) and np.array_equal(again[2], good[2])
+
+
+def test_bump_too_narrow_for_binary32(fpt):
+    """A bump so narrow that (phi - phi0) / w^2 overflows binary32 away from it: its term in the drift is
+    infinity times zero there, and a run that gets that far from it never ends.  Such a launch takes no
+    group without the bump."""
+    print("[case] w=8e-20", flush=True)
+    _check(fpt, [W.Instance("bump", pot=W.POT_QUADRATIC_BUMP, m=0.05, a=0.05, phi0=4.0, w=8e-20, phi_in=5.0, phi_uv=6.0,
+                            bias=W.BIAS_NOISE_SCALED, A=1.0, dN=1e-2, n_traj=n, k_max=1000, edges=np.linspace(1, 12, 31)) for n in (5, 300)])
