@@ -486,6 +486,17 @@ WsMap ws_map(const Prepared &P, int n_wg) {
     return m;
 }
 
+// The launch fields left 0, from the plan t, whose block x wg_per_cu is 1024.  A field given on its own
+// bounds the other: no more workgroups than the plan has and than fill a CU's 1024 threads with the block
+// given, and a block that fits the 2048 threads asked of a CU with the workgroups given (down to the
+// plans' smallest, 256).
+void complete_cfg(LaunchCfg &c, const LaunchCfg &t) {
+    const bool block_given = c.block > 0;
+    if (!block_given) c.block = c.wg_per_cu <= 0 ? t.block : std::min(t.block, std::max(256, 2048 / c.wg_per_cu / 64 * 64));
+    if (c.wg_per_cu <= 0) c.wg_per_cu = block_given ? std::min(t.wg_per_cu, std::max(1, 1024 / c.block)) : t.wg_per_cu;
+    if (c.chunk <= 0) c.chunk = t.chunk;
+}
+
 // Defaults of the launch fields left 0.
 void resolve_cfg(const Prepared &P, LaunchCfg &c) {
     const bool mlp = P.bias == PYFPT_BIAS_MLP;
@@ -839,9 +850,7 @@ int run_batch_impl(const pyfpt_instance *ins, int n_inst, uint64_t seed, pyfpt_r
         // sampler has one resident shape, its default
         LaunchCfg t{256, 4, 1};
         if (P.v_total > static_cast<uint64_t>(d->cus) * 1024 && (rc = autotune(*d, ins, n_inst, seed, stream, P, t))) return rc;
-        if (cfg.block <= 0) cfg.block = t.block;
-        if (cfg.wg_per_cu <= 0) cfg.wg_per_cu = t.wg_per_cu;
-        if (cfg.chunk <= 0) cfg.chunk = t.chunk;
+        complete_cfg(cfg, t);
     }
     LaunchCfg rcfg = cfg;
     if (rcfg.wg_per_cu <= 0 && P.bias == PYFPT_BIAS_MLP && P.order.size() > 1) rcfg.wg_per_cu = 2;   // two waves per SIMD

@@ -68,3 +68,16 @@ def test_mixed_batch_spread_over_waves(fpt):
         if inst.n_traj:
             assert_dump_matches(dump, tr)
         assert_histogram_matches(res, O.histogram(tr, inst.dN, inst.edges))
+
+
+@pytest.mark.parametrize("shape", [dict(block=b) for b in (64, 512, 576, 768, 1024)] + [dict(wg_per_cu=w) for w in (1, 2, 4, 8)] +
+                         [dict(block=1024, chunk=2), dict(block=640, n_traj=300_000)])
+def test_part_of_a_shape_given(fpt, shape):
+    """Block sizes and workgroups per CU given on their own: the library chooses the other to fit."""
+    shape = dict(shape)
+    inst = _well(shape.pop("n_traj", 300), k_max=400)
+    print(f"[case] shape={shape} n={inst.n_traj}", flush=True)
+    n = min(inst.n_traj, 2000)
+    res, dump, _ = fpt.run(inst, 3, dump_n=n, **shape)
+    assert_dump_matches(dump, O.simulate(to_model(inst), 3, n))
+    assert res.n_traj == inst.n_traj and int(res.count.sum()) == inst.n_traj
