@@ -8,6 +8,7 @@ log-sums within 1e-12 relative (only the order of the workgroup atomics differs)
 within the tolerances of the oracle comparisons.
 """
 import ctypes
+import dataclasses
 
 import numpy as np
 import pytest
@@ -112,3 +113,21 @@ def test_noalloc_rejects_what_does_not_fit(fpt):
     a, _, _ = fpt.run_batch(insts[:1], SEED, noalloc=True, **CFG)
     b, _, _ = fpt.run_batch(insts[:1], SEED, **CFG)
     _assert_results_agree(a[0], b[0])
+
+
+@pytest.mark.parametrize("n_bins", [20, 250])
+def test_noalloc_learned_batch_at_the_default_shape(fpt, n_bins):
+    """Several learned instances without a launch shape: two workgroups per CU, as pyfpt_run_batch takes,
+    or one where the tables of two (240 B a row and workgroup) do not fit the 64 MiB of scratch."""
+    p = W.c4_params(3, eval_every=4)
+    insts = [dataclasses.replace(W.c4_instance(p, n_traj=700), phi_in=2.5, k_max=2000, stream=i, edges=np.linspace(0.0, 2.0, n_bins + 1))
+             for i in range(3)]
+    per_wg = 240 * sum(len(i.edges) + 3 for i in insts)
+    assert (2 * fpt.device_cus() * per_wg > 64 << 20) == (n_bins == 250) and fpt.device_cus() * per_wg < 63 << 20
+    _print_case("noalloc learned batch", n_bins=n_bins)
+    a, da, _ = fpt.run_batch(insts, SEED, noalloc=True, dump_n=700)
+    b, db, _ = fpt.run_batch(insts, SEED, dump_n=700)
+    for x, y, dx, dy in zip(a, b, da, db):
+        _assert_results_agree(x, y)
+        for name in ("k", "lw", "phi", "status"):
+            assert np.array_equal(getattr(dx, name), getattr(dy, name)), name
