@@ -32,7 +32,7 @@ struct TableLayout {
     uint32_t n_inst;
     uint32_t slice_bytes;
     // binary64 arrays
-    uint32_t off_scal;    // [n_inst][16]: two unused, lse_wk, lse_wk2, sum_k2, steps, then over the ended runs: n, sum x, sum x^2, sum y, sum y^2, sum xy (x = ln w, y = k - k_center), pad
+    uint32_t off_scal;    // [n_inst][16]: sums of the low and of the high words of k^2 (integers), lse_wk, lse_wk2, unused, steps, then over the ended runs: n, sum x, sum x^2, sum y, sum y^2, sum xy (x = ln w, y = k - k_center), pad
     uint32_t off_jk_lse;  // [J][n_rows]
     uint32_t off_lse_w2;  // [n_rows]
     uint32_t off_shift;   // [n_rows]

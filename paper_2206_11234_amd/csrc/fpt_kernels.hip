@@ -89,7 +89,7 @@ __device__ __forceinline__ void init_table(unsigned char *base, const TableLayou
         unsigned long long v = 0ull;
         if (off < L.off_jk_lse) {
             const uint32_t f = ((off - L.off_scal) / 8) & 15u;
-            v = (f < 4) ? FPT_NEG_INF_BITS : 0ull;
+            v = (f == 2 || f == 3) ? FPT_NEG_INF_BITS : 0ull;
         } else if (off < L.off_shift) {
             v = FPT_NEG_INF_BITS;           // jk_lse, lse_w2
         } else if (off < L.off_s1) {
@@ -522,10 +522,14 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
                 atomic_add_f64(sc + 10, y * y);
                 atomic_add_f64(sc + 11, lw * y);
             }
-            // instance-wide sums: of k and k^2 in the table (exact: integers below 2^53 and their
-            // squares' rounded sum), the log-sums in lane registers
+            // instance-wide sums: of k in the table (exact: integers below 2^53), of k^2 as the integer
+            // sums of its two 32-bit words (exact up to 2^32 runs a workgroup; one binary64 sum of the
+            // workgroup's runs in turn rounds once a run beyond 2^53), the log-sums in lane registers
             const double kd = static_cast<double>(k);
-            atomic_add_f64(T.scal + static_cast<size_t>(cur_inst) * 16 + 4, kd * kd);
+            const uint64_t k2 = static_cast<uint64_t>(k) * k;
+            unsigned long long *sk = reinterpret_cast<unsigned long long *>(T.scal + static_cast<size_t>(cur_inst) * 16);
+            atomicAdd(sk + 0, static_cast<unsigned long long>(k2 & 0xFFFFFFFFu));
+            atomicAdd(sk + 1, static_cast<unsigned long long>(k2 >> 32));
             atomic_add_f64(T.scal + static_cast<size_t>(cur_inst) * 16 + 5, kd);
             const double lk = log(kd);
             acc.wk = lse2(acc.wk, lw + lk);
@@ -793,21 +797,28 @@ __global__ __launch_bounds__(MERGE_BLOCK) void fpt_merge_kernel(MergeArgs a) {
         // one instance's whole-run sums
         const int i = static_cast<int>(blockIdx.x - n_cell_blocks - n_row_blocks);
         LseAcc f[2];
-        double acc[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+        unsigned long long k2[2] = {0, 0};          // sum of k^2: low and high words of the runs' k^2
+        double acc[7] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
         for (int w = tid; w < a.n_wg; w += MERGE_BLOCK) {
             const double *sc = reinterpret_cast<const double *>(a.slices + static_cast<size_t>(w) * L.slice_bytes + L.off_scal) +
                                static_cast<size_t>(i) * 16;
+            // (each workgroup's low sum carried, so that the sums over all stay in range)
+            const unsigned long long lo = static_cast<unsigned long long>(__double_as_longlong(sc[0]));
+            k2[0] += lo & 0xFFFFFFFFull;
+            k2[1] += static_cast<unsigned long long>(__double_as_longlong(sc[1])) + (lo >> 32);
 #pragma unroll
             for (int q = 0; q < 2; ++q) f[q].add(sc[2 + q]);
 #pragma unroll
-            for (int q = 0; q < 8; ++q) acc[q] += sc[4 + q];
+            for (int q = 0; q < 7; ++q) acc[q] += sc[5 + q];
         }
         // fold each wave, then the waves in order
         for (int h = 32; h >= 1; h >>= 1) {
 #pragma unroll
+            for (int q = 0; q < 2; ++q) k2[q] += __shfl_down(k2[q], h, 64);
+#pragma unroll
             for (int q = 0; q < 2; ++q) f[q].fold(__shfl_down(f[q].m, h, 64), __shfl_down(f[q].s, h, 64));
 #pragma unroll
-            for (int q = 0; q < 8; ++q) acc[q] += __shfl_down(acc[q], h, 64);
+            for (int q = 0; q < 7; ++q) acc[q] += __shfl_down(acc[q], h, 64);
         }
         if (tid % 64 == 0) {
             double *o = &red[0][0] + (tid / 64) * 16;
@@ -815,33 +826,38 @@ __global__ __launch_bounds__(MERGE_BLOCK) void fpt_merge_kernel(MergeArgs a) {
             for (int q = 0; q < 2; ++q) {
                 o[2 * q] = f[q].m;
                 o[2 * q + 1] = f[q].s;
+                o[4 + q] = __longlong_as_double(static_cast<long long>(k2[q]));
             }
 #pragma unroll
-            for (int q = 0; q < 8; ++q) o[8 + q] = acc[q];
+            for (int q = 0; q < 7; ++q) o[8 + q] = acc[q];
         }
         __syncthreads();
         if (tid == 0) {
             for (int wave = 1; wave < MERGE_BLOCK / 64; ++wave) {
                 const double *o = &red[0][0] + wave * 16;
 #pragma unroll
-                for (int q = 0; q < 2; ++q) f[q].fold(o[2 * q], o[2 * q + 1]);
+                for (int q = 0; q < 2; ++q) {
+                    f[q].fold(o[2 * q], o[2 * q + 1]);
+                    k2[q] += static_cast<unsigned long long>(__double_as_longlong(o[4 + q]));
+                }
 #pragma unroll
-                for (int q = 0; q < 8; ++q) acc[q] += o[8 + q];
+                for (int q = 0; q < 7; ++q) acc[q] += o[8 + q];
             }
             const MergeInst m = a.mi[i];
             const ResultLayout RL = result_layout(m.n_bins, J);
             double *V = a.values + m.values_off;
             V[RL.lse_wk] = f[0].value();
             V[RL.lse_wk2] = f[1].value();
-            V[RL.sum_k2] = acc[0];
+            // one rounding while the high sum is below 2^53
+            V[RL.sum_k2] = static_cast<double>(k2[1] + (k2[0] >> 32)) * 4294967296.0 + static_cast<double>(k2[0] & 0xFFFFFFFFull);
             // Pearson's r of ln w with N over the ended runs (equal to that of log10 w with N)
-            const double n = acc[2];
-            const double mx = acc[3] / n, my = acc[5] / n;
-            const double cxy = acc[7] / n - mx * my;
-            const double vx = acc[4] / n - mx * mx, vy = acc[6] / n - my * my;
+            const double n = acc[1];
+            const double mx = acc[2] / n, my = acc[4] / n;
+            const double cxy = acc[6] / n - mx * my;
+            const double vx = acc[3] / n - mx * mx, vy = acc[5] / n - my * my;
             V[RL.pearson_r] = (n >= 2.0 && vx > 0.0 && vy > 0.0) ? cxy / sqrt(vx * vy) : NAN;
             a.counts[m.counts_off + RL.n_traj] = m.n_traj;
-            a.counts[m.counts_off + RL.total_steps] = static_cast<uint64_t>(acc[1]);
+            a.counts[m.counts_off + RL.total_steps] = static_cast<uint64_t>(acc[0]);
             V[RL.lognormal_gate] = 1.0;     // cleared by the finalize kernel where a bin fails
         }
     }

@@ -75,3 +75,15 @@ def test_moments_are_folded_in_workgroup_order(fpt):
         assert (res.mean_lnw[r], res.m2_lnw[r], res.m3_lnw[r], res.m4_lnw[r]) == want, (r, t.size)
         seen += 1
     assert seen > 200, seen
+
+
+def test_sum_of_squared_steps_is_the_exact_sum_rounded(fpt):
+    """Runs of up to 2^21 - 1 steps: the sum of k^2 over them is beyond binary64's integers."""
+    inst = _flat(40_000, 30, k_max=2 ** 21 - 1)
+    inst.dN, inst.A, inst.bias = 1e-6, 0.0, W.BIAS_NONE
+    print("[case] sum k^2", flush=True)
+    res, dump, _ = fpt.run(inst, 1, dump_n=inst.n_traj)
+    exact = sum(int(k) * int(k) for k in dump.k)
+    assert exact > 2 ** 55
+    assert res.sum_k2 == float(exact)
+    assert res.total_steps == int(dump.k.astype(np.int64).sum())
