@@ -1,0 +1,28 @@
+// fpt_launch.h -- sizes of the record and training kernels' launches, as plain functions of the work and
+// of the number of compute units.
+#pragma once
+
+#include <stdint.h>
+
+#include <algorithm>
+
+namespace fpt {
+
+// Paths per wave of a replay: as few of 64, 32, 16 and 8 as leave each SIMD two waves, since a SIMD issues
+// an instruction per 5 cycles for one wave and per 2.4 for two or more.
+inline uint32_t record_slots(uint64_t n_paths, int cus) {
+    uint32_t slots = 64;
+    while (slots > 8 && (n_paths + slots / 2 - 1) / (slots / 2) <= 8ull * cus) slots /= 2;
+    return slots;
+}
+
+// Waves per workgroup of a replay: one while the waves fit the SIMDs once, else one for each SIMD of a CU.
+inline uint32_t record_waves_per_group(uint64_t waves, int cus) { return waves <= 4ull * cus ? 1 : 4; }
+
+// Workgroups of the evaluation, 256 records each at a time: those that share the CUs (three waves per SIMD).
+constexpr int EVAL_WG_PER_CU = 3;
+inline uint32_t eval_groups(uint64_t n_rec, int cus) {
+    return static_cast<uint32_t>(std::min<uint64_t>((n_rec + 255) / 256, static_cast<uint64_t>(EVAL_WG_PER_CU) * cus));
+}
+
+}  // namespace fpt

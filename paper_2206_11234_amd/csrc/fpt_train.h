@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "fpt_kernels.h"
+#include "fpt_launch.h"
 
 namespace fpt {
 
@@ -29,6 +30,7 @@ struct RecordArgs {
     int32_t group;              // one record per group of 1, 4, 8 or 16 steps
     int32_t stride;             // keep the record of every stride-th group (g % stride == 0)
     int32_t mlp_every;
+    int32_t cus;                // compute units of the device
     uint32_t slots;             // paths per wave: 64, 32, 16 or 8
     uint32_t bump_far;          // see StepArgs
     const uint16_t *mlp_params; // bfloat16 network of the sampling proposal
@@ -46,6 +48,7 @@ struct TrainArgs {
     const uint64_t *rec_off;    // n_paths + 1
     int32_t n_paths;
     int32_t n_part;             // workgroups of the backward pass
+    int32_t cus;                // compute units of the device
     int32_t objective;          // 0: log M2 (c ~ w_0 w_theta); 1: cross entropy (c ~ w_0)
     float temper;               // w_0 enters the path weights as w_0^temper
     float rec_weight;           // each record stands for this many groups (the record stride)

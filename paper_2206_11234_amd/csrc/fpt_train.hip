@@ -33,7 +33,6 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 
-#include <algorithm>
 
 #include "fpt_kernels.h"
 #include "fpt_team.h"
@@ -240,7 +239,6 @@ __device__ __forceinline__ void net_layer1(const float *__restrict__ th, const f
 // The binary32 product adds k in ascending order with one rounding each, as a chain of fma does, so r
 // is the same bit for bit.  7.4e5 records of 700 paths: one workgroup per path 190 us; two records per
 // lane with W2 (more than the scalar cache) read by scalar loads 126 us; now 87 us.
-constexpr int EVAL_WG_PER_CU = 3;
 typedef float f32x16v __attribute__((ext_vector_type(16)));
 
 struct Half2 {
@@ -624,9 +622,8 @@ __global__ __launch_bounds__(256) void fpt_to_bf16_kernel(const float *theta, ui
 // ---------------------------------------------------------------------------
 template <int POT, int BIAS>
 static hipError_t launch_record_t(const RecordArgs &a, hipStream_t s) {
-    // one wave per workgroup while the waves fit the chip's SIMDs once, else four
     const unsigned waves = (a.n_paths + a.slots - 1) / a.slots;
-    const unsigned per_wg = waves <= 1024 ? 1 : 4;
+    const unsigned per_wg = record_waves_per_group(waves, a.cus);
     hipLaunchKernelGGL((fpt_record_kernel<POT, BIAS>), dim3((waves + per_wg - 1) / per_wg), dim3(64 * per_wg), 0, s, a);
     return hipGetLastError();
 }
@@ -663,8 +660,7 @@ hipError_t launch_train_loss(const TrainArgs &a, hipStream_t s) {
     if (a.n_paths <= 0) return hipErrorInvalidValue;
     hipError_t e = hipSuccess;
     if (a.n_rec > 0) {
-        const uint64_t wgs = std::min<uint64_t>((a.n_rec + 255) / 256, EVAL_WG_PER_CU * 256);
-        hipLaunchKernelGGL(fpt_train_eval_kernel, dim3(static_cast<unsigned>(wgs)), dim3(256), 0, s, a, a.theta);
+        hipLaunchKernelGGL(fpt_train_eval_kernel, dim3(eval_groups(a.n_rec, a.cus)), dim3(256), 0, s, a, a.theta);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

@@ -991,6 +991,19 @@ MlpConsts mlp_consts(const pyfpt_mlp &m, double target_N) {
     return c;
 }
 
+// Compute units of the current device (1 where they cannot be told).
+int current_cus() {
+    Device *d = nullptr;
+    std::lock_guard<std::mutex> lock(g_mu);
+    return get_device(&d) == PYFPT_OK && d->cus > 0 ? d->cus : 1;
+}
+
+int backward_groups(uint64_t n_rec, int cus) {
+    const uint64_t tiles = (n_rec + 63) / 64;
+    const uint64_t cap = static_cast<uint64_t>(cus) * 4;   // four backward workgroups per CU
+    return static_cast<int>(std::max<uint64_t>(1, std::min(tiles, cap)));
+}
+
 // Replay on the device: buffers already on the device; outputs per path on the device.
 int records_device(const Prepared &P, uint64_t seed, int group, int stride, const uint64_t *d_t, uint32_t n_paths,
                    const uint64_t *d_off, TrainRec *d_rec, uint32_t *d_k, double *d_lw, int32_t *d_st,
@@ -1004,9 +1017,8 @@ int records_device(const Prepared &P, uint64_t seed, int group, int stride, cons
     ra.group = group;
     ra.stride = stride;
     ra.mlp_every = P.mlp_every;
-    // paths per wave: as few as leave each SIMD two waves (launch_shape's balance)
-    ra.slots = 64;
-    while (ra.slots > 8 && (n_paths + ra.slots / 2 - 1) / (ra.slots / 2) <= 2048) ra.slots /= 2;
+    ra.cus = current_cus();
+    ra.slots = record_slots(n_paths, ra.cus);
     ra.bump_far = P.bump_far ? 1u : 0u;
     ra.mlp_params = P.mlp_params;
     ra.rec_off = d_off;
@@ -1017,18 +1029,6 @@ int records_device(const Prepared &P, uint64_t seed, int group, int stride, cons
     ra.n_rec_out = d_nrec;
     HIP_TRY(launch_records(P.pot, P.bias, ra, stream), "launch record kernel");
     return PYFPT_OK;
-}
-
-int backward_groups(uint64_t n_rec) {
-    int cus = 0;
-    {
-        Device *d = nullptr;
-        std::lock_guard<std::mutex> lock(g_mu);
-        if (get_device(&d) == PYFPT_OK) cus = d->cus;
-    }
-    const uint64_t tiles = (n_rec + 63) / 64;
-    const uint64_t cap = static_cast<uint64_t>(cus > 0 ? cus : 1) * 4;   // four backward workgroups per CU
-    return static_cast<int>(std::max<uint64_t>(1, std::min(tiles, cap)));
 }
 
 }  // namespace
@@ -1309,7 +1309,8 @@ static int pyfpt_proposal_loss_grad_impl(const pyfpt_mlp *net, double target_N, 
     int rc = check_offsets(rec_off, n_paths, n_rec);
     if (rc) return rc;
     hipStream_t stream = opt ? static_cast<hipStream_t>(opt->stream) : nullptr;
-    const int n_part = backward_groups(n_rec);
+    const int cus = current_cus();
+    const int n_part = backward_groups(n_rec, cus);
     // one allocation for the call's device arrays
     size_t top = 0;
     auto take = [&](size_t bytes) {
@@ -1348,6 +1349,7 @@ static int pyfpt_proposal_loss_grad_impl(const pyfpt_mlp *net, double target_N, 
     ta.rec_off = reinterpret_cast<uint64_t *>(D + o_off);
     ta.n_paths = n_paths;
     ta.n_part = n_part;
+    ta.cus = cus;
     ta.objective = objective;
     ta.temper = static_cast<float>(temper);
     ta.rec_weight = static_cast<float>(rec_weight);
@@ -1550,7 +1552,8 @@ static int pyfpt_train_proposal_impl(const pyfpt_instance *inst, uint64_t seed, 
         Prepared P;
         if ((rc = prepare(&I, 1, P))) return rc;
         DevBuf dt, doff, drec, rk, rlw, rst, rnr, lwt, l0, c, ls, part, rr;
-        const int n_part = backward_groups(n_rec);
+        const int cus = current_cus();
+        const int n_part = backward_groups(n_rec, cus);
         if ((rc = rr.alloc(4ull * n_rec)) || (rc = dt.alloc(8ull * np)) || (rc = doff.alloc(8ull * (np + 1))) || (rc = drec.alloc(16ull * n_rec)) ||
             (rc = rk.alloc(4ull * np)) || (rc = rlw.alloc(8ull * np)) || (rc = rst.alloc(4ull * np)) ||
             (rc = rnr.alloc(8ull * np)) || (rc = lwt.alloc(8ull * np)) ||
@@ -1584,6 +1587,7 @@ static int pyfpt_train_proposal_impl(const pyfpt_instance *inst, uint64_t seed, 
         ta.rec_off = doff.as<uint64_t>();
         ta.n_paths = static_cast<int32_t>(np);
         ta.n_part = n_part;
+        ta.cus = cus;
         ta.objective = cfg->objective;
         ta.temper = cfg->temper;
         ta.rec_weight = static_cast<float>(cfg->stride);
