@@ -25,4 +25,10 @@ inline uint32_t eval_groups(uint64_t n_rec, int cus) {
     return static_cast<uint32_t>(std::min<uint64_t>((n_rec + 255) / 256, static_cast<uint64_t>(EVAL_WG_PER_CU) * cus));
 }
 
+// Workgroups of the record check, 256 records each at a time: a CU's 2048 threads.  (A launch holds fewer
+// than 2^32 threads; a call may hold more records.)
+inline uint32_t check_groups(uint64_t n_rec, int cus) {
+    return static_cast<uint32_t>(std::min<uint64_t>((n_rec + 255) / 256, 8ull * cus));
+}
+
 }  // namespace fpt

@@ -33,7 +33,6 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 
-
 #include "fpt_kernels.h"
 #include "fpt_team.h"
 #include "fpt_train.h"
@@ -338,9 +337,9 @@ __global__ __launch_bounds__(256) void fpt_train_path_kernel(TrainArgs a) {
 // records took longer than the kernels that use them).
 __global__ __launch_bounds__(256) void fpt_train_check_kernel(const TrainRec *rec, uint64_t n_rec, uint32_t n_paths,
                                                               unsigned long long *first_bad) {
-    const uint64_t e = static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (e >= n_rec) return;
-    if (!train_record_ok(rec[e].pn, n_paths)) atomicMin(first_bad, static_cast<unsigned long long>(e));
+    for (uint64_t e = static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x; e < n_rec;
+         e += static_cast<uint64_t>(gridDim.x) * blockDim.x)
+        if (!train_record_ok(rec[e].pn, n_paths)) atomicMin(first_bad, static_cast<unsigned long long>(e));
 }
 
 // ---------------------------------------------------------------------------
@@ -651,7 +650,7 @@ hipError_t launch_records(int pot, int bias, const RecordArgs &a, hipStream_t s)
 
 hipError_t launch_train_check(const TrainArgs &a, unsigned long long *first_bad, hipStream_t s) {
     if (a.n_rec == 0) return hipSuccess;
-    hipLaunchKernelGGL(fpt_train_check_kernel, dim3(static_cast<unsigned>((a.n_rec + 255) / 256)), dim3(256), 0, s, a.rec, a.n_rec,
+    hipLaunchKernelGGL(fpt_train_check_kernel, dim3(check_groups(a.n_rec, a.cus)), dim3(256), 0, s, a.rec, a.n_rec,
                        static_cast<uint32_t>(a.n_paths), first_bad);
     return hipGetLastError();
 }

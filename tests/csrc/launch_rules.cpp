@@ -13,6 +13,7 @@ int main(int argc, char **argv) {
         if (!std::strcmp(argv[i], "slots")) v = fpt::record_slots(n, cus);
         else if (!std::strcmp(argv[i], "waves")) v = fpt::record_waves_per_group(n, cus);
         else if (!std::strcmp(argv[i], "eval")) v = fpt::eval_groups(n, cus);
+        else if (!std::strcmp(argv[i], "check")) v = fpt::check_groups(n, cus);
         else return 2;
         std::printf("%u\n", v);
     }

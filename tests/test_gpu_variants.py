@@ -158,3 +158,15 @@ def test_bump_too_narrow_for_binary32(fpt):
     print("[case] w=8e-20", flush=True)
     _check(fpt, [W.Instance("bump", pot=W.POT_QUADRATIC_BUMP, m=0.05, a=0.05, phi0=4.0, w=8e-20, phi_in=5.0, phi_uv=6.0,
                             bias=W.BIAS_NOISE_SCALED, A=1.0, dN=1e-2, n_traj=n, k_max=1000, edges=np.linspace(1, 12, 31)) for n in (5, 300)])
+
+
+@pytest.mark.parametrize("first,second", [(524288 + 3, 524288 + 200), (262144 + 7, 2 * 524288 + 9)])
+def test_records_out_of_range_beyond_one_grid(fpt, first, second):
+    """The check's threads (2048 a CU, 524 288 on 256 CUs) take several records each: the lowest one out of
+    range is named whichever round it falls in."""
+    print(f"[case] bad records {first} {second}", flush=True)
+    recs, lw0 = _records(fpt, 2 * 524288 + 333, 5)
+    p = W.c4_params(7)
+    recs.rec["pn"][[first, second]] = 17
+    with pytest.raises(Exception, match=f"record {first}:"):
+        fpt.proposal_loss_grad(p, 196.0, 1e-3, p.values_f32(), recs, lw0, 100.0)

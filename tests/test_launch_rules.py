@@ -38,3 +38,11 @@ def test_evaluation_groups(rule, cus):
     full = 3 * cus
     assert rule(("eval", 1, cus), ("eval", 257, cus), ("eval", 256 * full, cus), ("eval", 256 * full + 1, cus),
                 ("eval", 1 << 40, cus)) == [1, min(2, full), full, full, full]
+
+
+@pytest.mark.parametrize("cus", [1, 256])
+def test_record_check_groups(rule, cus):
+    """A launch holds fewer than 2^32 threads, whatever the number of records."""
+    full = 8 * cus
+    got = rule(("check", 1, cus), ("check", 256 * full, cus), ("check", 1 << 32, cus), ("check", 1 << 45, cus))
+    assert got == [1, full, full, full] and 256 * full < 1 << 32
