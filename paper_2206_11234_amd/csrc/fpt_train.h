@@ -55,7 +55,9 @@ struct TrainArgs {
     const float *theta;         // binary32 master parameters
     MlpConsts mc;               // input normalisation, output scale, N*
     float dN;                   // binary32 dN
-    float *r;                   // r_theta per record (n_rec)
+    float *r;                   // r_theta per record of a piece (eval_capacity)
+    int32_t path0;              // the piece's first path
+    uint64_t rec0;              // and its first record
     double *lw_theta;           // ln w_theta per path
     const double *lw0;          // ln w_0 per path (sampled)
     double n_total;             // runs drawn
@@ -80,7 +82,8 @@ __host__ __device__ inline bool train_record_ok(uint32_t pn, uint32_t n_paths) {
 }
 
 hipError_t launch_train_check(const TrainArgs &a, unsigned long long *first_bad, hipStream_t s);
-hipError_t launch_train_loss(const TrainArgs &a, hipStream_t s);
+// h_off: the host's copy of a.rec_off
+hipError_t launch_train_loss(const TrainArgs &a, const uint64_t *h_off, hipStream_t s);
 hipError_t launch_train_grad(const TrainArgs &a, hipStream_t s);
 hipError_t launch_adam(const AdamArgs &a, hipStream_t s);
 hipError_t launch_to_bf16(const float *theta, uint16_t *bf, hipStream_t s);

@@ -314,13 +314,13 @@ fpt_train_eval_kernel(TrainArgs a, const float *__restrict__ th0) {
 // ln w_theta of a path: its records' terms in binary64, one workgroup per path, in a fixed order.
 __global__ __launch_bounds__(256) void fpt_train_path_kernel(TrainArgs a) {
     __shared__ double red[256];
-    const int i = blockIdx.x;
+    const int i = a.path0 + blockIdx.x;
     const uint64_t e0 = a.rec_off[i], e1 = a.rec_off[i + 1];
     const double hdN = 0.5 * static_cast<double>(a.dN);
     double s = 0.0;
     for (uint64_t e = e0 + threadIdx.x; e < e1; e += blockDim.x) {
         const TrainRec R = a.rec[e];
-        const double rd = static_cast<double>(a.r[e]);
+        const double rd = static_cast<double>(a.r[e - a.rec0]);
         const double n = static_cast<double>(R.pn & 31u);
         s += (-rd * static_cast<double>(R.H) + rd * rd * n * hdN) * static_cast<double>(a.rec_weight);
     }
@@ -655,17 +655,26 @@ hipError_t launch_train_check(const TrainArgs &a, unsigned long long *first_bad,
     return hipGetLastError();
 }
 
-hipError_t launch_train_loss(const TrainArgs &a, hipStream_t s) {
+hipError_t launch_train_loss(const TrainArgs &a, const uint64_t *h_off, hipStream_t s) {
     if (a.n_paths <= 0) return hipErrorInvalidValue;
     hipError_t e = hipSuccess;
-    if (a.n_rec > 0) {
-        hipLaunchKernelGGL(fpt_train_eval_kernel, dim3(eval_groups(a.n_rec, a.cus)), dim3(256), 0, s, a, a.theta);
+    for (int64_t i = 0, j; i < a.n_paths; i = j) {
+        j = eval_piece_end(h_off, a.n_paths, i);
+        TrainArgs p = a;
+        p.path0 = static_cast<int32_t>(i);
+        p.rec0 = h_off[i];
+        if (h_off[j] > h_off[i]) {
+            p.rec = a.rec + h_off[i];
+            p.n_rec = h_off[j] - h_off[i];
+            hipLaunchKernelGGL(fpt_train_eval_kernel, dim3(eval_groups(p.n_rec, a.cus)), dim3(256), 0, s, p, a.theta);
+            e = hipGetLastError();
+            if (e != hipSuccess) return e;
+            p.rec = a.rec;
+        }
+        hipLaunchKernelGGL(fpt_train_path_kernel, dim3(static_cast<unsigned>(j - i)), dim3(256), 0, s, p);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(fpt_train_path_kernel, dim3(a.n_paths), dim3(256), 0, s, a);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(fpt_train_softmax_kernel, dim3(1), dim3(1024), 0, s, a);
     return hipGetLastError();
 }

@@ -1318,7 +1318,7 @@ static int pyfpt_proposal_loss_grad_impl(const pyfpt_mlp *net, double target_N, 
         top = align_up(top + bytes, kAlign);
         return at;
     };
-    const size_t o_rec = take(16ull * n_rec), o_r = take(4ull * n_rec), o_off = take(8ull * (n_paths + 1)),
+    const size_t o_rec = take(16ull * n_rec), o_r = take(4ull * eval_capacity(rec_off, n_paths)), o_off = take(8ull * (n_paths + 1)),
                  o_lwt = take(8ull * n_paths), o_l0 = take(8ull * n_paths), o_c = take(8ull * n_paths),
                  o_part = take(4ull * NET_N_PARAMS * static_cast<uint64_t>(n_part)), o_th = take(4ull * NET_N_PARAMS),
                  o_ls = take(16 + 8ull * NET_N_PARAMS), o_g = o_ls + 16;
@@ -1365,7 +1365,7 @@ static int pyfpt_proposal_loss_grad_impl(const pyfpt_mlp *net, double target_N, 
     ta.part = reinterpret_cast<float *>(D + o_part);
     ta.grad = reinterpret_cast<double *>(D + o_g);
     HIP_TRY(launch_train_check(ta, reinterpret_cast<unsigned long long *>(D + o_ls + 8), stream), "launch record check");
-    HIP_TRY(launch_train_loss(ta, stream), "launch loss kernels");
+    HIP_TRY(launch_train_loss(ta, rec_off, stream), "launch loss kernels");
     HIP_TRY(launch_train_grad(ta, stream), "launch gradient kernels");
     // the records were checked on the device, beside the work (which reads no array through them
     // out of range): nothing is given back where one is out of range
@@ -1554,7 +1554,7 @@ static int pyfpt_train_proposal_impl(const pyfpt_instance *inst, uint64_t seed, 
         DevBuf dt, doff, drec, rk, rlw, rst, rnr, lwt, l0, c, ls, part, rr;
         const int cus = current_cus();
         const int n_part = backward_groups(n_rec, cus);
-        if ((rc = rr.alloc(4ull * n_rec)) || (rc = dt.alloc(8ull * np)) || (rc = doff.alloc(8ull * (np + 1))) || (rc = drec.alloc(16ull * n_rec)) ||
+        if ((rc = rr.alloc(4ull * eval_capacity(off.data(), np))) || (rc = dt.alloc(8ull * np)) || (rc = doff.alloc(8ull * (np + 1))) || (rc = drec.alloc(16ull * n_rec)) ||
             (rc = rk.alloc(4ull * np)) || (rc = rlw.alloc(8ull * np)) || (rc = rst.alloc(4ull * np)) ||
             (rc = rnr.alloc(8ull * np)) || (rc = lwt.alloc(8ull * np)) ||
             (rc = l0.alloc(8ull * np)) || (rc = c.alloc(8ull * np)) || (rc = ls.alloc(8)) ||
@@ -1606,7 +1606,7 @@ static int pyfpt_train_proposal_impl(const pyfpt_instance *inst, uint64_t seed, 
         for (int step = 0; step < cfg->steps; ++step) {
             // the cross-entropy weights c_i depend on w_0 only: the forward pass (ln w_theta and
             // the weights) is needed once per round; log M2's weights change with theta
-            if (step == 0 || cfg->objective == 0) HIP_TRY(launch_train_loss(ta, stream), "launch loss kernels");
+            if (step == 0 || cfg->objective == 0) HIP_TRY(launch_train_loss(ta, off.data(), stream), "launch loss kernels");
             if (step == 0) HIP_TRY(hipMemcpyAsync(&R.loss_first, ls.p, 8, hipMemcpyDeviceToHost, stream), "download loss");
             HIP_TRY(launch_train_grad(ta, stream), "launch gradient kernels");
             t_adam += 1;
@@ -1625,7 +1625,7 @@ static int pyfpt_train_proposal_impl(const pyfpt_instance *inst, uint64_t seed, 
             HIP_TRY(launch_adam(aa, stream), "launch Adam");
         }
         // loss at the updated parameters
-        HIP_TRY(launch_train_loss(ta, stream), "launch loss kernels");
+        HIP_TRY(launch_train_loss(ta, off.data(), stream), "launch loss kernels");
         HIP_TRY(hipEventRecord(ev[3], stream), "event");
         HIP_TRY(hipMemcpyAsync(&R.loss_last, ls.p, 8, hipMemcpyDeviceToHost, stream), "download loss");
         HIP_TRY(hipStreamSynchronize(stream), "hipStreamSynchronize");

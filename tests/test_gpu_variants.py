@@ -170,3 +170,24 @@ def test_records_out_of_range_beyond_one_grid(fpt, first, second):
     recs.rec["pn"][[first, second]] = 17
     with pytest.raises(Exception, match=f"record {first}:"):
         fpt.proposal_loss_grad(p, 196.0, 1e-3, p.values_f32(), recs, lw0, 100.0)
+
+
+def test_log_weights_over_several_pieces(fpt):
+    """More records than one piece of the evaluation holds (2^24): ln w_theta of a path is the same bits in
+    whichever piece its records lie."""
+    print("[case] 2^24 records and more", flush=True)
+    few, lw0 = _records(fpt, 100_000, 40)
+    copies = 200
+    rec = np.tile(few.rec, copies)
+    rec["pn"] += np.repeat(np.arange(copies, dtype=np.uint32) * np.uint32(40 << 5), few.rec.size)
+    off = np.concatenate([[0]] + [few.off[1:] + np.uint64(c * few.rec.size) for c in range(copies)]).astype(np.uint64)
+    assert rec.size > 1 << 24
+    p = W.c4_params(7)
+    z = np.zeros(40 * copies)
+    many = O.Records(rec, off, z.astype(np.uint64), z, z.astype(np.int32))
+    _, grad, lwt = fpt.proposal_loss_grad(p, 196.0, 1e-3, p.values_f32(), few, lw0, 100.0, 1)
+    _, grad_n, lwt_n = fpt.proposal_loss_grad(p, 196.0, 1e-3, p.values_f32(), many, np.tile(lw0, copies), 100.0, 1)
+    assert np.array_equal(lwt_n.reshape(copies, 40), np.broadcast_to(lwt, (copies, 40)))
+    # the weights of each path are those of the few paths over the number of copies: the same gradient, with
+    # the binary32 sums of a workgroup 200 times as long (2e5 terms of either sign, within 2^-24 each)
+    assert np.abs(grad_n - grad).max() <= 1e-3 * np.abs(grad).max()
