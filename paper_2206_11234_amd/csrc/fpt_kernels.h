@@ -65,9 +65,9 @@ struct StepArgs {
     uint32_t lane_cap;            // lanes of a wave that take runs (below 64 the queue is empty from the start)
     uint32_t cus, turn;           // CUs; waves by which the order turns between the workgroups of one
     uint32_t spread;              // first ids: 1 a lane of every wave in turn, 0 wave by wave
-    uint32_t bump_far;            // bump potential: groups may leave its exponential out (group4)
     const uint16_t *mlp_params;   // bfloat16 network shared by the batch (learned proposal)
     int32_t mlp_every;            // evaluate the network every 1, 4, 8 or 16 steps
+    uint32_t bump_far;            // bump potential: groups may leave its exponential out (group4)
 };
 
 // Per-instance merge metadata.

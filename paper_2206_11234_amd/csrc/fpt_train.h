@@ -30,9 +30,7 @@ struct RecordArgs {
     int32_t group;              // one record per group of 1, 4, 8 or 16 steps
     int32_t stride;             // keep the record of every stride-th group (g % stride == 0)
     int32_t mlp_every;
-    int32_t cus;                // compute units of the device
     uint32_t slots;             // paths per wave: 64, 32, 16 or 8
-    uint32_t bump_far;          // see StepArgs
     const uint16_t *mlp_params; // bfloat16 network of the sampling proposal
     const uint64_t *rec_off;    // n_paths + 1 record offsets
     TrainRec *rec;
@@ -40,6 +38,8 @@ struct RecordArgs {
     double *lw_out;
     int32_t *st_out;
     uint64_t *n_rec_out;        // records the replay produced (equals the slot when it matches)
+    int32_t cus;                // compute units of the device
+    uint32_t bump_far;          // see StepArgs
 };
 
 struct TrainArgs {
@@ -48,7 +48,6 @@ struct TrainArgs {
     const uint64_t *rec_off;    // n_paths + 1
     int32_t n_paths;
     int32_t n_part;             // workgroups of the backward pass
-    int32_t cus;                // compute units of the device
     int32_t objective;          // 0: log M2 (c ~ w_0 w_theta); 1: cross entropy (c ~ w_0)
     float temper;               // w_0 enters the path weights as w_0^temper
     float rec_weight;           // each record stands for this many groups (the record stride)
@@ -56,8 +55,6 @@ struct TrainArgs {
     MlpConsts mc;               // input normalisation, output scale, N*
     float dN;                   // binary32 dN
     float *r;                   // r_theta per record of a piece (eval_capacity)
-    int32_t path0;              // the piece's first path
-    uint64_t rec0;              // and its first record
     double *lw_theta;           // ln w_theta per path
     const double *lw0;          // ln w_0 per path (sampled)
     double n_total;             // runs drawn
@@ -65,6 +62,9 @@ struct TrainArgs {
     double *loss;               // log M2
     float *part;                // n_part x NET_N_PARAMS
     double *grad;               // NET_N_PARAMS
+    int32_t cus;                // compute units of the device
+    int32_t path0;              // the evaluation's piece: its first path
+    uint64_t rec0;              // and its first record
 };
 
 struct AdamArgs {
