@@ -87,3 +87,17 @@ def test_sum_of_squared_steps_is_the_exact_sum_rounded(fpt):
     assert exact > 2 ** 55
     assert res.sum_k2 == float(exact)
     assert res.total_steps == int(dump.k.astype(np.int64).sum())
+
+
+@pytest.mark.parametrize("extra", [-2, -1, 0, 1, 2])
+@pytest.mark.parametrize("block,wg_per_cu", [(64, 1), (256, 1)])
+def test_tables_at_the_edge_of_lds(fpt, block, wg_per_cu, extra):
+    """The largest tables that share a CU's 160 KiB with the lanes' stopped runs (16 B each), and the first
+    that go to global memory: 240 B a row with 16 subsets, 128 B an instance, in units of 256 B."""
+    lanes = fpt.device_cus() * wg_per_cu * block
+    rows = (160 * 1024 // wg_per_cu // 256 * 256 - 16 * block - 128) // 240
+    inst = W.Instance("flat", pot=W.POT_FLAT, V0=3 * (2 * math.pi) ** 2, phi_in=1.0, phi_end=0.0, phi_uv=1.5, dN=1e-2,
+                      bias=W.BIAS_NOISE_SCALED, A=-1.0, n_traj=lanes + 100, k_max=2000, edges=np.linspace(0.05, 3.0, rows - 4 + extra + 1))
+    print(f"[case] block {block} x {wg_per_cu}, {rows + extra} rows", flush=True)
+    res, _, _ = fpt.run(inst, 4, block=block, wg_per_cu=wg_per_cu, chunk=1)
+    assert_histogram_matches(res, O.histogram(O.simulate(to_model(inst), 4, inst.n_traj), inst.dN, inst.edges))

@@ -191,3 +191,100 @@ def test_log_weights_over_several_pieces(fpt):
     # the weights of each path are those of the few paths over the number of copies: the same gradient, with
     # the binary32 sums of a workgroup 200 times as long (2e5 terms of either sign, within 2^-24 each)
     assert np.abs(grad_n - grad).max() <= 1e-3 * np.abs(grad).max()
+
+
+@pytest.mark.parametrize("every", [1, 4, 8, 16])
+@pytest.mark.parametrize("n_inst", [1, 3])
+def test_learned_teams_against_full_waves(fpt, every, n_inst):
+    """A launch whose waves hold 64 runs each and refill (one workgroup of four waves per CU, more runs than
+    its lanes) evaluates the network on two blocks of 32 columns and draws each lane's normals itself, until
+    its waves drain into teams; launches of few runs are teams of 8, 16 and 32 from the start.  A run's every
+    bit is the same in both, for one instance and for several of different lengths."""
+    n_full = 70000 // n_inst + 1
+    base = dataclasses.replace(W.c4_instance(W.c4_params(3, eval_every=every), n_traj=n_full), phi_in=2.5, k_max=2000)
+    insts = [dataclasses.replace(base, stream=i, target_N=196.0 - 20.0 * i, k_max=2000 - 300 * i) for i in range(n_inst)]
+    print(f"[case] every={every} instances={n_inst} full", flush=True)
+    _, full, _ = fpt.run_batch(insts, 2, dump_n=n_full, block=256, wg_per_cu=1, chunk=1)
+    for n in (9, 5461, 11000, 22000):
+        print(f"[case] every={every} instances={n_inst} n={n}", flush=True)
+        _, few, _ = fpt.run_batch([W.with_runs(i, n) for i in insts], 2, dump_n=n)
+        for a, b in zip(few, full):
+            for name in ("k", "lw", "phi", "status"):
+                assert np.array_equal(getattr(a, name)[:n], getattr(b, name)[:n]), (n, name)
+
+
+@pytest.mark.parametrize("n_paths", [16385, 32769, 65537])
+@pytest.mark.parametrize("proposal,group,stride", [("fixed", 1, 1), ("fixed", 4, 3), ("fixed", 16, 1), ("bump", 4, 1), ("bump", 16, 2),
+                                                   ("network", 1, 2), ("network", 4, 1), ("network", 8, 1), ("network", 16, 2)])
+def test_records_of_many_paths(fpt, n_paths, proposal, group, stride):
+    """16, 32 and 64 paths a wave (8 a wave last up to 16384 paths, each further doubling one more), ragged
+    last waves among them."""
+    print(f"[case] {n_paths} paths {proposal} group {group} stride {stride}", flush=True)
+    inst = dataclasses.replace(W.c2(1)[3], phi_in=1.6, dN=1e-2, k_max=90)
+    if proposal == "bump":
+        inst = W.Instance("bump", pot=W.POT_QUADRATIC_BUMP, m=0.5, a=0.05, phi0=1.7, w=0.02, phi_in=2.0, phi_uv=6.0,
+                          bias=W.BIAS_NOISE_SCALED, A=1.0, dN=1.5e-2, n_traj=1, k_max=90)
+    elif proposal == "network":
+        v = np.zeros(W.MlpParams.N_PARAMS, np.float32)
+        v[4480] = 0.5
+        inst = dataclasses.replace(inst, bias=W.BIAS_MLP, A=0.0, target_N=196.0, mlp=W.MlpParams(v, out_scale=2.0, eval_every=group))
+    _check_records(fpt, inst, n_paths, group, stride)
+
+
+@pytest.mark.parametrize("n_paths", [9, 300])
+@pytest.mark.parametrize("group,stride", [(4, 1), (8, 4), (16, 3)])
+@pytest.mark.parametrize("a,w,wall", [(0.05, 0.05, True), (-0.02, 0.2, False)])
+def test_records_at_the_bump(fpt, n_paths, group, stride, a, w, wall):
+    """Paths that start far from the bump, cross it and end beyond it."""
+    print(f"[case] {n_paths} paths group {group} stride {stride} a={a} w={w}", flush=True)
+    _check_records(fpt, W.Instance("bump", pot=W.POT_QUADRATIC_BUMP, m=0.05, a=a, phi0=3.0, w=w, phi_in=5.0,
+                                   phi_uv=6.0 if wall else math.inf, bias=W.BIAS_NOISE_SCALED, A=1.0, dN=2e-3, n_traj=1, k_max=9000),
+                   n_paths, group, stride)
+
+
+def _check_records(fpt, inst, n_paths, group, stride):
+    ids = np.arange(n_paths, dtype=np.uint64) * np.uint64(3)
+    o = O.records(to_model(inst), 0, ids, group, stride)
+    g = fpt.proposal_records(inst, 0, ids, o.k, group, stride)
+    assert np.array_equal(g.k, o.k) and np.array_equal(g.lw, o.lw) and np.array_equal(g.status, o.status)
+    assert np.array_equal(g.off, o.off) and g.rec.tobytes() == o.rec.tobytes()
+
+
+@pytest.mark.parametrize("objective", [0, 1])
+def test_loss_and_gradient_beyond_one_grid(fpt, objective):
+    """More records than the evaluation's and the backward pass's grids hold at once (196 608 and 65 536 on
+    256 CUs), so that workgroups and waves take second and third tiles, with a ragged last one.
+
+    A gradient component is a sum over records of coef_e times a factor of at most F (below), each formed
+    from sums of 64 binary32 terms and added up along a chain of some hundred more: 256 2^-24 of the sum of
+    the terms' sizes bounds its error."""
+    print(f"[case] second tiles, objective {objective}", flush=True)
+    n_rec = 196608 + 65
+    recs, lw0 = _records(fpt, n_rec, 40)
+    p = W.c4_params(7, scale=1.5, out_scale=0.8)
+    theta = p.values_f32()
+    inst = W.c4_instance(p, n_traj=1)
+    loss, grad, lwt = fpt.proposal_loss_grad(p, inst.target_N, inst.dN, theta, recs, lw0, 100.0, objective)
+    loss_o, grad_o, lwt_o = O.loss_grad(to_model(inst), theta.astype(np.float64), recs, lw0, 100.0, objective)
+    th = theta.astype(np.float64)
+    W2, w3 = th[256:4352].reshape(64, 64), th[4416:4480]
+    r_max = abs(p.out_scale) * (np.abs(w3).sum() + abs(th[4480]))
+    a = lw0 + (lwt_o if objective == 0 else 0.0)
+    c = np.exp(a - a.max())
+    c /= c.sum()
+    n = (recs.rec["pn"] & 31).astype(np.float64)
+    H = np.abs(recs.rec["H"].astype(np.float64))
+    size = (r_max * n * inst.dN + H) * abs(p.out_scale)
+    x = 1.0 + max(np.abs((recs.rec["phi"] - p.in_mean[0]) * p.in_inv_scale[0]).max(),
+                  np.abs((recs.rec["k"] * inst.dN - p.in_mean[1]) * p.in_inv_scale[1]).max(),
+                  abs((inst.target_N - p.in_mean[2]) * p.in_inv_scale[2]))
+    F = max(1.0, np.abs(w3).max(), (np.abs(w3) @ np.abs(W2)).max() * x)
+    owner = (recs.rec["pn"] >> 5).astype(np.int64)
+    eps = 256.0 * 2.0 ** -24
+    # ln w_theta: sums of r H and r^2 n dN / 2
+    term = r_max * H + r_max ** 2 * n * inst.dN
+    assert np.all(np.abs(lwt - lwt_o) <= eps * np.bincount(owner, term, len(lw0)))
+    assert abs(loss - loss_o) <= eps * np.bincount(owner, term, len(lw0)).max() * (1.0 if objective == 0 else 2.0)
+    # the path weights follow ln w_theta
+    shift = 2.0 * np.abs(lwt - lwt_o).max() if objective == 0 else 0.0
+    assert np.abs(grad - grad_o).max() <= (eps + shift) * F * float((c[owner] * size).sum())
