@@ -467,11 +467,12 @@ __device__ __forceinline__ Steps4 steps4(const StepConsts &C, const F4 &z, float
     return S;
 }
 
-// Bump potential: whether the launch's groups may be taken without the bump, and whether the wave's
-// next one is (group4).  They may not where a run can get so far from the bump that (phi - phi0) / w^2
-// overflows: the bump's term is then infinity times 0, and leaving it out would give another field.
+// Bump potential: the least (phi - phi0)^2 / (2 w^2) at which a group may be taken without the bump, and
+// whether the wave's next one is (group4).  It is infinite, and every group is taken with the bump, where
+// a run can get so far from it that (phi - phi0) / w^2 overflows: the bump's term is then infinity times
+// 0, and leaving it out would give another field.
 struct BumpFar {
-    bool may;
+    float least;
     bool now = false;
 };
 
@@ -494,14 +495,14 @@ __device__ __forceinline__ uint64_t group4(const StepConsts &C, uint32_t j_cap, 
                                            uint64_t &running, Stopped *F, BumpFar &far, float *H = nullptr) {
     Steps4 S;
     if constexpr (POT == POT_QUADRATIC_BUMP) {
-        auto came_near = [&]() { return (__builtin_amdgcn_ballot_w64(!(S.near * C.inv_2w2 > BUMP_FAR)) & running) != 0; };
+        auto came_near = [&]() { return (__builtin_amdgcn_ballot_w64(!(S.near * C.inv_2w2 > far.least)) & running) != 0; };
         if (far.now) {
             S = steps4<POT, BIAS, P, WALL, true>(C, z, r_net, R, H);
             far.now = !came_near();
         }
         if (!far.now) {
             S = steps4<POT, BIAS, P, WALL, false>(C, z, r_net, R, H);
-            far.now = far.may && !came_near();
+            far.now = !came_near();
         }
     } else {
         S = steps4<POT, BIAS, P, WALL, false>(C, z, r_net, R, H);

@@ -67,7 +67,7 @@ struct StepArgs {
     uint32_t spread;              // first ids: 1 a lane of every wave in turn, 0 wave by wave
     const uint16_t *mlp_params;   // bfloat16 network shared by the batch (learned proposal)
     int32_t mlp_every;            // evaluate the network every 1, 4, 8 or 16 steps
-    uint32_t bump_far;            // bump potential: groups may leave its exponential out (group4)
+    float bump_far;               // bump potential: BumpFar::least
 };
 
 // Per-instance merge metadata.

@@ -179,7 +179,7 @@ __device__ __forceinline__ void fpt_step_body(const StepArgs &a) {
     // branch: with the choice, the refill's tests and the teams' around each group, six instances of
     // 1e5 runs took 186 ms (chosen by group, 214), now 166.
     int walls = WALL_ANY;
-    BumpFar far{a.bump_far != 0};   // bump potential: see group4
+    BumpFar far{a.bump_far};    // bump potential: see group4
     auto specialised = [&](auto f) {
         auto with = [&](auto p, auto wall) { f([&](const F4 &z) { (void)group4<POT, BIAS, p(), wall()>(C, j_cap, z, 0.0f, R, running, F, far); }); };
         using std::integral_constant;

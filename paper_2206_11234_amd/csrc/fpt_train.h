@@ -39,7 +39,7 @@ struct RecordArgs {
     int32_t *st_out;
     uint64_t *n_rec_out;        // records the replay produced (equals the slot when it matches)
     int32_t cus;                // compute units of the device
-    uint32_t bump_far;          // see StepArgs
+    float bump_far;             // see StepArgs
 };
 
 struct TrainArgs {

@@ -110,7 +110,7 @@ __global__ __launch_bounds__(256) void fpt_record_kernel(RecordArgs a) {
         return mc.out_scale * lane_read(team.fetch0, o);
     };
     const uint32_t odd_mask = normals_mask();
-    BumpFar far{a.bump_far != 0};   // bump potential: see group4
+    BumpFar far{a.bump_far};    // bump potential: see group4
     F4 batch{};
     float r_mlp = 0.0f;
     const int batch_mask = team.groups() - 1;

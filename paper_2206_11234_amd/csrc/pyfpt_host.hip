@@ -188,7 +188,7 @@ struct Prepared {
     TableLayout lay{};
     const uint16_t *mlp_params = nullptr;
     int mlp_every = 1;
-    bool bump_far = true;    // no run can get where the bump's (phi - phi0) / w^2 overflows
+    float bump_far = BUMP_FAR;  // infinite where a run can get where the bump's (phi - phi0) / w^2 overflows
     uint64_t v_total = 0;
     uint64_t counts_total = 0, values_total = 0;
     int pot = 0, bias = 0;
@@ -389,7 +389,7 @@ int prepare(const pyfpt_instance *ins, int n_inst, Prepared &P) {
             // the roundings
             const double top = wall ? C.phi_uv : C.phi_esc;
             const double reach = std::max(std::fabs(top - C.phi0), std::fabs(static_cast<double>(C.phi_end) - C.phi0));
-            P.bump_far = P.bump_far && reach * C.inv_w2 < 0.5 * std::numeric_limits<float>::max();
+            if (!(reach * C.inv_w2 < 0.5 * std::numeric_limits<float>::max())) P.bump_far = INFINITY;
         }
         D.stream = I.stream;
         D.n_bins = static_cast<uint32_t>(I.bins.n_bins);
@@ -665,7 +665,7 @@ int run_prepared(Device &d, const Prepared &P, uint64_t seed, const LaunchCfg &c
     sa.chunk = static_cast<uint32_t>(cfg.chunk);
     sa.lane_cap = static_cast<uint32_t>(shape.lane_cap);
     sa.spread = shape.spread ? 1u : 0u;
-    sa.bump_far = P.bump_far ? 1u : 0u;
+    sa.bump_far = P.bump_far;
     sa.cus = static_cast<uint32_t>(d.cus);
     sa.turn = static_cast<uint32_t>(std::max(1, 4 * d.cus / std::max(1, shape.n_wg)));
     sa.mlp_params = P.mlp_params;
@@ -1019,7 +1019,7 @@ int records_device(const Prepared &P, uint64_t seed, int group, int stride, cons
     ra.mlp_every = P.mlp_every;
     ra.cus = current_cus();
     ra.slots = record_slots(n_paths, ra.cus);
-    ra.bump_far = P.bump_far ? 1u : 0u;
+    ra.bump_far = P.bump_far;
     ra.mlp_params = P.mlp_params;
     ra.rec_off = d_off;
     ra.rec = d_rec;
