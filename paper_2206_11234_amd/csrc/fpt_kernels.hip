@@ -641,9 +641,9 @@ struct LseAcc {
 // The power sums of ln w are one chain over the slices in order: the lognormal estimate's upper error
 // is exp(u) - 1 with u up to some hundreds in bins of a few widely spread runs, u times the rounding of
 // the second moment, and folding partial sums into one another would round more often than adding the
-// slices' terms one by one.  Only the additions are in turn; the terms are formed by all threads (the
-// kernel with a tree for them 119 us at 1000 workgroups of 104 rows and 879 us at 13 056 rows, now 129
-// and 933).
+// slices' terms one by one.  Only the additions are in turn; the terms are formed by all threads, from
+// loads of which all but the counts are in flight together (with a tree for them the kernel took 120 us
+// at 1000 workgroups of 104 rows and 875 us at 13 056 rows, now 117 and 917).
 constexpr int MERGE_CELLS = 32, MERGE_SPLIT = 16, MERGE_BLOCK = MERGE_CELLS * MERGE_SPLIT;
 constexpr int MERGE_CHUNK = 2 * MERGE_SPLIT;        // slices whose terms are in LDS at a time
 
@@ -695,39 +695,27 @@ __global__ __launch_bounds__(MERGE_BLOCK) void fpt_merge_kernel(MergeArgs a) {
         // log-sum of w^2 and the moments of ln w per row
         const uint32_t r = (blockIdx.x - n_cell_blocks) * MERGE_CELLS + lc;
         const bool have = r < RT;
-        LseAcc l2;
         double c = NAN;             // shift of the first slice that has one
         int first = a.n_wg;
-        if (have)
+        if (have) {
+#pragma unroll 8
             for (int w = part; w < a.n_wg; w += MERGE_SPLIT) {
-                const unsigned char *sl = a.slices + static_cast<size_t>(w) * L.slice_bytes;
-                l2.add(reinterpret_cast<const double *>(sl + L.off_lse_w2)[r]);
-                const double cw = reinterpret_cast<const double *>(sl + L.off_shift)[r];
-                if (first == a.n_wg && !isnan(cw)) {
-                    first = w;
-                    c = cw;
-                }
+                const double cw = reinterpret_cast<const double *>(a.slices + static_cast<size_t>(w) * L.slice_bytes + L.off_shift)[r];
+                const bool take = first == a.n_wg && !isnan(cw);
+                first = take ? w : first;
+                c = take ? cw : c;
             }
-        for (int half = MERGE_SPLIT / 2; half >= 1; half >>= 1) {
-            red[0][tid] = l2.m;
-            red[1][tid] = l2.s;
-            red[2][tid] = static_cast<double>(first);
-            red[3][tid] = c;
-            __syncthreads();
-            if (part < half) {
-                const int o = tid + half * MERGE_CELLS;
-                l2.fold(red[0][o], red[1][o]);
-                if (red[2][o] < static_cast<double>(first)) {
-                    first = static_cast<int>(red[2][o]);
-                    c = red[3][o];
-                }
-            }
-            __syncthreads();
         }
-        if (part == 0) red[0][lc] = c;
+        red[0][tid] = static_cast<double>(first);
+        red[1][tid] = c;
         __syncthreads();
-        c = red[0][lc];
+        for (int q = 0; q < MERGE_SPLIT; ++q)
+            if (red[0][q * MERGE_CELLS + lc] < static_cast<double>(first)) {
+                first = static_cast<int>(red[0][q * MERGE_CELLS + lc]);
+                c = red[1][q * MERGE_CELLS + lc];
+            }
         __syncthreads();
+        LseAcc l2;
         // n values and their power sums about c, sum (x - c)^j = sum ((x - cw) + d)^j: the slices' terms
         // by all threads, MERGE_CHUNK slices at a time, then their sums in slice order, S_j by part j - 1
         double n = 0.0, S = 0.0;
@@ -738,16 +726,19 @@ __global__ __launch_bounds__(MERGE_BLOCK) void fpt_merge_kernel(MergeArgs a) {
                 const int at = u * MERGE_SPLIT + part, w = w0 + at;
                 double t1 = 0.0, t2 = 0.0, t3 = 0.0, t4 = 0.0;
                 if (have && w < a.n_wg) {
+                    // (all loads before the first test, so that they are in flight together)
                     const unsigned char *sl = a.slices + static_cast<size_t>(w) * L.slice_bytes;
+                    const double xw2 = reinterpret_cast<const double *>(sl + L.off_lse_w2)[r];
                     const double cw = reinterpret_cast<const double *>(sl + L.off_shift)[r];
+                    const double s1 = reinterpret_cast<const double *>(sl + L.off_s1)[r];
+                    const double s2 = reinterpret_cast<const double *>(sl + L.off_s2)[r];
+                    const double s3 = reinterpret_cast<const double *>(sl + L.off_s3)[r];
+                    const double s4 = reinterpret_cast<const double *>(sl + L.off_s4)[r];
+                    l2.add(xw2);
                     if (!isnan(cw)) {
                         double nw = 0.0;
                         for (uint32_t s = 0; s < J; ++s)
                             nw += static_cast<double>(reinterpret_cast<const uint32_t *>(sl + L.off_cnt)[s * RT + r]);
-                        const double s1 = reinterpret_cast<const double *>(sl + L.off_s1)[r];
-                        const double s2 = reinterpret_cast<const double *>(sl + L.off_s2)[r];
-                        const double s3 = reinterpret_cast<const double *>(sl + L.off_s3)[r];
-                        const double s4 = reinterpret_cast<const double *>(sl + L.off_s4)[r];
                         const double d = cw - c;
                         t4 = s4 + 4.0 * d * s3 + 6.0 * d * d * s2 + 4.0 * d * d * d * s1 + nw * d * d * d * d;
                         t3 = s3 + 3.0 * d * s2 + 3.0 * d * d * s1 + nw * d * d * d;
@@ -768,8 +759,19 @@ __global__ __launch_bounds__(MERGE_BLOCK) void fpt_merge_kernel(MergeArgs a) {
             }
             __syncthreads();
         }
-        red[0][tid] = n;
-        red[1][tid] = S;
+        for (int half = MERGE_SPLIT / 2; half >= 1; half >>= 1) {
+            red[0][tid] = l2.m;
+            red[1][tid] = l2.s;
+            red[2][tid] = n;
+            __syncthreads();
+            if (part < half) {
+                const int o = tid + half * MERGE_CELLS;
+                l2.fold(red[0][o], red[1][o]);
+                n += red[2][o];
+            }
+            __syncthreads();
+        }
+        red[0][tid] = S;
         __syncthreads();
         if (have && part == 0) {
             const MergeInst m = a.mi[inst_of_row(a.mi, a.n_inst, r)];
@@ -777,11 +779,10 @@ __global__ __launch_bounds__(MERGE_BLOCK) void fpt_merge_kernel(MergeArgs a) {
             const ResultLayout RL = result_layout(m.n_bins, J);
             double *V = a.values + m.values_off;
             V[RL.lse_w2 + lr] = l2.value();
-            for (int q = 1; q < MERGE_SPLIT; ++q) n += red[0][q * MERGE_CELLS + lc];
             if (n > 0.0) {
                 const double mu = S / n;
-                const double e2 = red[1][MERGE_CELLS + lc] / n, e3 = red[1][2 * MERGE_CELLS + lc] / n,
-                             e4 = red[1][3 * MERGE_CELLS + lc] / n;
+                const double e2 = red[0][MERGE_CELLS + lc] / n, e3 = red[0][2 * MERGE_CELLS + lc] / n,
+                             e4 = red[0][3 * MERGE_CELLS + lc] / n;
                 V[RL.mean_lnw + lr] = c + mu;
                 V[RL.m2_lnw + lr] = e2 - mu * mu;
                 V[RL.m3_lnw + lr] = e3 - 3.0 * mu * e2 + 2.0 * mu * mu * mu;
