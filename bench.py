@@ -25,7 +25,7 @@ if ROOT not in sys.path:
 # VALU issue peak of MI355X: 256 CUs x 4 SIMDs x 32 lanes per clock x 2.4 GHz = 7.86e13
 # lane-ops/s, i.e. the 157.3 TFLOP/s fp32 vector peak divided by 2 flops per FMA.  In the step
 # kernel every VALU instruction kind it uses issues at about that rate: its counters show 61.9 VALU
-# instructions per wave-step in 142.9 SIMD-cycles, 30.4 of them fma, 32x32 integer multiplies,
+# instructions per wave-step in 142.0 SIMD-cycles, 30.4 of them fma, 32x32 integer multiplies,
 # f64 adds and conversions; at two issue slots for those the wave-step would need 184.6 cycles.
 PEAK_LANE_OPS = 256 * 4 * 32 * 2.4e9
 # MI355X binary32 vector peak (packed FMA on every lane), for the FLOP reading of the roofline
@@ -51,7 +51,7 @@ OPS_PER_STEP = (37 + 118 + 87) / 4
 # + round) and every selection pilot seed (those + 2^30 + c), so the evaluated proposal does not
 # depend on the evaluation's noise.
 EVAL_SEED = 99991
-TRAFFIC = (519111.375 * 1.99994 + 2879290.6875 * 1.0) * 1024
+TRAFFIC = (521524.875 * 1.99994 + 3069716.90625 * 1.0) * 1024
 
 
 def parse():

@@ -170,7 +170,10 @@ typedef struct pyfpt_instance {
  *   rel_err_ln_lo[B], rel_err_ln_hi[B]
  *                      its error (eq. eq_log_normal_bin_pdf_reconstrcuted_error_maximum_likelihood,
  *                      the Cox interval): P_hat (1 - rel_lo) .. P_hat (1 + rel_hi), rel = |exp(-+u) - 1|,
- *                      u = sqrt(s^2/n_j + s^4/(2 n_j - 2))
+ *                      u = sqrt(s^2/n_j + s^4/(2 n_j - 2)).  s^2 carries a few roundings of the order
+ *                      in which the runs were summed, and rel_hi u times as much of them relative:
+ *                      in bins of a few widely spread runs, where u is some hundreds and rel_hi may
+ *                      exceed 1e150, two launches of the same runs agree to about 4e-13 of it
  *   normal_p[B]        p-value of D'Agostino and Pearson's K^2 normality test of ln w in the bin
  *                      (skewness test of D'Agostino 1970, kurtosis test of Anscombe and Glynn 1983,
  *                      K^2 ~ chi^2 with 2 degrees of freedom; NaN for n_j < 8).  The paper accepts
@@ -216,12 +219,15 @@ typedef struct pyfpt_dump {
 typedef struct pyfpt_options {
     void *stream;                    /* hipStream_t; NULL = null stream */
     int32_t block;                   /* threads per workgroup (64..1024, multiple of 64; <= 256 for the
-                                        learned bias); 0 = autotune */
-    int32_t chunk;                   /* queue claim multiplier per wave (>= 1); 0 = autotune */
-    int32_t wg_per_cu;               /* persistent workgroups per CU; 0 = autotune.  Autotuning takes place
-                                        where there are more runs than the largest shape has lanes; a
-                                        launch with fewer runs than its shape's lanes takes fewer or
-                                        smaller workgroups than block and wg_per_cu say */
+                                        learned bias); 0 = chosen by the library */
+    int32_t chunk;                   /* queue claim multiplier per wave (>= 1); 0 = chosen */
+    int32_t wg_per_cu;               /* persistent workgroups per CU, at most 2048 threads with block;
+                                        0 = chosen.  With more runs than the largest shape has lanes, the
+                                        closed-form biases' shape is tuned by short launches; otherwise,
+                                        and for the learned bias, it is a fixed one.  A field given on its
+                                        own bounds the others chosen.  A launch with fewer runs than its
+                                        shape's lanes takes fewer or smaller workgroups than block and
+                                        wg_per_cu say */
     int32_t use_graph;               /* capture the launch sequence in a hipGraph and replay it */
     void *workspace;                 /* device scratch; NULL = library-managed */
     size_t workspace_bytes;

@@ -125,7 +125,8 @@ __device__ __forceinline__ float sqrt_f32(float x) {
 // Two words at a time, one operation of each in turn: a wave's instruction that needs the one before
 // it waits 9 cycles, an independent one 5, and the compiler, which takes every operation to be ready
 // at once, orders one chain after the other (a group of steps by the count 1840 cycles of a lone wave,
-// now 1450; 70 000 runs on the bump, two waves per SIMD, 51.8 ms, now 48.4; four waves per SIMD hide it).
+// now 1450; 70 000 runs on the bump, one or two waves per SIMD, 51.8 ms, now 48.1; four waves per SIMD
+// hide it).
 __device__ __forceinline__ void in_turn(float x, float y) { asm volatile("" ::"v"(x), "v"(y)); }
 __device__ __forceinline__ void in_turn(uint32_t x, uint32_t y) { asm volatile("" ::"v"(x), "v"(y)); }
 
@@ -489,7 +490,8 @@ struct BumpFar {
 // Bump potential: far.now tells whether the wave's runs were all far from the bump in the last group;
 // then this one is taken without it (65 instructions a step instead of 108), and again with it if a
 // run came near.  The rule is the wave's, as a divergent step would issue both; it pays where the
-// wave's runs move together (70 000 runs that all fit the launch: 60.3 ms, then 52.6).
+// wave's runs move together (70 000 runs that all fit the launch: 60.3 ms without
+// the rule, 52.6 with it; now 48.1).
 template <int POT, int BIAS, int P = 0, int WALL = WALL_ANY>
 __device__ __forceinline__ uint64_t group4(const StepConsts &C, uint32_t j_cap, const F4 &z, float r_net, RunState &R,
                                            uint64_t &running, Stopped *F, BumpFar &far, float *H = nullptr) {

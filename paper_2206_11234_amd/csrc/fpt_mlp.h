@@ -258,7 +258,7 @@ __device__ __forceinline__ void act_to_operands16(const f32x16 &d0, const f32x16
 // K-block's eight units (a shift by 8 lanes within the rows of 16, then the swap of rows), so that a
 // lane has 8 activations a layer.  A wave alone on its SIMD issues one instruction per 5 cycles, and
 // these are most of its evaluation (with loops of their own for the passes, 60 000 runs evaluated every
-// 4 steps: 105 ms, now 74).
+// 4 steps: 105 ms, now 64 to 76 by box and seed).
 __device__ __forceinline__ void act_to_operands8(const f32x16 &d0, const f32x16 &d1, bf16x8 b[5]) {
     typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));

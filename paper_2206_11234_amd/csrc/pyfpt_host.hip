@@ -533,6 +533,11 @@ int resident_per_cu(const Prepared &P, const LaunchCfg &c) {
 // than the chain of dependent operations of one step (about 130 cycles).  500 direct runs of 5.8e3
 // steps took 1.18 ms at 64 runs per wave (whole call) and 0.65 ms at 8 (now 0.46); 2e5
 // diffusion-dominated runs, whose last ones end on teams, 14.7 and 8.7 ms (now 7.2).
+// The counts are those of the quadratic step.  The bump's step is longer (65 instructions far from it,
+// 108 near it) and the power law has a second Newton chain, but the balance falls the same way: of 64,
+// 32, 16 and 8 runs per wave, 2000, 20 000, 70 000 and 130 000 runs on the bump take 3.34 / 2.88 / 2.48 /
+// 2.23, 3.40 / 2.87 / 2.68 / 3.27, 3.82 / 4.46 / 5.61 / 5.58 and 3.97 / 5.65 / 5.69 / 5.67 ms, and the rule
+// chooses the fastest or one within 4 %; with the power law the same.
 Shape launch_shape(const Device &d, const Prepared &P, const LaunchCfg &c) {
     Shape s;
     s.block = c.block;
@@ -579,8 +584,10 @@ Shape launch_shape(const Device &d, const Prepared &P, const LaunchCfg &c) {
     for (uint32_t i : P.order)
         if (2.0 * P.inst[i].k_center >= P.inst[P.order[0]].k_center) longest += P.inst[i].n_traj;
     s.spread = longest * 2 <= lanes;
-    // tables go to LDS where the workgroups that share a CU can all hold theirs, beside the
-    // learned sampler's copy of the network's operand tiles
+    // tables go to LDS where the workgroups that share a CU can all hold theirs, beside the lanes'
+    // stopped runs (16 B a thread) and the learned sampler's copy of the network's operand tiles.  In
+    // global memory 4e5 runs of 200 steps took 1.38 ms (311 rows, 512 threads x 2) against 1.16 in LDS
+    // (302 rows), of 1e3 steps 2.58 against 2.54.
     const size_t share = std::min<size_t>(d.max_lds, 160 * 1024 / static_cast<size_t>(std::max(1, (s.n_wg + d.cus - 1) / d.cus)));
     const size_t other = sizeof(Stopped) * s.block + (P.bias == PYFPT_BIAS_MLP ? fpt::MLP_TILE_LDS_BYTES : 0);
     s.lds = P.lay.slice_bytes + other <= share;
@@ -1135,7 +1142,7 @@ int pyfpt_workspace_size(const pyfpt_instance *inst, int32_t n_inst, const pyfpt
             c.wg_per_cu = opt->wg_per_cu;
             c.chunk = opt->chunk;
         }
-        if (c.wg_per_cu <= 0) c.wg_per_cu = 8;   // the largest grid the autotuner may pick
+        if (c.wg_per_cu <= 0) c.wg_per_cu = 8;   // twice the largest plan: room for a shape given at the run alone
         resolve_cfg(P, c);
         *bytes = ws_map(P, d->cus * c.wg_per_cu).total;
         return PYFPT_OK;
